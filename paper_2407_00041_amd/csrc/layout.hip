@@ -3,9 +3,8 @@
 // of Sec. 4.5, here with one 16-byte vector per (block, site)), and the
 // reduced-precision copies of the operator data.
 //
-// Each thread owns one site: it reads the site's contiguous canonical record
-// (whole cache lines per wavefront) and writes each native component at
-// consecutive sites across the wavefront.
+// The operator kernels give each thread one site; the spinor kernels turn tiles
+// of sites through LDS.
 #include <algorithm>
 #include <cstring>
 
@@ -13,101 +12,126 @@
 
 namespace wd {
 
-// canonical spinor [V][12] c128 (one rhs) -> native
+// Spinors move in tiles of kTileSites sites through LDS: on the canonical side
+// the work-group's 256 threads read or write the tile's 12 x 64 entries as one
+// contiguous run, on the native side wave w the components of its share at 64
+// consecutive sites, so both sides move whole cache lines.  (One thread per
+// site left every canonical access 192 B from its neighbour lane's: 64 lines
+// per instruction.)  The pitch of 13 entries per site keeps the column accesses
+// free of bank conflicts.  Bound by HBM.
+constexpr int kTileSites = 64;
+constexpr int kTilePitch = 13;
+constexpr int kTileThreads = 256;
+
+// canonical spinor [V][12] c128 (one rhs per blockIdx.y) -> native
 template <int P>
-__global__ __launch_bounds__(256) void pack_kernel(void *__restrict__ nat, const double2 *__restrict__ can,
-                                                   int V, size_t rhs_bytes) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    const double2 *src = can + (size_t)blockIdx.y * 12 * V + (size_t)12 * s;
+__global__ __launch_bounds__(kTileThreads) void pack_kernel(void *__restrict__ nat, const double2 *__restrict__ can,
+                                                            int V, size_t rhs_bytes) {
+    __shared__ d2v tile[kTileSites * kTilePitch];
+    const int s0 = blockIdx.x * kTileSites, n = min(kTileSites, V - s0);
+    const d2v *src = reinterpret_cast<const d2v *>(can) + (size_t)blockIdx.y * 12 * V + (size_t)12 * s0;
     char *dst = static_cast<char *>(nat) + (size_t)blockIdx.y * rhs_bytes;
-    if (P == WDIRAC_F64) {
-        double2 *o = reinterpret_cast<double2 *>(dst);
 #pragma unroll
-        for (int k = 0; k < 12; k++) o[(size_t)k * V + s] = src[k];
+    for (int j = 0; j < 12 * kTileSites / kTileThreads; j++) {
+        const int e = j * kTileThreads + threadIdx.x;
+        if (e < 12 * n) tile[e / 12 * kTilePitch + e % 12] = src[e];
+    }
+    __syncthreads();
+    const int l = threadIdx.x & (kTileSites - 1), w = threadIdx.x / kTileSites, s = s0 + l;
+    if (l >= n) return;
+    const d2v *v = tile + l * kTilePitch;
+    if (P == WDIRAC_F64) {
+        d2v *o = reinterpret_cast<d2v *>(dst);
+#pragma unroll
+        for (int j = 0; j < 3; j++) o[(size_t)(4 * j + w) * V + s] = v[4 * j + w];
     } else if (P == WDIRAC_F32) {
         float4 *o = reinterpret_cast<float4 *>(dst);
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            double2 a = src[2 * k], b = src[2 * k + 1];
+        for (int k = w; k < 6; k += 4) {
+            const d2v a = v[2 * k], b = v[2 * k + 1];
             o[(size_t)k * V + s] = make_float4((float)a.x, (float)a.y, (float)b.x, (float)b.y);
         }
     } else {
-        // F16S: scale = fp32(max |component|), q = fp16_rn(fp32(v) / scale)
-        float v[24];
+        // F16S: scale = fp32(max |component|), q = fp16_rn(fp32(v) / scale); waves 0-2 one vector of four
+        // components each, wave 3 the scale
         float m = 0.f;
 #pragma unroll
         for (int k = 0; k < 12; k++) {
-            double2 a = src[k];
-            v[2 * k] = (float)a.x;
-            v[2 * k + 1] = (float)a.y;
-            m = fmaxf(m, fmaxf(fabsf(v[2 * k]), fabsf(v[2 * k + 1])));
+            const d2v a = v[k];
+            m = fmaxf(m, fmaxf(fabsf((float)a.x), fabsf((float)a.y)));
         }
-        half8 *o = reinterpret_cast<half8 *>(dst);
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
+        if (w < 3) {
             half8 q;
 #pragma unroll
-            for (int j = 0; j < 8; j++) q[j] = m > 0.f ? (_Float16)(v[8 * k + j] / m) : (_Float16)0.f;
-            o[(size_t)k * V + s] = q;
+            for (int j = 0; j < 4; j++) {
+                const d2v a = v[4 * w + j];
+                q[2 * j] = m > 0.f ? (_Float16)((float)a.x / m) : (_Float16)0.f;
+                q[2 * j + 1] = m > 0.f ? (_Float16)((float)a.y / m) : (_Float16)0.f;
+            }
+            reinterpret_cast<half8 *>(dst)[(size_t)w * V + s] = q;
+        } else {
+            reinterpret_cast<float *>(dst + (size_t)48 * V)[s] = m;
         }
-        reinterpret_cast<float *>(dst + (size_t)48 * V)[s] = m;
     }
 }
 
 template <int P>
-__global__ __launch_bounds__(256) void unpack_kernel(double2 *__restrict__ can, const void *__restrict__ nat,
-                                                     int V, size_t rhs_bytes) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    double2 *dst = can + (size_t)blockIdx.y * 12 * V + (size_t)12 * s;
+__global__ __launch_bounds__(kTileThreads) void unpack_kernel(double2 *__restrict__ can, const void *__restrict__ nat,
+                                                              int V, size_t rhs_bytes) {
+    __shared__ d2v tile[kTileSites * kTilePitch];
+    const int s0 = blockIdx.x * kTileSites, n = min(kTileSites, V - s0);
+    d2v *dst = reinterpret_cast<d2v *>(can) + (size_t)blockIdx.y * 12 * V + (size_t)12 * s0;
     const char *src = static_cast<const char *>(nat) + (size_t)blockIdx.y * rhs_bytes;
-    if (P == WDIRAC_F64) {
-        const double2 *i = reinterpret_cast<const double2 *>(src);
+    const int l = threadIdx.x & (kTileSites - 1), w = threadIdx.x / kTileSites, s = s0 + l;
+    d2v *v = tile + l * kTilePitch;
+    if (l < n) {
+        if (P == WDIRAC_F64) {
+            const d2v *i = reinterpret_cast<const d2v *>(src);
 #pragma unroll
-        for (int k = 0; k < 12; k++) dst[k] = i[(size_t)k * V + s];
-    } else if (P == WDIRAC_F32) {
-        const float4 *i = reinterpret_cast<const float4 *>(src);
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            float4 a = i[(size_t)k * V + s];
-            dst[2 * k] = make_double2(a.x, a.y);
-            dst[2 * k + 1] = make_double2(a.z, a.w);
-        }
-    } else {
-        const half8 *i = reinterpret_cast<const half8 *>(src);
-        float m = reinterpret_cast<const float *>(src + (size_t)48 * V)[s];
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            half8 q = i[(size_t)k * V + s];
+            for (int j = 0; j < 3; j++) v[4 * j + w] = i[(size_t)(4 * j + w) * V + s];
+        } else if (P == WDIRAC_F32) {
+            const float4 *i = reinterpret_cast<const float4 *>(src);
+            for (int k = w; k < 6; k += 4) {
+                const float4 a = i[(size_t)k * V + s];
+                v[2 * k] = d2v{a.x, a.y};
+                v[2 * k + 1] = d2v{a.z, a.w};
+            }
+        } else if (w < 3) {
+            const half8 q = reinterpret_cast<const half8 *>(src)[(size_t)w * V + s];
+            const float m = reinterpret_cast<const float *>(src + (size_t)48 * V)[s];
 #pragma unroll
             for (int j = 0; j < 4; j++)
-                dst[4 * k + j] = make_double2((double)(m * (float)q[2 * j]), (double)(m * (float)q[2 * j + 1]));
+                v[4 * w + j] = d2v{(double)(m * (float)q[2 * j]), (double)(m * (float)q[2 * j + 1])};
         }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 12 * kTileSites / kTileThreads; j++) {
+        const int e = j * kTileThreads + threadIdx.x;
+        if (e < 12 * n) dst[e] = tile[e / 12 * kTilePitch + e % 12];
     }
 }
 
 hipError_t pack_launch(void *nat, const double *can, int nrhs, int prec, int V, hipStream_t st) {
-    dim3 grid((V + 255) / 256, nrhs);
+    const dim3 grid((V + kTileSites - 1) / kTileSites, nrhs), blk(kTileThreads);
     size_t rb = field_rhs_bytes(prec, V);
     const double2 *c = reinterpret_cast<const double2 *>(can);
     switch (prec) {
-    case WDIRAC_F64: hipLaunchKernelGGL(pack_kernel<WDIRAC_F64>, grid, dim3(256), 0, st, nat, c, V, rb); break;
-    case WDIRAC_F32: hipLaunchKernelGGL(pack_kernel<WDIRAC_F32>, grid, dim3(256), 0, st, nat, c, V, rb); break;
-    case WDIRAC_F16S: hipLaunchKernelGGL(pack_kernel<WDIRAC_F16S>, grid, dim3(256), 0, st, nat, c, V, rb); break;
+    case WDIRAC_F64: hipLaunchKernelGGL(pack_kernel<WDIRAC_F64>, grid, blk, 0, st, nat, c, V, rb); break;
+    case WDIRAC_F32: hipLaunchKernelGGL(pack_kernel<WDIRAC_F32>, grid, blk, 0, st, nat, c, V, rb); break;
+    case WDIRAC_F16S: hipLaunchKernelGGL(pack_kernel<WDIRAC_F16S>, grid, blk, 0, st, nat, c, V, rb); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 hipError_t unpack_launch(double *can, const void *nat, int nrhs, int prec, int V, hipStream_t st) {
-    dim3 grid((V + 255) / 256, nrhs);
+    const dim3 grid((V + kTileSites - 1) / kTileSites, nrhs), blk(kTileThreads);
     size_t rb = field_rhs_bytes(prec, V);
     double2 *c = reinterpret_cast<double2 *>(can);
     switch (prec) {
-    case WDIRAC_F64: hipLaunchKernelGGL(unpack_kernel<WDIRAC_F64>, grid, dim3(256), 0, st, c, nat, V, rb); break;
-    case WDIRAC_F32: hipLaunchKernelGGL(unpack_kernel<WDIRAC_F32>, grid, dim3(256), 0, st, c, nat, V, rb); break;
-    case WDIRAC_F16S: hipLaunchKernelGGL(unpack_kernel<WDIRAC_F16S>, grid, dim3(256), 0, st, c, nat, V, rb); break;
+    case WDIRAC_F64: hipLaunchKernelGGL(unpack_kernel<WDIRAC_F64>, grid, blk, 0, st, c, nat, V, rb); break;
+    case WDIRAC_F32: hipLaunchKernelGGL(unpack_kernel<WDIRAC_F32>, grid, blk, 0, st, c, nat, V, rb); break;
+    case WDIRAC_F16S: hipLaunchKernelGGL(unpack_kernel<WDIRAC_F16S>, grid, blk, 0, st, c, nat, V, rb); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
