@@ -44,13 +44,15 @@ template <typename T> __device__ __forceinline__ cx<T> mk(T r, T i) { return {r,
 template <typename T> __device__ __forceinline__ cx<T> operator+(cx<T> a, cx<T> b) { return {a.r + b.r, a.i + b.i}; }
 template <typename T> __device__ __forceinline__ cx<T> operator-(cx<T> a, cx<T> b) { return {a.r - b.r, a.i - b.i}; }
 template <typename T> __device__ __forceinline__ cx<T> operator*(T s, cx<T> a) { return {s * a.r, s * a.i}; }
+// Products are written as explicit fused multiply-adds, so that their rounding does not depend on how the compiler
+// contracts the code around them (the kernels' register blocks and work orders give the same bits).
 // a * b
 template <typename T> __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
-    return {a.r * b.r - a.i * b.i, a.r * b.i + a.i * b.r};
+    return {fma(-a.i, b.i, a.r * b.r), fma(a.i, b.r, a.r * b.i)};
 }
 // conj(a) * b
 template <typename T> __device__ __forceinline__ cx<T> cjmul(cx<T> a, cx<T> b) {
-    return {a.r * b.r + a.i * b.i, a.r * b.i - a.i * b.r};
+    return {fma(a.i, b.i, a.r * b.r), fma(-a.i, b.r, a.r * b.i)};
 }
 // acc + a * b
 template <typename T> __device__ __forceinline__ cx<T> cfma(cx<T> acc, cx<T> a, cx<T> b) {

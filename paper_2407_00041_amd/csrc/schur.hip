@@ -47,41 +47,37 @@ __device__ __forceinline__ int parity_site(const Geom &g, int i, int p, int c[4]
     return ((c[0] * g.n[1] + c[1]) * g.n[2] + c[2]) * g.n[3] + c[3];
 }
 
-// Fence between hops.  The kernel is one basic block, so the compiler would
-// issue every hop's loads first and do all the arithmetic afterwards (all
-// eight hops in flight, far beyond the register file).  The empty asm takes
-// the accumulators as in/out operands, so a hop's arithmetic must be done
-// before it, and clobbers memory, so the next hop's loads stay after it.
-// WD_PARITY_FENCE = 1: a fence after every hop; 2: after each direction's pair of hops.
-#ifndef WD_PARITY_FENCE
-#define WD_PARITY_FENCE 1
-#endif
-template <typename T, int NR>
-__device__ __forceinline__ void hop_boundary(cx<T> (&acc)[NR][12], int level = 1) {
-    if (level < WD_PARITY_FENCE) return;
-#pragma unroll
-    for (int r = 0; r < NR; r++)
-#pragma unroll
-        for (int k = 0; k < 12; k++) asm volatile("" : "+v"(acc[r][k].r), "+v"(acc[r][k].i) : : "memory");
-    __builtin_amdgcn_sched_barrier(0);
+// Launch shapes.  What bounds these kernels is the traffic between the L2s and the fabric: a spinor is read by
+// eight sites, and an XCD streams its 4 MB L2 over in about 5 us, so the uses have to fall together.  Three things
+// serve that, each measured per application of S (48^3 x 96 down to 8^4, two-row links, compact clover, us):
+//  - hops in flight: the loads of several hops are issued together (parity_fence), which shortens a wave's life,
+//    even where the registers then allow fewer waves.  64 x 32^3, hop by hop against the value chosen: FP32 pair
+//    748 -> 619, FP16S pair 335 -> 308, FP16S single 213 -> 200; FP64 pair (column walk) 1403 -> 1380.  A fence
+//    every 8 hops spills in pairs and is slower.
+//  - right-hand sides of one tile run one after the other on the same XCD, so links and A come from its L2: four
+//    right-hand sides, pairs, FP64 2840 -> 2301, FP32 1495 -> 1150, FP16S 655 -> 578.
+//  - right-hand sides per lane: a pair shares its links and A in registers, but halves the waves; below 2^18
+//    site-right-hand-sides (a few waves per SIMD) one per lane is faster: FP64 16^4, two: 47 -> 43; 8^4, two:
+//    25 -> 17; FP16S 16^4, two: 23 -> 17, four: 25 -> 23; above it pairs are: FP16S 32 x 16^2 x 32, two: 49 -> 43.
+//    Four per lane gained 4 % at 48^3 x 96 and lost up to 15 % below.
+// The arithmetic of a right-hand side is the same in every shape (explicit multiply-adds), so results do not depend
+// on how right-hand sides are grouped.
+constexpr int kParMax = 16;  // right-hand sides per launch
+constexpr int kParChunk = 4;  // T-slices per chunk of the column walk (kParChunk / 2 sites per lane)
+constexpr long long kParPairs = 1LL << 18;
+inline int rhs_per_lane(long long V, size_t n) { return n >= 2 && V * (long long)n > kParPairs ? 2 : 1; }
+// FP64 above 2^17 sites walks T columns (parity_column_kernel); below it the columns leave the chip idle: S of a
+// pair at 16^4 96 us against 47, at 32 x 16^2 x 32 185 against 204.  At FP32 the column walk is slower than the
+// site kernel with four hops in flight (64 x 32^3 pair 674 against 619), at FP16S too.
+inline bool column_walk(int prec, int V) { return prec == WDIRAC_F64 && V > 1 << 17; }
+// hops between two fences
+template <int P, int NR> constexpr int parity_fence() {
+    return P == WDIRAC_F64 ? (NR == 1 ? 2 : 1) : (P == WDIRAC_F16S && NR == 1) ? 8 : 4;
 }
-
-// Right-hand sides of one launch: a work-group row (blockIdx.y) takes NR
-// consecutive entries, so each lane loads its links and A(x) or A(x)^{-1}
-// once for all of them.
-constexpr int kParMax = 16;
-constexpr int kParNr = 2;  // right-hand sides per lane
-// FP16S with at least four right-hand sides in a launch: four per lane (147-151 VGPRs, 3 waves/SIMD instead of
-// 4), so a lane's links and A or A^-1 serve four of them (measured at 48^3 x 96: S 0.84 -> 0.77 ms per RHS on
-// 4 RHS).  With two or three the idle slots would cost the occupancy for nothing (0.82 -> 0.89 ms per launch on 2).
-constexpr int kParNrF16 = 4;
-#ifndef WD_PARITY_COLUMN
-#define WD_PARITY_COLUMN 1
-#endif
-#ifndef WD_PARITY_COLUMN_F16
-#define WD_PARITY_COLUMN_F16 0
-#endif
-constexpr bool kParColumnWalk = WD_PARITY_COLUMN != 0;
+// waves per SIMD the registers must allow: with these the kernels just do not spill
+template <int P, int NR> constexpr int parity_waves() {
+    return P == WDIRAC_F64 ? 2 : P == WDIRAC_F32 ? (NR == 1 ? 4 : 2) : 3;
+}
 struct ParityTable {
     void *out[kParMax];
     const void *self[kParMax];
@@ -89,9 +85,37 @@ struct ParityTable {
     int n;
 };
 
-template <int P, int MU, bool DAG, int ROWS, int NR>
-__device__ __forceinline__ void parity_hops(const OpData &d, const Geom &g, const ParityTable &tab, int r0, int nr,
-                                            int Vh, int s, const int c[4], bool apbc, typename Store<P>::T fh,
+// acc += f (1 + S gamma_mu)-projected hop of the neighbour at half-lattice index j of every right-hand side, through
+// the link U (DAGU: its adjoint)
+template <int P, int MU, int S, bool DAGU, int NR>
+__device__ __forceinline__ void parity_hop(const cx<typename Store<P>::T> U[9], const ParityTable &tab, int r0, int Vh,
+                                           int j, typename Store<P>::T f, cx<typename Store<P>::T> (&acc)[NR][12]) {
+    using T = typename Store<P>::T;
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+        cx<T> h[6], chi[6];
+        if constexpr (P == WDIRAC_F16S) {
+            // the projection takes the stored fp16 values as they are (exact in FP32); the site's scale and the
+            // factor f enter once, where the product is added
+            half8 q[3];
+            const T sc = Store<P>::load_raw(tab.hop[r0 + r], Vh, j, q);
+            project_half<MU, S>(q, h);
+            su3_mul<DAGU>(U, h, chi);
+            reconstruct_scaled<MU, S>(acc[r], chi, f * sc);
+        } else {
+            cx<T> p[12];
+            Store<P>::load_spinor(tab.hop[r0 + r], Vh, j, p);
+            project<MU, S>(p, h, f);
+            su3_mul<DAGU>(U, h, chi);
+            reconstruct<MU, S>(acc[r], chi);
+        }
+    }
+}
+
+// both hops of direction MU; FENCE: hops between two fences (1, 2, 4 or 8)
+template <int P, int MU, bool DAG, int ROWS, int NR, int FENCE>
+__device__ __forceinline__ void parity_hops(const OpData &d, const Geom &g, const ParityTable &tab, int r0, int Vh,
+                                            int s, const int c[4], bool apbc, typename Store<P>::T fh,
                                             cx<typename Store<P>::T> (&acc)[NR][12]) {
     using T = typename Store<P>::T;
     constexpr int SF = DAG ? +1 : -1;
@@ -103,33 +127,15 @@ __device__ __forceinline__ void parity_hops(const OpData &d, const Geom &g, cons
     {
         const T f = (MU == 0 && apbc && c[0] == g.n[0] - 1) ? -fh : fh;
         Store<P>::load_link(d.links, g.V, MU, s, U, ROWS);
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            if (r < nr) {
-                cx<T> p[12], h[6], chi[6];
-                Store<P>::load_spinor(tab.hop[r0 + r], Vh, sf >> 1, p);
-                project<MU, SF>(p, h, f);
-                su3_mul<false>(U, h, chi);
-                reconstruct<MU, SF>(acc[r], chi);
-            }
-        }
+        parity_hop<P, MU, SF, false, NR>(U, tab, r0, Vh, sf >> 1, f, acc);
     }
-    hop_boundary<T, NR>(acc, 1);
+    if (FENCE == 1) hop_boundary<T, NR>(acc);
     {
         const T f = (MU == 0 && apbc && c[0] == 0) ? -fh : fh;
         Store<P>::load_link(d.links, g.V, MU, sb, U, ROWS);
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            if (r < nr) {
-                cx<T> p[12], h[6], chi[6];
-                Store<P>::load_spinor(tab.hop[r0 + r], Vh, sb >> 1, p);
-                project<MU, SB>(p, h, f);
-                su3_mul<true>(U, h, chi);
-                reconstruct<MU, SB>(acc[r], chi);
-            }
-        }
+        parity_hop<P, MU, SB, true, NR>(U, tab, r0, Vh, sb >> 1, f, acc);
     }
-    hop_boundary<T, NR>(acc, 2);
+    if (MU == 3 || FENCE <= 2 || (MU == 1 && FENCE == 4)) hop_boundary<T, NR>(acc);
 }
 
 // SELF: 0 none, 1 the input, 2 A(x) times the input.  HOP: add fh * 2 * H hop
@@ -138,23 +144,24 @@ __device__ __forceinline__ void parity_hops(const OpData &d, const Geom &g, cons
 // between the two link formats costs the FP64 kernels spills).  NR: right-
 // hand sides per lane (register block).
 template <int P, bool DAG, int SELF, bool HOP, bool INV, int ROWS, int NR>
-__global__ __launch_bounds__(256) void parity_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int parity,
-                                                     int apbc, typename Store<P>::T fh, int tpr) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(parity_waves<P, NR>())))
+void parity_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int parity, int apbc, typename Store<P>::T fh,
+                   int tpr) {
     using T = typename Store<P>::T;
     const int Vh = g.V >> 1;
-    int i;
+    int i, r0;
     {
-        // block -> (XCD k, T-slice t, tile within the slice's k-th eighth)
+        // block -> (XCD k, T-slice t, tile within the slice's k-th eighth), the right-hand sides of a tile in turn
         const int hs = Vh / g.n[0];
-        const int k = blockIdx.x & 7, j = blockIdx.x >> 3;
+        const int groups = tab.n / NR;
+        const int k = blockIdx.x & 7, jj = blockIdx.x >> 3, j = jj / groups;
+        r0 = (jj - j * groups) * NR;
         const int t = j / tpr, tile = j - t * tpr;
-        const int r0 = t * hs + (int)(((long long)k * hs) >> 3);
-        const int r1 = t * hs + (int)(((long long)(k + 1) * hs) >> 3);
-        i = r0 + tile * (int)blockDim.x + (int)threadIdx.x;
-        if (i >= r1) return;
+        const int lo = t * hs + (int)(((long long)k * hs) >> 3);
+        const int hi = t * hs + (int)(((long long)(k + 1) * hs) >> 3);
+        i = lo + tile * (int)blockDim.x + (int)threadIdx.x;
+        if (i >= hi) return;
     }
-    const int r0 = (int)blockIdx.y * NR;
-    const int nr = min(NR, tab.n - r0);
     int c[4];
     const int s = parity_site(g, i, parity, c);
     cx<T> acc[NR][12];
@@ -165,7 +172,7 @@ __global__ __launch_bounds__(256) void parity_kernel(ParityTable tab, OpData d, 
     if (SELF == 1) {
 #pragma unroll
         for (int r = 0; r < NR; r++)
-            if (r < nr) Store<P>::load_spinor(tab.self[r0 + r], Vh, i, acc[r]);
+            Store<P>::load_spinor(tab.self[r0 + r], Vh, i, acc[r]);
     } else if (SELF == 2) {
 #pragma unroll
         for (int b = 0; b < 2; b++) {
@@ -174,11 +181,9 @@ __global__ __launch_bounds__(256) void parity_kernel(ParityTable tab, OpData d, 
                 Store<P>::load_clover_compact(d.clover, g.V, b, s, cr);
 #pragma unroll
                 for (int r = 0; r < NR; r++) {
-                    if (r < nr) {
-                        cx<T> x[6];
-                        Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
-                        clover_block_compact((T)d.diag, cr, x, &acc[r][6 * b]);
-                    }
+                    cx<T> x[6];
+                    Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
+                    clover_block_compact((T)d.diag, cr, x, &acc[r][6 * b]);
                 }
             } else {
                 T dd[6];
@@ -186,21 +191,19 @@ __global__ __launch_bounds__(256) void parity_kernel(ParityTable tab, OpData d, 
                 Store<P>::load_clover(d.clover, g.V, b, s, dd, uu);
 #pragma unroll
                 for (int r = 0; r < NR; r++) {
-                    if (r < nr) {
-                        cx<T> x[6];
-                        Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
-                        clover_block(dd, uu, x, &acc[r][6 * b]);
-                    }
+                    cx<T> x[6];
+                    Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
+                    clover_block(dd, uu, x, &acc[r][6 * b]);
                 }
             }
         }
     }
     if (HOP) {
-        hop_boundary<T, NR>(acc, 2);
-        parity_hops<P, 0, DAG, ROWS, NR>(d, g, tab, r0, nr, Vh, s, c, apbc != 0, fh, acc);
-        parity_hops<P, 1, DAG, ROWS, NR>(d, g, tab, r0, nr, Vh, s, c, apbc != 0, fh, acc);
-        parity_hops<P, 2, DAG, ROWS, NR>(d, g, tab, r0, nr, Vh, s, c, apbc != 0, fh, acc);
-        parity_hops<P, 3, DAG, ROWS, NR>(d, g, tab, r0, nr, Vh, s, c, apbc != 0, fh, acc);
+        hop_boundary<T, NR>(acc);
+        parity_hops<P, 0, DAG, ROWS, NR, parity_fence<P, NR>()>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 1, DAG, ROWS, NR, parity_fence<P, NR>()>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 2, DAG, ROWS, NR, parity_fence<P, NR>()>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 3, DAG, ROWS, NR, parity_fence<P, NR>()>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
     }
     if (INV) {
 #pragma unroll
@@ -210,18 +213,17 @@ __global__ __launch_bounds__(256) void parity_kernel(ParityTable tab, OpData d, 
             Store<P>::load_clover(cinv, g.V, b, s, dd, uu);
 #pragma unroll
             for (int r = 0; r < NR; r++) {
-                if (r < nr) {
-                    cx<T> y[6];
-                    clover_block(dd, uu, &acc[r][6 * b], y);
+                cx<T> y[6];
+                clover_block(dd, uu, &acc[r][6 * b], y);
 #pragma unroll
-                    for (int k = 0; k < 6; k++) acc[r][6 * b + k] = y[k];
-                }
+                for (int k = 0; k < 6; k++) acc[r][6 * b + k] = y[k];
             }
+            hop_boundary<T, NR>(acc);
         }
     }
 #pragma unroll
     for (int r = 0; r < NR; r++)
-        if (r < nr) Store<P>::store_spinor(tab.out[r0 + r], Vh, i, acc[r]);
+        Store<P>::store_spinor(tab.out[r0 + r], Vh, i, acc[r]);
 }
 
 // Column walk of the parity kernel: a lane takes one (z, y, x) column and the
@@ -231,11 +233,6 @@ __global__ __launch_bounds__(256) void parity_kernel(ParityTable tab, OpData d, 
 // U_T(t+1)^H (1 + s gamma_T) psi(t+1) is formed once and carried in registers
 // (one spinor load per site saved).  Work-groups are dealt as in the T-sweep
 // above: each XCD takes 1/8 of the columns of every T-chunk.
-#ifndef WD_PARITY_CHUNK
-#define WD_PARITY_CHUNK 4
-#endif
-constexpr int kParChunk = WD_PARITY_CHUNK;  // T-slices per chunk (kParChunk / 2 sites per lane)
-
 template <int P, bool DAG, int SELF, bool HOP, bool INV, int ROWS, int NR, int CH>
 __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpData d, const void *cinv, Geom g,
                                                             int parity, int apbc, typename Store<P>::T fh,
@@ -245,9 +242,11 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
     constexpr int SF = DAG ? +1 : -1;
     constexpr int SB = -SF;
     const int Vh = g.V >> 1, C = g.stride[0], nT = g.n[0];
-    int col, t0;
+    int col, t0, r0;
     {
-        const int k = blockIdx.x & 7, j = blockIdx.x >> 3;
+        const int groups = tab.n / NR;
+        const int k = blockIdx.x & 7, jj = blockIdx.x >> 3, j = jj / groups;
+        r0 = (jj - j * groups) * NR;
         const int tc = j / tpr, tile = j - tc * tpr;
         const int q0 = (int)(((long long)k * C) >> 3), q1 = (int)(((long long)(k + 1) * C) >> 3);
         col = q0 + tile * (int)blockDim.x + (int)threadIdx.x;
@@ -255,8 +254,6 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
         t0 = tc * CH;
     }
     const int t1 = min(t0 + CH, nT);
-    const int r0 = (int)blockIdx.y * NR;
-    const int nr = min(NR, tab.n - r0);
     int c[4];
     c[3] = col % g.n[3];
     c[2] = (col / g.n[3]) % g.n[2];
@@ -271,12 +268,10 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
         Store<P>::load_link(d.links, g.V, 0, tm * C + col, U, ROWS);
 #pragma unroll
         for (int r = 0; r < NR; r++) {
-            if (r < nr) {
-                cx<T> p[12], h[6];
-                Store<P>::load_spinor(tab.hop[r0 + r], Vh, (tm * C + col) >> 1, p);
-                project<0, SB>(p, h, f);
-                su3_mul<true>(U, h, chiT[r]);
-            }
+            cx<T> p[12], h[6];
+            Store<P>::load_spinor(tab.hop[r0 + r], Vh, (tm * C + col) >> 1, p);
+            project<0, SB>(p, h, f);
+            su3_mul<true>(U, h, chiT[r]);
         }
     }
     for (; t < t1; t += 2) {
@@ -290,7 +285,7 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
         if (SELF == 1) {
 #pragma unroll
             for (int r = 0; r < NR; r++)
-                if (r < nr) Store<P>::load_spinor(tab.self[r0 + r], Vh, i, acc[r]);
+                Store<P>::load_spinor(tab.self[r0 + r], Vh, i, acc[r]);
         } else if (SELF == 2) {
 #pragma unroll
             for (int b = 0; b < 2; b++) {
@@ -299,11 +294,9 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
                     Store<P>::load_clover_compact(d.clover, g.V, b, s, cr);
 #pragma unroll
                     for (int r = 0; r < NR; r++) {
-                        if (r < nr) {
-                            cx<T> x[6];
-                            Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
-                            clover_block_compact((T)d.diag, cr, x, &acc[r][6 * b]);
-                        }
+                        cx<T> x[6];
+                        Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
+                        clover_block_compact((T)d.diag, cr, x, &acc[r][6 * b]);
                     }
                 } else {
                     T dd[6];
@@ -311,16 +304,14 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
                     Store<P>::load_clover(d.clover, g.V, b, s, dd, uu);
 #pragma unroll
                     for (int r = 0; r < NR; r++) {
-                        if (r < nr) {
-                            cx<T> x[6];
-                            Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
-                            clover_block(dd, uu, x, &acc[r][6 * b]);
-                        }
+                        cx<T> x[6];
+                        Store<P>::load_half(tab.self[r0 + r], Vh, i, b, x);
+                        clover_block(dd, uu, x, &acc[r][6 * b]);
                     }
                 }
             }
         }
-        hop_boundary<T, NR>(acc, 2);
+        hop_boundary<T, NR>(acc);
         // T: the forward hop loads psi(t+1); the carried backward hop is added; when t + 2 is this lane's next
         // site, psi(t+1) also yields that site's backward half-spinor (the link U_T(t+1) loaded for it)
         {
@@ -333,24 +324,22 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
             if (next) Store<P>::load_link(d.links, g.V, 0, tp * C + col, Un, ROWS);
 #pragma unroll
             for (int r = 0; r < NR; r++) {
-                if (r < nr) {
-                    cx<T> p[12], h[6], chi[6];
-                    Store<P>::load_spinor(tab.hop[r0 + r], Vh, (tp * C + col) >> 1, p);
-                    project<0, SF>(p, h, ff);
-                    su3_mul<false>(U, h, chi);
-                    reconstruct<0, SF>(acc[r], chi);
-                    reconstruct<0, SB>(acc[r], chiT[r]);
-                    if (next) {
-                        project<0, SB>(p, h, fh);
-                        su3_mul<true>(Un, h, chiT[r]);
-                    }
+                cx<T> p[12], h[6], chi[6];
+                Store<P>::load_spinor(tab.hop[r0 + r], Vh, (tp * C + col) >> 1, p);
+                project<0, SF>(p, h, ff);
+                su3_mul<false>(U, h, chi);
+                reconstruct<0, SF>(acc[r], chi);
+                reconstruct<0, SB>(acc[r], chiT[r]);
+                if (next) {
+                    project<0, SB>(p, h, fh);
+                    su3_mul<true>(Un, h, chiT[r]);
                 }
             }
         }
-        hop_boundary<T, NR>(acc, 1);
-        parity_hops<P, 1, DAG, ROWS, NR>(d, g, tab, r0, nr, Vh, s, c, apbc != 0, fh, acc);
-        parity_hops<P, 2, DAG, ROWS, NR>(d, g, tab, r0, nr, Vh, s, c, apbc != 0, fh, acc);
-        parity_hops<P, 3, DAG, ROWS, NR>(d, g, tab, r0, nr, Vh, s, c, apbc != 0, fh, acc);
+        hop_boundary<T, NR>(acc);
+        parity_hops<P, 1, DAG, ROWS, NR, 4>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 2, DAG, ROWS, NR, 4>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 3, DAG, ROWS, NR, 4>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
         if (INV) {
 #pragma unroll
             for (int b = 0; b < 2; b++) {
@@ -359,81 +348,70 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
                 Store<P>::load_clover(cinv, g.V, b, s, dd, uu);
 #pragma unroll
                 for (int r = 0; r < NR; r++) {
-                    if (r < nr) {
-                        cx<T> y[6];
-                        clover_block(dd, uu, &acc[r][6 * b], y);
+                    cx<T> y[6];
+                    clover_block(dd, uu, &acc[r][6 * b], y);
 #pragma unroll
-                        for (int k = 0; k < 6; k++) acc[r][6 * b + k] = y[k];
-                    }
+                    for (int k = 0; k < 6; k++) acc[r][6 * b + k] = y[k];
                 }
+                hop_boundary<T, NR>(acc);
             }
         }
 #pragma unroll
         for (int r = 0; r < NR; r++)
-            if (r < nr) Store<P>::store_spinor(tab.out[r0 + r], Vh, i, acc[r]);
+            Store<P>::store_spinor(tab.out[r0 + r], Vh, i, acc[r]);
     }
+}
+
+// one launch, NR right-hand sides per lane; tab.n is a multiple of NR
+template <int P, bool DAG, int SELF, bool HOP, bool INV, int NR>
+hipError_t launch_nr(const dirac_op *op, int parity, const ParityTable &tab, double fh, hipStream_t st) {
+    using T = typename Store<P>::T;
+    const Geom &g = op->g;
+    const int apbc = (op->flags & WDIRAC_ANTIPERIODIC_T) ? 1 : 0;
+    const bool rows2 = op->link_rows == 2 || !HOP;
+    if constexpr (HOP && P == WDIRAC_F64) {
+        if (column_walk(P, g.V)) {
+            // T-chunks of kParChunk slices, each XCD 1/8 of the columns
+            const int tpc = ((g.stride[0] + 7) / 8 + 255) / 256;
+            const dim3 grid((g.n[0] + kParChunk - 1) / kParChunk * 8 * tpc * (tab.n / NR));
+            if (rows2)
+                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 2, NR, kParChunk>), grid, dim3(256),
+                                   0, st, tab, op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
+            else
+                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 3, NR, kParChunk>), grid, dim3(256),
+                                   0, st, tab, op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
+            return hipGetLastError();
+        }
+    }
+    const int hs = (g.V >> 1) / g.n[0];          // half-lattice sites per T-slice
+    const int tpr = ((hs + 7) / 8 + 255) / 256;  // 256-site tiles per eighth of a slice
+    const dim3 grid(g.n[0] * 8 * tpr * (tab.n / NR));
+    if (rows2)
+        hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 2, NR>), grid, dim3(256), 0, st, tab, op->data(P),
+                           op->cinv(P), g, parity, apbc, (T)fh, tpr);
+    else
+        hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 3, NR>), grid, dim3(256), 0, st, tab, op->data(P),
+                           op->cinv(P), g, parity, apbc, (T)fh, tpr);
+    return hipGetLastError();
 }
 
 template <int P, bool DAG, int SELF, bool HOP, bool INV>
 hipError_t launch_mode(const dirac_op *op, int parity, const ParityItem *items, size_t nitems, double fh,
                        hipStream_t st) {
-    using T = typename Store<P>::T;
-    const int Vh = op->g.V >> 1;
-    const int hs = Vh / op->g.n[0];                 // half-lattice sites per T-slice
-    const int tpr = ((hs + 7) / 8 + 255) / 256;     // 256-site tiles per eighth of a slice
-    const int apbc = (op->flags & WDIRAC_ANTIPERIODIC_T) ? 1 : 0;
-    const bool rows2 = op->link_rows == 2 || !HOP;
-    for (size_t a = 0; a < nitems; a += kParMax) {
+    const int nrmax = rhs_per_lane(op->g.V, nitems);
+    for (size_t a = 0; a < nitems;) {
+        const size_t left = nitems - a;
+        const int nr = left >= 2 ? nrmax : 1;
         ParityTable tab;
-        tab.n = (int)std::min<size_t>(kParMax, nitems - a);
+        tab.n = (int)std::min<size_t>(kParMax, left / nr * nr);
         for (int q = 0; q < tab.n; q++) {
             tab.out[q] = items[a + q].out;
             tab.self[q] = items[a + q].self;
             tab.hop[q] = items[a + q].hop;
         }
-        // pairs (or fours, see kParNrF16) for every count, a lone last right-hand side included: a single-RHS
-        // instantiation may round differently, and results must not depend on how right-hand sides are grouped
-        // (the per-RHS arithmetic of the pair and four instantiations is the same code, unrolled)
-        if constexpr (HOP && (P != WDIRAC_F16S || WD_PARITY_COLUMN_F16)) {
-            if (kParColumnWalk) {
-                // the column walk: T-chunks of CH slices, each XCD 1/8 of the columns
-                constexpr int CH = P == WDIRAC_F16S ? 2 : kParChunk;
-                const int C = op->g.stride[0];
-                const int tpc = ((C + 7) / 8 + 255) / 256;
-                const dim3 gc((op->g.n[0] + CH - 1) / CH * 8 * tpc, (tab.n + kParNr - 1) / kParNr);
-                if (rows2)
-                    hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 2, kParNr, CH>), gc, dim3(256),
-                                       0, st, tab, op->data(P), op->cinv(P), op->g, parity, apbc, (T)fh, tpc);
-                else
-                    hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 3, kParNr, CH>), gc, dim3(256),
-                                       0, st, tab, op->data(P), op->cinv(P), op->g, parity, apbc, (T)fh, tpc);
-                hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return e;
-                continue;
-            }
-        }
-        if constexpr (P == WDIRAC_F16S) {
-            if (tab.n >= kParNrF16) {
-                const dim3 g4(op->g.n[0] * 8 * tpr, (tab.n + kParNrF16 - 1) / kParNrF16);
-                if (rows2)
-                    hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 2, kParNrF16>), g4, dim3(256), 0, st,
-                                       tab, op->data(P), op->cinv(P), op->g, parity, apbc, (T)fh, tpr);
-                else
-                    hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 3, kParNrF16>), g4, dim3(256), 0, st,
-                                       tab, op->data(P), op->cinv(P), op->g, parity, apbc, (T)fh, tpr);
-                hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return e;
-                continue;
-            }
-        }
-        const dim3 grid(op->g.n[0] * 8 * tpr, (tab.n + kParNr - 1) / kParNr);
-        if (rows2)
-            hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 2, kParNr>), grid, dim3(256), 0, st, tab,
-                               op->data(P), op->cinv(P), op->g, parity, apbc, (T)fh, tpr);
-        else
-            hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 3, kParNr>), grid, dim3(256), 0, st, tab,
-                               op->data(P), op->cinv(P), op->g, parity, apbc, (T)fh, tpr);
-        hipError_t e = hipGetLastError();
+        a += tab.n;
+        const hipError_t e = nr == 2 ? launch_nr<P, DAG, SELF, HOP, INV, 2>(op, parity, tab, fh, st)
+                                     : launch_nr<P, DAG, SELF, HOP, INV, 1>(op, parity, tab, fh, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

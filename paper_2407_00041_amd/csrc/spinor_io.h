@@ -25,15 +25,17 @@ template <typename V> __device__ __forceinline__ V ld_once(const V *p) {
     return *p;
 }
 
+// conj(a b - c d)
+template <typename T> __device__ __forceinline__ cx<T> cross_conj(cx<T> a, cx<T> b, cx<T> c, cx<T> d) {
+    return {fma(a.r, b.r, fma(-a.i, b.i, fma(-c.r, d.r, c.i * d.i))),
+            fma(-a.r, b.i, fma(-a.i, b.r, fma(c.r, d.i, c.i * d.r)))};
+}
 // third row of an SU(3) matrix from the first two: conj(row0 x row1)
 template <typename T> __device__ __forceinline__ void third_row(cx<T> U[9]) {
     const cx<T> a0 = U[0], a1 = U[1], a2 = U[2], b0 = U[3], b1 = U[4], b2 = U[5];
-    const cx<T> c0 = cmul(a1, b2) - cmul(a2, b1);
-    const cx<T> c1 = cmul(a2, b0) - cmul(a0, b2);
-    const cx<T> c2 = cmul(a0, b1) - cmul(a1, b0);
-    U[6] = {c0.r, -c0.i};
-    U[7] = {c1.r, -c1.i};
-    U[8] = {c2.r, -c2.i};
+    U[6] = cross_conj(a1, b2, a2, b1);
+    U[7] = cross_conj(a2, b0, a0, b2);
+    U[8] = cross_conj(a0, b1, a1, b0);
 }
 
 template <int P> struct Store;
@@ -201,6 +203,13 @@ template <> struct Store<WDIRAC_F16S> {
             for (int j = 0; j < 4; j++) v[4 * k + j] = {sc * (float)a[2 * j], sc * (float)a[2 * j + 1]};
         }
     }
+    // the stored fp16 values as they are; returns the scale
+    static __device__ __forceinline__ float load_raw(const void *base, int V, int s, half8 q[3]) {
+        const half8 *p = static_cast<const half8 *>(base);
+#pragma unroll
+        for (int k = 0; k < 3; k++) q[k] = p[(size_t)k * V + s];
+        return scales(base, V)[s];
+    }
     static __device__ __forceinline__ void load_half(const void *base, int V, int s, int h, cx<T> v[6]) {
         cx<T> w[12];
         load_spinor(base, V, s, w);
@@ -212,16 +221,30 @@ template <> struct Store<WDIRAC_F16S> {
         float m = 0.f;
 #pragma unroll
         for (int k = 0; k < 12; k++) m = fmaxf(m, fmaxf(fabsf(v[k].r), fabsf(v[k].i)));
+        half8 a[3];
+        if (m >= 0x1p-60f && m <= 0x1p+100f) {
+            // v / m as the division rounds it, without 24 divisions: y = 1/m correctly rounded by one Newton step,
+            // then quotient, exact remainder and correction (Markstein); the bounds keep every step normal
+            const float y0 = __builtin_amdgcn_rcpf(m);
+            const float y = __builtin_fmaf(__builtin_fmaf(-m, y0, 1.f), y0, y0);
+            auto quot = [&](float x) {
+                const float q = x * y;
+                return (_Float16)__builtin_fmaf(__builtin_fmaf(-q, m, x), y, q);
+            };
 #pragma unroll
-        for (int k = 0; k < 3; k++) {
-            half8 a;
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                a[2 * j] = m > 0.f ? (_Float16)(v[4 * k + j].r / m) : (_Float16)0.f;
-                a[2 * j + 1] = m > 0.f ? (_Float16)(v[4 * k + j].i / m) : (_Float16)0.f;
+            for (int k = 0; k < 12; k++) {
+                a[k >> 2][2 * (k & 3)] = quot(v[k].r);
+                a[k >> 2][2 * (k & 3) + 1] = quot(v[k].i);
             }
-            __builtin_nontemporal_store(a, &p[(size_t)k * V + s]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 12; k++) {
+                a[k >> 2][2 * (k & 3)] = m > 0.f ? (_Float16)(v[k].r / m) : (_Float16)0.f;
+                a[k >> 2][2 * (k & 3) + 1] = m > 0.f ? (_Float16)(v[k].i / m) : (_Float16)0.f;
+            }
         }
+#pragma unroll
+        for (int k = 0; k < 3; k++) __builtin_nontemporal_store(a[k], &p[(size_t)k * V + s]);
         float *sp = reinterpret_cast<float *>(static_cast<char *>(base) + (size_t)48 * V);
         __builtin_nontemporal_store(m, &sp[s]);
     }

@@ -12,6 +12,19 @@
 
 namespace wd {
 
+// Fence between hops.  A site's work is one basic block, so the compiler would
+// issue every hop's loads first and do all the arithmetic afterwards (all
+// eight hops in flight, far beyond the register file).  The empty asm takes
+// the accumulators as in/out operands, so a hop's arithmetic must be done
+// before it, and clobbers memory, so the next hop's loads stay after it.
+template <typename T, int NR> __device__ __forceinline__ void hop_boundary(cx<T> (&acc)[NR][12]) {
+#pragma unroll
+    for (int r = 0; r < NR; r++)
+#pragma unroll
+        for (int k = 0; k < 12; k++) asm volatile("" : "+v"(acc[r][k].r), "+v"(acc[r][k].i) : : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // h = f (u + S B_mu d)  (u = spins 0,1; d = spins 2,3)
 template <int MU, int S, typename T>
 __device__ __forceinline__ void project(const cx<T> p[12], cx<T> h[6], T f) {
@@ -56,6 +69,47 @@ __device__ __forceinline__ void reconstruct(cx<T> acc[12], const cx<T> chi[6]) {
         else { l0 = times_i(c1); l1 = times_i(c0); }
         if (S > 0) { acc[6 + c] = acc[6 + c] + l0; acc[9 + c] = acc[9 + c] + l1; }
         else { acc[6 + c] = acc[6 + c] - l0; acc[9 + c] = acc[9 + c] - l1; }
+    }
+}
+
+// h = u + S B_mu d of a stored FP16S site without its scale.  Each component is one multiply-add on two fp16
+// operands (exact: the sum of two fp16 values in FP32); `one` is opaque so that it stays one.
+template <int MU, int S> __device__ __forceinline__ void project_half(const half8 q[3], cx<float> h[6]) {
+    float one;
+    asm("s_mov_b32 %0, 1.0" : "=s"(one));
+    auto re = [&](int k) { return (float)q[k >> 2][2 * (k & 3)]; };
+    auto im = [&](int k) { return (float)q[k >> 2][2 * (k & 3) + 1]; };
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        // S B_mu d of the two spins
+        float b0r, b0i, b1r, b1i;
+        const int d0 = 6 + c, d1 = 9 + c;
+        if (MU == 0) { b0r = re(d0); b0i = im(d0); b1r = re(d1); b1i = im(d1); }
+        else if (MU == 1) { b0r = im(d0); b0i = -re(d0); b1r = -im(d1); b1i = re(d1); }
+        else if (MU == 2) { b0r = -re(d1); b0i = -im(d1); b1r = re(d0); b1i = im(d0); }
+        else { b0r = im(d1); b0i = -re(d1); b1r = im(d0); b1i = -re(d0); }
+        if (S < 0) { b0r = -b0r; b0i = -b0i; b1r = -b1r; b1i = -b1i; }
+        h[c] = {__builtin_fmaf(b0r, one, re(c)), __builtin_fmaf(b0i, one, im(c))};
+        h[3 + c] = {__builtin_fmaf(b1r, one, re(3 + c)), __builtin_fmaf(b1i, one, im(3 + c))};
+    }
+}
+
+// upper += f chi; lower += f S B_mu^H chi
+template <int MU, int S, typename T>
+__device__ __forceinline__ void reconstruct_scaled(cx<T> acc[12], const cx<T> chi[6], T f) {
+    const T g = S > 0 ? f : -f;
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const cx<T> c0 = chi[c], c1 = chi[3 + c];
+        cx<T> l0, l1;
+        acc[c] = {fma(f, c0.r, acc[c].r), fma(f, c0.i, acc[c].i)};
+        acc[3 + c] = {fma(f, c1.r, acc[3 + c].r), fma(f, c1.i, acc[3 + c].i)};
+        if (MU == 0) { l0 = c0; l1 = c1; }
+        else if (MU == 1) { l0 = times_i(c0); l1 = times_mi(c1); }
+        else if (MU == 2) { l0 = c1; l1 = mk<T>(-c0.r, -c0.i); }
+        else { l0 = times_i(c1); l1 = times_i(c0); }
+        acc[6 + c] = {fma(g, l0.r, acc[6 + c].r), fma(g, l0.i, acc[6 + c].i)};
+        acc[9 + c] = {fma(g, l1.r, acc[9 + c].r), fma(g, l1.i, acc[9 + c].i)};
     }
 }
 

@@ -1,0 +1,46 @@
+"""The launch shapes that a rule on sizes chooses: on both sides of each rule's
+line the results match the oracle and do not depend on the grouping of the
+right-hand sides (byte for byte).  (GPU)"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import evenodd
+from paper_2407_00041_amd import DiracOp, synth
+
+from util import TOL, fields, need_gpu, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+# 16^4: one right-hand side per lane up to 4, pairs and a lone last one at 5; 24 x 16^2 x 24 is past 2^17 sites
+# (the FP64 column walk, chunks of four slices) and a pair there past 2^18 site-right-hand-sides; 10 x 32^2 x 14
+# ends in a half chunk of the column walk
+@pytest.mark.parametrize("dims,n", [((16, 16, 16, 16), 3), ((16, 16, 16, 16), 5), ((24, 16, 16, 24), 3),
+                                    ((10, 32, 32, 14), 2)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("compress,ap", [(True, False), (False, True)])
+def test_reduced_operator_shapes(dims, n, prec, compress, ap):
+    need_gpu()
+    U = synth.smooth_links(dims, 71, device="cuda").cpu().numpy()
+    op = DiracOp(dims, U, -0.3, 1.0, antiperiodic_t=ap, even_odd=True, compress_links=compress,
+                 compress_clover=compress)
+    psi = synth.gaussian_spinor(dims, 72, nrhs=n, device="cuda")
+    e, o = op.split(op.pack(psi, prec), prec, n)
+    out, tmp = op.empty_parity(prec, n), op.empty_parity(prec, n)
+    rb = op.parity_field_bytes(prec, 1)
+    for dagger in (False, True):
+        op.apply_schur_native(out, e, tmp, n, prec, dagger)
+        for r in range(n):
+            o1, t1 = op.empty_parity(prec, 1), op.empty_parity(prec, 1)
+            op.apply_schur_native(o1, e[r * rb:(r + 1) * rb], t1, 1, prec, dagger)
+            assert torch.equal(o1, out[r * rb:(r + 1) * rb]), (dagger, r)
+    op.apply_schur_native(out, e, tmp, n, prec)
+    even_sites = evenodd.sites_of(dims, 0)
+    pick = np.sort(np.random.default_rng(73).choice(len(even_sites), 48, replace=False))
+    o.zero_()
+    got = op.unpack(op.merge(out, o, prec, n), prec, n)[:, torch.from_numpy(even_sites[pick]).cuda()].cpu().numpy()
+    for r in range(n):
+        want = evenodd.schur_sites(dims, U, psi[r].cpu().numpy()[even_sites], even_sites[pick], -0.3, 1.0,
+                                   antiperiodic_t=ap)
+        assert rel_l2(got[r], want) < TOL[prec], r
