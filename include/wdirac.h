@@ -215,6 +215,8 @@ int dirac_apply_batched(const dirac_op *op, const dirac_batch *batches, int nbat
  * consecutive z-planes, one wave each, 4 for those walked along T in (y, x)
  * blocks of about eight x-rows).  Setting any of these launch knobs makes them override autotuned
  * choices; "explicit" = 0 returns to the autotuned ones (1 forces the knobs).
+ * A launch that is neither set here nor autotuned takes order, register block
+ * and T-chunk from the lattice size, precision and number of right-hand sides.
  * Not synchronised with launches in flight; set before applying.
  * Errors: EINVAL (unknown key or value out of range).
  */

@@ -8,11 +8,10 @@
 
 namespace wd {
 
-// A register block: up to NR right-hand sides handled by the same lanes.
+// A register block: NR right-hand sides handled by the same lanes.
 template <int NR> struct Chunk {
     const void *in[NR];
     void *out[NR];
-    int nr;  // valid entries; the rest repeat the last valid pointers
 };
 
 constexpr int kMaxChunks = 24;  // register blocks per launch (kernel-argument budget)

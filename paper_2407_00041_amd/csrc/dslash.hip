@@ -9,7 +9,11 @@
 // reconstruction of the lower half as s B_mu^H (U h) (the back-substitution
 // of Sec. 2.2).  Every link and clover entry is loaded once per site and
 // register block and used for all NR right-hand sides; nothing but the
-// result is written.
+// result is written.  The count of right-hand sides and the link format are
+// compile-time constants: with branches on either, a hop's spinor loads waited
+// for its link and each right-hand side for the one before (site kernel, us,
+// 64 x 32^3: FP64 678 -> 568, FP16S 4 RHS 543 -> 460; columns FP32 4 RHS
+// 722 -> 686; FP64 48^3 x 96 2735 -> 2696, bound by fabric traffic).
 //
 // Gamma basis: gamma_mu = [[0, B_mu], [B_mu^H, 0]], B_T = 1, B_Z = -i s3,
 // B_Y = -i s2, B_X = -i s1, so the projector (I + s gamma_mu) maps
@@ -57,16 +61,25 @@ __device__ __forceinline__ Nbr neighbours(const Geom &g, int s) {
     return n;
 }
 
-// Scheduling fences between hops bound how far the compiler hoists the
-// loads of later hops (and with them the register pressure).
-#ifndef WD_HOP_FENCE
-#define WD_HOP_FENCE 1
-#endif
-__device__ __forceinline__ void hop_fence(int level) {
-    if (WD_HOP_FENCE >= level) __builtin_amdgcn_sched_barrier(0);
+// acc += f (1 + S gamma_mu)-projected hop of the neighbour at site j of every right-hand side, through the link U
+// (DAGU: its adjoint)
+template <int P, int MU, int S, bool DAGU, int NR>
+__device__ __forceinline__ void hop(const cx<typename Store<P>::T> U[9], const Chunk<NR> &ch, int V, int j,
+                                    typename Store<P>::T f, cx<typename Store<P>::T> (&acc)[NR][12]) {
+    using T = typename Store<P>::T;
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+        Raw<P> x;
+        cx<T> h[6], chi[6];
+        x.load(ch.in[r], V, j);
+        project_raw<MU, S>(x, h);
+        su3_mul<DAGU>(U, h, chi);
+        reconstruct_scaled<MU, S>(acc[r], chi, x.weight(f));
+    }
 }
 
-template <int P, int MU, bool DAG, int NR>
+// both hops of direction MU; FENCE: hops between two fences (1, 2, 4 or 8)
+template <int P, int MU, bool DAG, int ROWS, int NR, int FENCE>
 __device__ __forceinline__ void hop_pair(const Chunk<NR> &ch, const OpData &d, int V, int s, const Nbr &nb,
                                          bool apbc, cx<typename Store<P>::T> (&acc)[NR][12]) {
     using T = typename Store<P>::T;
@@ -74,43 +87,20 @@ __device__ __forceinline__ void hop_pair(const Chunk<NR> &ch, const OpData &d, i
     constexpr int SB = -SF;            // backward projector
     cx<T> U[9];
     // forward: -1/2 (I + SF gamma) (x) U_mu(x) psi(x+mu)
-    {
-        const T f = (MU == 0 && apbc && nb.fwd_wrapT) ? T(0.5) : T(-0.5);
-        Store<P>::load_link(d.links, V, MU, s, U, d.rows);
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            if (r < ch.nr) {
-                cx<T> p[12], h[6], chi[6];
-                Store<P>::load_spinor(ch.in[r], V, nb.fwd[MU], p);
-                project<MU, SF>(p, h, f);
-                su3_mul<false>(U, h, chi);
-                reconstruct<MU, SF>(acc[r], chi);
-            }
-        }
-    }
-    hop_fence(2);
+    Store<P>::load_link(d.links, V, MU, s, U, ROWS);
+    hop<P, MU, SF, false, NR>(U, ch, V, nb.fwd[MU], (MU == 0 && apbc && nb.fwd_wrapT) ? T(0.5) : T(-0.5), acc);
+    if (FENCE == 1) hop_boundary<T, NR>(acc);
     // backward: -1/2 (I + SB gamma) (x) U_mu(x-mu)^H psi(x-mu)
-    {
-        const T f = (MU == 0 && apbc && nb.bwd_wrapT) ? T(0.5) : T(-0.5);
-        Store<P>::load_link(d.links, V, MU, nb.bwd[MU], U, d.rows);
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            if (r < ch.nr) {
-                cx<T> p[12], h[6], chi[6];
-                Store<P>::load_spinor(ch.in[r], V, nb.bwd[MU], p);
-                project<MU, SB>(p, h, f);
-                su3_mul<true>(U, h, chi);
-                reconstruct<MU, SB>(acc[r], chi);
-            }
-        }
-    }
+    Store<P>::load_link(d.links, V, MU, nb.bwd[MU], U, ROWS);
+    hop<P, MU, SB, true, NR>(U, ch, V, nb.bwd[MU], (MU == 0 && apbc && nb.bwd_wrapT) ? T(0.5) : T(-0.5), acc);
+    if (MU == 3 || FENCE <= 2 || (MU == 1 && FENCE == 4)) hop_boundary<T, NR>(acc);
 }
 
-template <int P, bool DAG, int NR>
-__device__ __forceinline__ void site_apply(const Chunk<NR> &ch, const OpData &d, const Geom &g, int s, bool apbc) {
+// acc = A(x) x of every right-hand side, x(r, b, v) giving chirality block b of the r-th
+template <int P, int NR, typename X>
+__device__ __forceinline__ void self_term(const OpData &d, int V, int s, X x,
+                                          cx<typename Store<P>::T> (&acc)[NR][12]) {
     using T = typename Store<P>::T;
-    const int V = g.V;
-    cx<T> acc[NR][12];
 #pragma unroll
     for (int b = 0; b < 2; b++) {
         if (d.clover_compact) {
@@ -118,11 +108,9 @@ __device__ __forceinline__ void site_apply(const Chunk<NR> &ch, const OpData &d,
             Store<P>::load_clover_compact(d.clover, V, b, s, cr);
 #pragma unroll
             for (int r = 0; r < NR; r++) {
-                if (r < ch.nr) {
-                    cx<T> p[6];
-                    Store<P>::load_half(ch.in[r], V, s, b, p);
-                    clover_block_compact((T)d.diag, cr, p, &acc[r][6 * b]);
-                }
+                cx<T> p[6];
+                x(r, b, p);
+                clover_block_compact((T)d.diag, cr, p, &acc[r][6 * b]);
             }
         } else {
             T dd[6];
@@ -130,27 +118,28 @@ __device__ __forceinline__ void site_apply(const Chunk<NR> &ch, const OpData &d,
             Store<P>::load_clover(d.clover, V, b, s, dd, uu);
 #pragma unroll
             for (int r = 0; r < NR; r++) {
-                if (r < ch.nr) {
-                    cx<T> p[6];
-                    Store<P>::load_half(ch.in[r], V, s, b, p);
-                    clover_block(dd, uu, p, &acc[r][6 * b]);
-                }
+                cx<T> p[6];
+                x(r, b, p);
+                clover_block(dd, uu, p, &acc[r][6 * b]);
             }
         }
     }
+}
+
+template <int P, bool DAG, int ROWS, int NR, int FENCE>
+__device__ __forceinline__ void site_apply(const Chunk<NR> &ch, const OpData &d, const Geom &g, int s, bool apbc) {
+    using T = typename Store<P>::T;
+    const int V = g.V;
+    cx<T> acc[NR][12];
+    self_term<P, NR>(d, V, s, [&](int r, int b, cx<T> *p) { Store<P>::load_half(ch.in[r], V, s, b, p); }, acc);
     const Nbr nb = neighbours(g, s);
-    hop_fence(1);
-    hop_pair<P, 0, DAG, NR>(ch, d, V, s, nb, apbc, acc);
-    hop_fence(1);
-    hop_pair<P, 1, DAG, NR>(ch, d, V, s, nb, apbc, acc);
-    hop_fence(1);
-    hop_pair<P, 2, DAG, NR>(ch, d, V, s, nb, apbc, acc);
-    hop_fence(1);
-    hop_pair<P, 3, DAG, NR>(ch, d, V, s, nb, apbc, acc);
-    hop_fence(1);
+    hop_boundary<T, NR>(acc);
+    hop_pair<P, 0, DAG, ROWS, NR, FENCE>(ch, d, V, s, nb, apbc, acc);
+    hop_pair<P, 1, DAG, ROWS, NR, FENCE>(ch, d, V, s, nb, apbc, acc);
+    hop_pair<P, 2, DAG, ROWS, NR, FENCE>(ch, d, V, s, nb, apbc, acc);
+    hop_pair<P, 3, DAG, ROWS, NR, FENCE>(ch, d, V, s, nb, apbc, acc);
 #pragma unroll
-    for (int r = 0; r < NR; r++)
-        if (r < ch.nr) Store<P>::store_spinor(ch.out[r], V, s, acc[r]);
+    for (int r = 0; r < NR; r++) Store<P>::store_spinor(ch.out[r], V, s, acc[r]);
 }
 
 // Register T-sweep (tile order 3): one lane walks the sites t0..t1-1 of one
@@ -158,7 +147,7 @@ __device__ __forceinline__ void site_apply(const Chunk<NR> &ch, const OpData &d,
 // kept as the next step's own spinor, and the backward T hop of site t+1,
 // -1/2 (I + SB gamma_T) (x) U_T(t)^H psi(t), is formed at step t and carried
 // in registers, so no T-neighbour spinor or backward T link is re-read.
-template <int P, bool DAG, int NR>
+template <int P, bool DAG, int ROWS, int NR, int FENCE>
 __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &d, const Geom &g, int c, int t0,
                                              int t1, bool apbc) {
     using T = typename Store<P>::T;
@@ -179,44 +168,29 @@ __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &
             cb[mu] = (q[mu] == 0) ? c + (L - 1) * st : c - st;
         }
     }
-    cx<T> self[NR][12], chiT[NR][6];
+    Raw<P> self[NR];
+    cx<T> chiT[NR][6];  // carried product and its weight
+    T wT[NR];
     {
         const int tm = (t0 == 0) ? nT - 1 : t0 - 1;
         const T f = (apbc && t0 == 0) ? T(0.5) : T(-0.5);
         cx<T> U[9];
-        Store<P>::load_link(d.links, V, 0, tm * S + c, U, d.rows);
+        Store<P>::load_link(d.links, V, 0, tm * S + c, U, ROWS);
 #pragma unroll
         for (int r = 0; r < NR; r++) {
-            if (r < ch.nr) {
-                cx<T> p[12], h[6];
-                Store<P>::load_spinor(ch.in[r], V, tm * S + c, p);
-                project<0, SB>(p, h, f);
-                su3_mul<true>(U, h, chiT[r]);
-                Store<P>::load_spinor(ch.in[r], V, t0 * S + c, self[r]);
-            }
+            Raw<P> x;
+            cx<T> h[6];
+            x.load(ch.in[r], V, tm * S + c);
+            self[r].load(ch.in[r], V, t0 * S + c);
+            project_raw<0, SB>(x, h);
+            su3_mul<true>(U, h, chiT[r]);
+            wT[r] = x.weight(f);
         }
     }
     for (int t = t0; t < t1; t++) {
         const int s = t * S + c;
         cx<T> acc[NR][12];
-        // self coupling
-#pragma unroll
-        for (int b = 0; b < 2; b++) {
-            if (d.clover_compact) {
-                T cr[28];
-                Store<P>::load_clover_compact(d.clover, V, b, s, cr);
-#pragma unroll
-                for (int r = 0; r < NR; r++)
-                    if (r < ch.nr) clover_block_compact((T)d.diag, cr, &self[r][6 * b], &acc[r][6 * b]);
-            } else {
-                T dd[6];
-                cx<T> uu[15];
-                Store<P>::load_clover(d.clover, V, b, s, dd, uu);
-#pragma unroll
-                for (int r = 0; r < NR; r++)
-                    if (r < ch.nr) clover_block(dd, uu, &self[r][6 * b], &acc[r][6 * b]);
-            }
-        }
+        self_term<P, NR>(d, V, s, [&](int r, int b, cx<T> *p) { self[r].half(b, p); }, acc);
         // backward T hop (carried), then the one for site t+1
         const bool last = (t == nT - 1);
         // U_T(s) serves both T hops of the step; the copy parked in the lane's LDS slot between them spares a
@@ -225,20 +199,19 @@ __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &
         {
             const T f = (apbc && last) ? T(0.5) : T(-0.5);
             cx<T> U[9];
-            Store<P>::load_link(d.links, V, 0, s, U, d.rows);
+            Store<P>::load_link(d.links, V, 0, s, U, ROWS);
 #pragma unroll
             for (int e = 0; e < 9; e++) ut_lds[threadIdx.x][e] = U[e];
 #pragma unroll
             for (int r = 0; r < NR; r++) {
-                if (r < ch.nr) {
-                    reconstruct<0, SB>(acc[r], chiT[r]);
-                    cx<T> h[6];
-                    project<0, SB>(self[r], h, f);
-                    su3_mul<true>(U, h, chiT[r]);
-                }
+                reconstruct_scaled<0, SB>(acc[r], chiT[r], wT[r]);
+                cx<T> h[6];
+                project_raw<0, SB>(self[r], h);
+                su3_mul<true>(U, h, chiT[r]);
+                wT[r] = self[r].weight(f);
             }
         }
-        hop_fence(1);
+        hop_boundary<T, NR>(acc);
         Nbr nb;
 #pragma unroll
         for (int mu = 1; mu < 4; mu++) {
@@ -247,12 +220,9 @@ __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &
         }
         nb.fwd[0] = nb.bwd[0] = s;
         nb.fwd_wrapT = nb.bwd_wrapT = false;
-        hop_pair<P, 1, DAG, NR>(ch, d, V, s, nb, false, acc);
-        hop_fence(1);
-        hop_pair<P, 2, DAG, NR>(ch, d, V, s, nb, false, acc);
-        hop_fence(1);
-        hop_pair<P, 3, DAG, NR>(ch, d, V, s, nb, false, acc);
-        hop_fence(1);
+        hop_pair<P, 1, DAG, ROWS, NR, FENCE>(ch, d, V, s, nb, false, acc);
+        hop_pair<P, 2, DAG, ROWS, NR, FENCE>(ch, d, V, s, nb, false, acc);
+        hop_pair<P, 3, DAG, ROWS, NR, FENCE>(ch, d, V, s, nb, false, acc);
         // forward T hop; psi(t+1) becomes the next step's own spinor
         {
             const int sp = (last ? 0 : t + 1) * S + c;
@@ -262,19 +232,16 @@ __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &
             for (int e = 0; e < 9; e++) U[e] = ut_lds[threadIdx.x][e];
 #pragma unroll
             for (int r = 0; r < NR; r++) {
-                if (r < ch.nr) {
-                    cx<T> h[6], chi[6];
-                    Store<P>::load_spinor(ch.in[r], V, sp, self[r]);
-                    project<0, SF>(self[r], h, f);
-                    su3_mul<false>(U, h, chi);
-                    reconstruct<0, SF>(acc[r], chi);
-                }
+                cx<T> h[6], chi[6];
+                self[r].load(ch.in[r], V, sp);
+                project_raw<0, SF>(self[r], h);
+                su3_mul<false>(U, h, chi);
+                reconstruct_scaled<0, SF>(acc[r], chi, self[r].weight(f));
             }
         }
 #pragma unroll
-        for (int r = 0; r < NR; r++)
-            if (r < ch.nr) Store<P>::store_spinor(ch.out[r], V, s, acc[r]);
-        hop_fence(1);
+        for (int r = 0; r < NR; r++) Store<P>::store_spinor(ch.out[r], V, s, acc[r]);
+        hop_boundary<T, NR>(acc);
     }
 }
 
@@ -330,43 +297,17 @@ __device__ __forceinline__ int zgroup_site(const TileMap &m, int vb, int l) {
     return (t * m.nz + z) * plane + xy;
 }
 
-// Minimum waves per SIMD the register allocation must allow, per precision
-// and register block (the compiler otherwise trades occupancy for early
-// load hoisting).  Values from launch sweeps at 48^3 x 96.
-#ifndef WD_OCC_F64_1
-#define WD_OCC_F64_1 2
-#endif
-#ifndef WD_OCC_F64_2
-#define WD_OCC_F64_2 2
-#endif
-#ifndef WD_OCC_F64_4
-#define WD_OCC_F64_4 1
-#endif
-#ifndef WD_OCC_F32_1
-#define WD_OCC_F32_1 4
-#endif
-#ifndef WD_OCC_F32_2
-#define WD_OCC_F32_2 4
-#endif
-#ifndef WD_OCC_F32_4
-#define WD_OCC_F32_4 3
-#endif
-#ifndef WD_OCC_F16_1
-#define WD_OCC_F16_1 6
-#endif
-#ifndef WD_OCC_F16_2
-#define WD_OCC_F16_2 4
-#endif
-#ifndef WD_OCC_F16_4
-#define WD_OCC_F16_4 3
-#endif
+// Hops between two fences and waves per SIMD the registers must allow, of the
+// site kernel: FP64 keeps one hop's loads in flight (two: 568 -> 581 us at
+// 64 x 32^3), FP32 and FP16S issue the loads of several hops together.
+template <int P, int NR> constexpr int site_fence() {
+    return (P == WDIRAC_F64 || NR == 4) ? 1 : (P == WDIRAC_F16S && NR == 1) ? 8 : 4;
+}
 template <int P, int NR> constexpr int occupancy() {
-    return P == WDIRAC_F64 ? (NR == 1 ? WD_OCC_F64_1 : NR == 2 ? WD_OCC_F64_2 : WD_OCC_F64_4)
-         : P == WDIRAC_F32 ? (NR == 1 ? WD_OCC_F32_1 : NR == 2 ? WD_OCC_F32_2 : WD_OCC_F32_4)
-                           : (NR == 1 ? WD_OCC_F16_1 : NR == 2 ? WD_OCC_F16_2 : WD_OCC_F16_4);
+    return P == WDIRAC_F64 ? (NR == 4 ? 1 : 2) : P == WDIRAC_F32 ? (NR == 1 ? 4 : 2) : (NR == 4 ? 2 : 3);
 }
 
-template <int P, bool DAG, int NR>
+template <int P, bool DAG, int ROWS, int NR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(occupancy<P, NR>())))
 void dslash_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int apbc) {
     const int nitems = m.nslots * tab.nchunks;   // nslots is a multiple of 8
@@ -379,27 +320,17 @@ void dslash_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int apbc) {
         int lo, hi;
         tile_range(m, vb, lo, hi);
         const int s = lo + (int)threadIdx.x;
-        if (s < hi) site_apply<P, DAG, NR>(tab.c[c], d, g, s, apbc != 0);
+        if (s < hi) site_apply<P, DAG, ROWS, NR, site_fence<P, NR>()>(tab.c[c], d, g, s, apbc != 0);
     }
 }
 
-// the column sweep carries psi(t+1) and the T half-spinors: fewer waves
-#ifndef WD_OCCC_F64_1
-#define WD_OCCC_F64_1 2
-#endif
-#ifndef WD_OCCC_F32_1
-#define WD_OCCC_F32_1 3
-#endif
-#ifndef WD_OCCC_F16_1
-#define WD_OCCC_F16_1 4
-#endif
-template <int P, int NR> constexpr int occupancy_col() {
-    return P == WDIRAC_F64 ? (NR == 1 ? WD_OCCC_F64_1 : 1)
-                           : P == WDIRAC_F32 ? (NR == 1 ? WD_OCCC_F32_1 : NR == 2 ? 2 : 1)
-                                             : (NR == 1 ? WD_OCCC_F16_1 : NR == 2 ? 2 : 1);
+// the same for the column kernel, which carries psi(t+1) and the T half-spinors
+template <int P, int NR> constexpr int column_fence() {
+    return P == WDIRAC_F64 ? (NR == 1 ? 2 : 4) : P == WDIRAC_F32 ? 4 : 8;
 }
+template <int P, int NR> constexpr int occupancy_col() { return NR == 1 ? 2 : 1; }
 
-template <int P, bool DAG, int NR>
+template <int P, bool DAG, int ROWS, int NR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(occupancy_col<P, NR>())))
 void dslash_column_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int apbc) {
     const int nitems = m.nslots * tab.nchunks;
@@ -425,7 +356,7 @@ void dslash_column_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int a
             const int cc = r0 + tile * m.block + (int)threadIdx.x;
             if (cc < r1) col = cc;
         }
-        if (col >= 0 && t0 < t1) column_sweep<P, DAG, NR>(tab.c[c], d, g, col, t0, t1, apbc != 0);
+        if (col >= 0 && t0 < t1) column_sweep<P, DAG, ROWS, NR, column_fence<P, NR>()>(tab.c[c], d, g, col, t0, t1, apbc != 0);
     }
 }
 
@@ -498,7 +429,8 @@ void dslash_stationary_kernel(RhsTable tab, OpData d, Geom g, TileMap m, int apb
     const T fbT = (apbc && nb.bwd_wrapT) ? T(-1) : T(1);
     for (int r = 0; r < tab.n; r++) {
         const void *in = tab.in[r];
-        cx<T> acc[12];
+        cx<T> accs[1][12];
+        cx<T>(&acc)[12] = accs[0];
         {
             cx<T> self[12];
             Store<P>::load_spinor(in, V, s, self);
@@ -528,27 +460,29 @@ void dslash_stationary_kernel(RhsTable tab, OpData d, Geom g, TileMap m, int apb
                 }
             }
         }
-        hop_fence(1);
+        hop_boundary<T, 1>(accs);
 #define WD_STAT_HOP(MU)                                                         \
         {                                                                       \
-            cx<T> U[9], p[12], h[6], chi[6];                                    \
+            cx<T> U[9], h[6], chi[6];                                           \
+            Raw<P> x;                                                           \
             _Pragma("unroll") for (int e = 0; e < 6; e++) U[e] = Lf[MU][e];     \
             third_row(U);                                                       \
-            Store<P>::load_spinor(in, V, nb.fwd[MU], p);                        \
-            if (MU == 0) project<MU, SF>(p, h, ffT); else project_unit<MU, SF>(p, h); \
+            x.load(in, V, nb.fwd[MU]);                                          \
+            project_raw<MU, SF>(x, h);                                          \
             su3_mul<false>(U, h, chi);                                          \
-            reconstruct<MU, SF>(acc, chi);                                      \
+            reconstruct_scaled<MU, SF>(acc, chi, x.weight(MU == 0 ? ffT : T(1))); \
         }                                                                       \
         {                                                                       \
-            cx<T> U[9], p[12], h[6], chi[6];                                    \
+            cx<T> U[9], h[6], chi[6];                                           \
+            Raw<P> x;                                                           \
             _Pragma("unroll") for (int e = 0; e < 6; e++) U[e] = Lb[MU][e];     \
             third_row(U);                                                       \
-            Store<P>::load_spinor(in, V, nb.bwd[MU], p);                        \
-            if (MU == 0) project<MU, SB>(p, h, fbT); else project_unit<MU, SB>(p, h); \
+            x.load(in, V, nb.bwd[MU]);                                          \
+            project_raw<MU, SB>(x, h);                                          \
             su3_mul<true>(U, h, chi);                                           \
-            reconstruct<MU, SB>(acc, chi);                                      \
+            reconstruct_scaled<MU, SB>(acc, chi, x.weight(MU == 0 ? fbT : T(1))); \
         }                                                                       \
-        hop_fence(1);
+        hop_boundary<T, 1>(accs);
         WD_STAT_HOP(0)
         WD_STAT_HOP(1)
         WD_STAT_HOP(2)
@@ -619,7 +553,7 @@ Tuning tuning_snapshot() {
 }
 
 // Work-groups of one kernel instance that fit on the device at once.
-template <int P, bool DAG, int NR>
+template <int P, bool DAG, int ROWS, int NR>
 static int resident_blocks(int block) {
     static int cached[5] = {0, 0, 0, 0, 0};
     const int slot = block / 64;
@@ -627,7 +561,7 @@ static int resident_blocks(int block) {
         int dev = 0, cus = 0, per_cu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, dslash_kernel<P, DAG, NR>, block, 0) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, dslash_kernel<P, DAG, ROWS, NR>, block, 0) != hipSuccess ||
             cus * per_cu < 8) {
             (void)hipGetLastError();
             return 8;
@@ -637,7 +571,7 @@ static int resident_blocks(int block) {
     return cached[slot];
 }
 
-template <int P, bool DAG, int NR>
+template <int P, bool DAG, int ROWS, int NR>
 static int resident_blocks_col(int block) {
     static int cached[5] = {0, 0, 0, 0, 0};
     const int slot = block / 64;
@@ -645,7 +579,7 @@ static int resident_blocks_col(int block) {
         int dev = 0, cus = 0, per_cu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, dslash_column_kernel<P, DAG, NR>, block, 0) !=
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, dslash_column_kernel<P, DAG, ROWS, NR>, block, 0) !=
                 hipSuccess ||
             cus * per_cu < 8) {
             (void)hipGetLastError();
@@ -656,11 +590,14 @@ static int resident_blocks_col(int block) {
     return cached[slot];
 }
 
-template <int P, bool DAG, int NR>
+template <int P, bool DAG, int ROWS, int NR>
 static hipError_t launch_chunks(const std::vector<Chunk<NR>> &chunks, const OpData &d, const Geom &g, int apbc,
                                 bool persistent, const LaunchCfg &cfg, hipStream_t st) {
     const Tuning tu = tuning_snapshot();
+    constexpr int NRC = NR > 2 ? 2 : NR;  // the column kernels take at most two right-hand sides per lane
     const TileMap m = make_tilemap(g, cfg.order, cfg.block, cfg.tchunk);
+    const bool column = is_column_order(m.order);
+    if (column && NR != NRC) return hipErrorInvalidValue;
     for (size_t c0 = 0; c0 < chunks.size(); c0 += kMaxChunks) {
         ChunkTable<NR> tab;
         tab.nchunks = (int)std::min(chunks.size() - c0, (size_t)kMaxChunks);
@@ -671,19 +608,24 @@ static hipError_t launch_chunks(const std::vector<Chunk<NR>> &chunks, const OpDa
             // a persistent grid: at most the resident work-groups, each striding
             // through the item list (by default the hardware dispatcher hands
             // out one work-group per item in order, which measured faster)
-            long long cap = is_column_order(m.order) ? resident_blocks_col<P, DAG, NR>(cfg.block)
-                                                    : resident_blocks<P, DAG, NR>(cfg.block);
+            long long cap = column ? resident_blocks_col<P, DAG, ROWS, NRC>(cfg.block)
+                                   : resident_blocks<P, DAG, ROWS, NR>(cfg.block);
             if (tu.persistent_blocks > 0 && tu.persistent_blocks < cap) cap = tu.persistent_blocks / 8 * 8;
             if (cap < 8) cap = 8;
             if (grid > cap) grid = cap;
         }
         if (grid > (1LL << 30)) return hipErrorInvalidValue;
-        if (is_column_order(m.order))
-            hipLaunchKernelGGL((dslash_column_kernel<P, DAG, NR>), dim3((unsigned)grid), dim3(cfg.block), 0, st, tab,
-                               d, g, m, apbc);
-        else
-            hipLaunchKernelGGL((dslash_kernel<P, DAG, NR>), dim3((unsigned)grid), dim3(cfg.block), 0, st, tab, d, g,
-                               m, apbc);
+        if constexpr (NR == NRC) {
+            if (column) {
+                hipLaunchKernelGGL((dslash_column_kernel<P, DAG, ROWS, NR>), dim3((unsigned)grid), dim3(cfg.block), 0,
+                                   st, tab, d, g, m, apbc);
+                const hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return e;
+                continue;
+            }
+        }
+        hipLaunchKernelGGL((dslash_kernel<P, DAG, ROWS, NR>), dim3((unsigned)grid), dim3(cfg.block), 0, st, tab, d, g,
+                           m, apbc);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -691,28 +633,36 @@ static hipError_t launch_chunks(const std::vector<Chunk<NR>> &chunks, const OpDa
 }
 
 // Group the right-hand sides of all batches, in order, into register blocks
-// of at most NR (a block may span batches).
-template <int P, bool DAG, int NR>
-static hipError_t launch_nr(const dirac_batch *batches, int nbatch, const OpData &d, const Geom &g, int apbc,
-                            bool persistent, const LaunchCfg &cfg, hipStream_t st) {
-    const size_t rb = field_rhs_bytes(P, g.V);
-    std::vector<std::pair<const void *, void *>> rhs;
-    for (int b = 0; b < nbatch; b++)
-        for (int r = 0; r < batches[b].nrhs; r++)
-            rhs.emplace_back(static_cast<const char *>(batches[b].in) + r * rb,
-                             static_cast<char *>(batches[b].out) + r * rb);
-    std::vector<Chunk<NR>> chunks;
-    for (size_t r0 = 0; r0 < rhs.size(); r0 += NR) {
-        Chunk<NR> c;
-        c.nr = (int)std::min<size_t>(NR, rhs.size() - r0);
+// of NR (a block may span batches), the remainder into smaller ones.
+template <int P, bool DAG, int ROWS, int NR>
+static hipError_t launch_nr(const std::pair<const void *, void *> *rhs, size_t n, const OpData &d, const Geom &g,
+                            int apbc, bool persistent, const LaunchCfg &cfg, hipStream_t st) {
+    std::vector<Chunk<NR>> chunks(n / NR);
+    for (size_t q = 0; q < chunks.size(); q++)
         for (int r = 0; r < NR; r++) {
-            const size_t rr = r0 + std::min(r, c.nr - 1);
-            c.in[r] = rhs[rr].first;
-            c.out[r] = rhs[rr].second;
+            chunks[q].in[r] = rhs[q * NR + r].first;
+            chunks[q].out[r] = rhs[q * NR + r].second;
         }
-        chunks.push_back(c);
+    if (!chunks.empty()) {
+        const hipError_t e = launch_chunks<P, DAG, ROWS, NR>(chunks, d, g, apbc, persistent, cfg, st);
+        if (e != hipSuccess) return e;
     }
-    return launch_chunks<P, DAG, NR>(chunks, d, g, apbc, persistent, cfg, st);
+    if constexpr (NR > 1) {
+        const size_t done = n / NR * NR;
+        if (done < n)
+            return launch_nr<P, DAG, ROWS, NR / 2>(rhs + done, n - done, d, g, apbc, persistent, cfg, st);
+    }
+    return hipSuccess;
+}
+
+template <int P, bool DAG, int ROWS>
+static hipError_t launch_rows(const std::vector<std::pair<const void *, void *>> &rhs, const OpData &d, const Geom &g,
+                              int apbc, bool persistent, const LaunchCfg &cfg, hipStream_t st) {
+    if (cfg.nr >= 4 && !is_column_order(cfg.order))
+        return launch_nr<P, DAG, ROWS, 4>(rhs.data(), rhs.size(), d, g, apbc, persistent, cfg, st);
+    if (cfg.nr >= 2)
+        return launch_nr<P, DAG, ROWS, 2>(rhs.data(), rhs.size(), d, g, apbc, persistent, cfg, st);
+    return launch_nr<P, DAG, ROWS, 1>(rhs.data(), rhs.size(), d, g, apbc, persistent, cfg, st);
 }
 
 // Link-stationary launch: all right-hand sides of all batches, in groups of
@@ -779,10 +729,15 @@ static hipError_t launch_p(const dirac_batch *batches, int nbatch, const OpData 
         cfg.order = kOrderTSweep;  // FP64 or full links: the register-blocked site kernel
     }
     if (total == 1) cfg.nr = 1;
-    if (is_column_order(cfg.order) && P == WDIRAC_F64 && cfg.nr > 2) cfg.nr = 2;  // register budget
-    if (cfg.nr >= 4) return launch_nr<P, DAG, 4>(batches, nbatch, d, g, apbc, persistent, cfg, st);
-    if (cfg.nr >= 2) return launch_nr<P, DAG, 2>(batches, nbatch, d, g, apbc, persistent, cfg, st);
-    return launch_nr<P, DAG, 1>(batches, nbatch, d, g, apbc, persistent, cfg, st);
+    if (is_column_order(cfg.order) && cfg.nr > 2) cfg.nr = 2;  // register budget
+    const size_t rb = field_rhs_bytes(P, g.V);
+    std::vector<std::pair<const void *, void *>> rhs;
+    for (int b = 0; b < nbatch; b++)
+        for (int r = 0; r < batches[b].nrhs; r++)
+            rhs.emplace_back(static_cast<const char *>(batches[b].in) + r * rb,
+                             static_cast<char *>(batches[b].out) + r * rb);
+    return d.rows == 2 ? launch_rows<P, DAG, 2>(rhs, d, g, apbc, persistent, cfg, st)
+                       : launch_rows<P, DAG, 3>(rhs, d, g, apbc, persistent, cfg, st);
 }
 
 hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, bool dagger, const OpData &d,
@@ -801,16 +756,39 @@ hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, b
     return hipErrorInvalidValue;
 }
 
+// Launch configuration of n right-hand sides where none was tuned or set.  Measured best of the site kernel (T-slice
+// order) against the column sweep, us, 16^4 / 32 x 16^2 x 32 / 48 x 24^3 / 32^4 / 64 x 32^3, two-row links:
+//   FP64 1 RHS   site 16 / 77 / 194 / 290 / 568   column 23 / 68 / 190 / 285 / 567
+//   FP64 4 RHS   site 62 / 227 / 555 / 956 / 1922  column 46 / 210 / 500 / 764 / 1533
+//   FP32 1 RHS   site 9.5 / 35 / 82 / 129 / 275   column 16 / 35 / 82 / 124 / 283
+//   FP32 4 RHS   site 23 / 104 / 259 / 403 / 784   column 25 / 91 / 239 / 352 / 686
+//   FP16S 4 RHS  site 18 / 62 / 149 / 232 / 460    column 21 / 62 / 154 / 245 / 477
+// The column sweep adds the hops in another order, so its last bits differ from the site kernel's; the choice between
+// the two goes by the lattice alone, so that a result does not depend on how many right-hand sides are applied
+// together: FP64 walks columns from 2^17 sites on (the lanes fill the chip), FP32 from 2^18, FP16S never.  Pairs per
+// lane halve the waves: site kernel from 2^17 site-right-hand-sides (FP32 16^4, two: one per lane 12.9, four: pairs
+// 22.8; 8^4: pairs 11.9 against 8), FP64 columns from 2^21 (48 x 24^3, two: one per lane 307, pairs 316; 32^4, two:
+// pairs 445).  The link-stationary kernel (the site kernel's order and bits) takes six and more FP32 right-hand sides
+// between 16^4 and 2^18 sites: 12 at 16^4 67 -> 54; at 12^4 25 against 49.
+static LaunchCfg default_cfg(int V, int prec, int n, int rows) {
+    const long long w = (long long)V * n;
+    if (prec == WDIRAC_F64 && V > 1 << 17) return {kOrderColumn, 256, 4, w >= 1 << 21 ? 2 : 1};
+    if (prec == WDIRAC_F32 && V >= 1 << 18) return {kOrderColumn, 256, w >= 1 << 21 ? 8 : 4, n > 1 ? 2 : 1};
+    if (prec == WDIRAC_F32 && rows == 2 && n >= 6 && V >= 1 << 16) return {kOrderStationary, kStationaryBlock, 1, 2};
+    return {kOrderTSweep, 256, 4, w > 1 << 17 ? 2 : 1};
+}
+
 // The configuration of a launch: the autotuned one for this lattice,
-// precision, right-hand-side count and link format if there is one, else
-// the process-wide defaults.
+// precision, right-hand-side count and link format if there is one, the
+// process-wide values once one of them was set, else the rule above.
 hipError_t dslash_launch_batches(const dirac_batch *batches, int nbatch, int prec, bool dagger, const OpData &d,
                                  const Geom &g, int apbc, bool persistent, hipStream_t st) {
     int total = 0;
     for (int b = 0; b < nbatch; b++) total += batches[b].nrhs;
     const Tuning tu = tuning_snapshot();
     LaunchCfg cfg{tu.order, tu.block, tu.tchunk, (prec >= 0 && prec < 3) ? tu.nr[prec] : 1};
-    if (!tu.explicit_launch) tuned_cfg(g, prec, total, d.rows, d.clover_compact, cfg);
+    if (!tu.explicit_launch && !tuned_cfg(g, prec, total, d.rows, d.clover_compact, cfg))
+        cfg = default_cfg(g.V, prec, total, d.rows);
     return dslash_launch_cfg(batches, nbatch, prec, dagger, d, g, apbc, persistent, cfg, st);
 }
 

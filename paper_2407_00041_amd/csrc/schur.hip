@@ -93,22 +93,12 @@ __device__ __forceinline__ void parity_hop(const cx<typename Store<P>::T> U[9], 
     using T = typename Store<P>::T;
 #pragma unroll
     for (int r = 0; r < NR; r++) {
+        Raw<P> x;
         cx<T> h[6], chi[6];
-        if constexpr (P == WDIRAC_F16S) {
-            // the projection takes the stored fp16 values as they are (exact in FP32); the site's scale and the
-            // factor f enter once, where the product is added
-            half8 q[3];
-            const T sc = Store<P>::load_raw(tab.hop[r0 + r], Vh, j, q);
-            project_half<MU, S>(q, h);
-            su3_mul<DAGU>(U, h, chi);
-            reconstruct_scaled<MU, S>(acc[r], chi, f * sc);
-        } else {
-            cx<T> p[12];
-            Store<P>::load_spinor(tab.hop[r0 + r], Vh, j, p);
-            project<MU, S>(p, h, f);
-            su3_mul<DAGU>(U, h, chi);
-            reconstruct<MU, S>(acc[r], chi);
-        }
+        x.load(tab.hop[r0 + r], Vh, j);
+        project_raw<MU, S>(x, h);
+        su3_mul<DAGU>(U, h, chi);
+        reconstruct_scaled<MU, S>(acc[r], chi, x.weight(f));
     }
 }
 

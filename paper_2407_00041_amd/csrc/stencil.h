@@ -113,6 +113,42 @@ __device__ __forceinline__ void reconstruct_scaled(cx<T> acc[12], const cx<T> ch
     }
 }
 
+// A neighbour's spinor as loaded: FP64 and FP32 values, or FP16S halves and
+// their scale.  project_raw leaves the scale out; the hop's factor times the
+// scale (weight) enters once, where the product is added (reconstruct_scaled).
+// The factors are +-1/2, so at FP64 and FP32 this is the projection with the
+// factor, bit for bit, without its multiplications.
+template <int P> struct Raw {
+    using T = typename Store<P>::T;
+    cx<T> p[12];
+    __device__ __forceinline__ void load(const void *base, int V, int s) { Store<P>::load_spinor(base, V, s, p); }
+    __device__ __forceinline__ T weight(T f) const { return f; }
+    __device__ __forceinline__ void half(int b, cx<T> v[6]) const {
+#pragma unroll
+        for (int k = 0; k < 6; k++) v[k] = p[6 * b + k];
+    }
+};
+template <> struct Raw<WDIRAC_F16S> {
+    half8 q[3];
+    float sc;
+    __device__ __forceinline__ void load(const void *base, int V, int s) {
+        sc = Store<WDIRAC_F16S>::load_raw(base, V, s, q);
+    }
+    __device__ __forceinline__ float weight(float f) const { return f * sc; }
+    __device__ __forceinline__ void half(int b, cx<float> v[6]) const {
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const int e = 6 * b + k;
+            v[k] = {sc * (float)q[e >> 2][2 * (e & 3)], sc * (float)q[e >> 2][2 * (e & 3) + 1]};
+        }
+    }
+};
+template <int MU, int S, int P>
+__device__ __forceinline__ void project_raw(const Raw<P> &x, cx<typename Store<P>::T> h[6]) {
+    if constexpr (P == WDIRAC_F16S) project_half<MU, S>(x.q, h);
+    else project_unit<MU, S>(x.p, h);
+}
+
 // chi_s = U h_s (DAGU = false) or U^H h_s (DAGU = true), s = 0, 1
 template <bool DAGU, typename T>
 __device__ __forceinline__ void su3_mul(const cx<T> U[9], const cx<T> h[6], cx<T> chi[6]) {
@@ -150,26 +186,21 @@ __device__ __forceinline__ void clover_block(const T d[6], const cx<T> u[15], co
 template <typename T>
 __device__ __forceinline__ void clover_block_compact(T dg, const T r[28], const cx<T> x[6], cx<T> y[6]) {
     const cx<T> u01 = {r[3], r[4]}, u02 = {r[5], r[6]}, u12 = {r[7], r[8]};
+    // off-diagonal entries of +H (spin 0) and -H (spin 1), then the diagonal
 #pragma unroll
-    for (int c = 0; c < 3; c++) {
-        y[c] = (dg + r[c]) * x[c];
-        y[3 + c] = (dg - r[c]) * x[3 + c];
+    for (int sp = 0; sp < 2; sp++) {
+        const cx<T> *v = x + 3 * sp;
+        cx<T> t[3] = {cmul(u01, v[1]), cjmul(u01, v[0]), cjmul(u02, v[0])};
+        t[0] = cfma(t[0], u02, v[2]);
+        t[1] = cfma(t[1], u12, v[2]);
+        t[2] = cjfma(t[2], u12, v[1]);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const T a = sp ? dg - r[c] : dg + r[c];
+            y[3 * sp + c] = sp ? cx<T>{fma(a, v[c].r, -t[c].r), fma(a, v[c].i, -t[c].i)}
+                               : cx<T>{fma(a, v[c].r, t[c].r), fma(a, v[c].i, t[c].i)};
+        }
     }
-    // off-diagonal entries of +H (spin 0) and -H (spin 1)
-    cx<T> t0 = cmul(u01, x[1]), t1 = cjmul(u01, x[0]), t2 = cjmul(u02, x[0]);
-    t0 = cfma(t0, u02, x[2]);
-    t1 = cfma(t1, u12, x[2]);
-    t2 = cjfma(t2, u12, x[1]);
-    y[0] = y[0] + t0;
-    y[1] = y[1] + t1;
-    y[2] = y[2] + t2;
-    cx<T> b0 = cmul(u01, x[4]), b1 = cjmul(u01, x[3]), b2 = cjmul(u02, x[3]);
-    b0 = cfma(b0, u02, x[5]);
-    b1 = cfma(b1, u12, x[5]);
-    b2 = cjfma(b2, u12, x[4]);
-    y[3] = y[3] - b0;
-    y[4] = y[4] - b1;
-    y[5] = y[5] - b2;
     // spin-off-diagonal block A_01 and its adjoint
 #pragma unroll
     for (int i = 0; i < 3; i++)

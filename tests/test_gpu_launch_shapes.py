@@ -5,10 +5,11 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from oracle import evenodd
 from paper_2407_00041_amd import DiracOp, synth
 
-from util import TOL, fields, need_gpu, rel_l2
+from util import TOL, need_gpu, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -43,4 +44,32 @@ def test_reduced_operator_shapes(dims, n, prec, compress, ap):
     for r in range(n):
         want = evenodd.schur_sites(dims, U, psi[r].cpu().numpy()[even_sites], even_sites[pick], -0.3, 1.0,
                                    antiperiodic_t=ap)
+        assert rel_l2(got[r], want) < TOL[prec], r
+
+
+# applies neither tuned nor set: 12^4 one right-hand side per lane up to 6, pairs at 7 (past 2^17 site-right-hand-
+# sides); 16^4 pairs, at FP32 with two-row links link-stationary from 6; 24 x 16^2 x 24 FP64 columns; 32 x 16^2 x 32
+# FP32 columns too, in pairs with a lone last one; odd extents
+@pytest.mark.parametrize("dims,n", [((12, 12, 12, 12), 6), ((12, 12, 12, 12), 7), ((16, 16, 16, 16), 3),
+                                    ((16, 16, 16, 16), 6), ((24, 16, 16, 24), 2), ((32, 16, 16, 32), 3),
+                                    ((17, 19, 21, 23), 1)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("compress,ap,dagger", [(True, False, False), (False, True, True)])
+def test_untuned_apply_shapes(dims, n, prec, compress, ap, dagger):
+    need_gpu()
+    U = synth.smooth_links(dims, 81, device="cuda").cpu().numpy()
+    op = DiracOp(dims, U, -0.3, 1.0, antiperiodic_t=ap, compress_links=compress, compress_clover=compress)
+    psi = synth.gaussian_spinor(dims, 82, nrhs=n, device="cuda")
+    x = op.pack(psi, prec)
+    out, one = op.empty(prec, n).zero_(), op.empty(prec, 1).zero_()  # a field's padding bytes stay as they are
+    op.apply_native(out, x, n, prec, dagger)
+    rb = op.field_bytes(prec, 1)
+    for r in range(n):
+        op.apply_native(one, x[r * rb:(r + 1) * rb], 1, prec, dagger)
+        assert torch.equal(one, out[r * rb:(r + 1) * rb]), r
+    sites = synth.random_sites(dims, 64, 83)
+    got = op.unpack(out, prec, n)[:, torch.from_numpy(sites).cuda()].cpu().numpy()
+    for r in range(n):
+        want = oracle.dirac_apply_sites(dims, U, psi[r].cpu().numpy(), sites, -0.3, 1.0, antiperiodic_t=ap,
+                                        dagger=dagger)
         assert rel_l2(got[r], want) < TOL[prec], r
