@@ -621,9 +621,9 @@ struct Givens {
     }
 };
 
-int fetch_scalars(const dirac_amg *A, const double2 *src, int n, std::vector<zc> &out, hipStream_t st) {
+// the first n scalars that the stream's kernels leave in the host staging
+int fetch_scalars(const dirac_amg *A, int n, std::vector<zc> &out, hipStream_t st) {
     if ((size_t)n > A->pinned_n) return fail(WDIRAC_EINVAL, "internal: AMG staging buffer too small");
-    AMG_TRY(hipMemcpyAsync(A->pinned, src, n * sizeof(double2), hipMemcpyDeviceToHost, st));
     AMG_TRY(hipStreamSynchronize(st));
     out.resize(n);
     for (int i = 0; i < n; i++) out[i] = zc(A->pinned[i].x, A->pinned[i].y);
@@ -648,9 +648,9 @@ int coarse_gmres(const dirac_amg *A, double2 *x, const double2 *b, long long *it
     double2 *hcol = A->scal, *nrm = A->scal + m + 2;
     AMG_TRY(hipMemsetAsync(x, 0, n * sizeof(double2), st));
     // |b|
-    AMG_TRY(mdot_all<double2>(vl.data(), 0, b, n, A->partial, nrm, st));
+    AMG_TRY(mdot_all<double2>(vl.data(), 0, b, n, A->partial, nrm, st, nullptr, nullptr, A->pinned));
     std::vector<zc> got;
-    int rc = fetch_scalars(A, nrm, 1, got, st);
+    int rc = fetch_scalars(A, 1, got, st);
     if (rc) return rc;
     const double bnorm = std::sqrt(std::max(got[0].real(), 0.0));
     long long applies = 0;
@@ -669,10 +669,11 @@ int coarse_gmres(const dirac_amg *A, double2 *x, const double2 *b, long long *it
         for (int j = 0; j < m; j++) {
             AMG_TRY(coarse_apply_launch(A, vec(j + 1), vec(j), 1, st));
             applies++;
-            AMG_TRY(mdot_all<double2>(vl.data(), j + 1, vec(j + 1), n, A->partial, hcol, st));
-            AMG_TRY(axpy_multi<double2>(vl.data(), j + 1, hcol, nullptr, vec(j + 1), n, A->partial, hcol + j + 1,
-                                        st));
-            rc = fetch_scalars(A, hcol, j + 2, got, st);
+            AMG_TRY(mdot_all<double2>(vl.data(), j + 1, vec(j + 1), n, A->partial, hcol, st, nullptr, nullptr,
+                                      A->pinned));
+            AMG_TRY(axpy_multi<double2>(vl.data(), j + 1, hcol, vec(j + 1), n, A->partial, hcol + j + 1, st,
+                                        A->pinned + j + 1));
+            rc = fetch_scalars(A, j + 2, got, st);
             if (rc) return rc;
             const double hn = std::sqrt(std::max(got[j + 1].real(), 0.0));
             got[j + 1] = hn;
@@ -693,8 +694,8 @@ int coarse_gmres(const dirac_amg *A, double2 *x, const double2 *b, long long *it
         // restart: r = b - D_c x into vec(0)
         AMG_TRY(coarse_apply_launch(A, vec(1), x, 1, st));
         applies++;
-        AMG_TRY(residual(b, vec(1), vec(0), n, A->partial, nrm, st));
-        rc = fetch_scalars(A, nrm, 1, got, st);
+        AMG_TRY(residual(b, vec(1), vec(0), n, A->partial, nrm, st, A->pinned));
+        rc = fetch_scalars(A, 1, got, st);
         if (rc) return rc;
         beta = std::sqrt(std::max(got[0].real(), 0.0));
         if (beta <= target || applies >= A->p.coarse_maxit) break;

@@ -8,9 +8,11 @@
 // solver uses the per-site kernels of blas_site.hip instead.
 //
 // Reductions are deterministic: a fixed grid of kRedBlocks work-groups, each
-// thread summing a fixed strided subset, a fixed LDS tree per work-group,
-// then one work-group per output summing the per-group partials in order.
-// No floating-point atomics.
+// thread summing a fixed strided subset, group_sums per work-group, then one
+// work-group per output summing the per-group partials in order.  No
+// floating-point atomics.  (With an LDS tree over the work-group's 9 x 256
+// values the inner products of one vector took 25 us at 16^4, mostly the tree;
+// now 8.)
 #include "blas.h"
 
 namespace wd {
@@ -23,29 +25,6 @@ template <> struct Elem<double2> {
 
 __device__ __forceinline__ double2 cj_mul(double2 a, double2 b) {  // conj(a) b
     return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
-}
-
-// LDS tree reduction of NV complex values per thread; thread 0 gets the sums
-template <int NV>
-__device__ __forceinline__ void block_reduce(double2 (&v)[NV], double2 *lds) {
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < NV; i++) lds[i * kRedThreads + t] = v[i];
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if (t < s) {
-#pragma unroll
-            for (int i = 0; i < NV; i++) {
-                double2 a = lds[i * kRedThreads + t], b = lds[i * kRedThreads + t + s];
-                lds[i * kRedThreads + t] = make_double2(a.x + b.x, a.y + b.y);
-            }
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-#pragma unroll
-        for (int i = 0; i < NV; i++) v[i] = lds[i * kRedThreads];
-    }
 }
 
 // Inner products of w with up to kGS basis vectors in ONE launch.  The grid
@@ -88,7 +67,7 @@ template <typename S, int NL>
 __global__ __launch_bounds__(kRedThreads) void k_mdot_all(VecList vl, const S *__restrict__ w,
                                                            double2 *__restrict__ partial, long long N, int ngroups,
                                                            int nchunks) {
-    __shared__ double2 lds[(kMdot + 1) * kRedThreads];
+    __shared__ double lds[kRedThreads / 64 * 2 * (kMdot + 1)];
     const int b = blockIdx.x, xcd = b & 7, q = b >> 3;
     const int group = q % ngroups, chunk = (q / ngroups) * 8 + xcd;
     double2 acc[kMdot + 1];
@@ -99,49 +78,55 @@ __global__ __launch_bounds__(kRedThreads) void k_mdot_all(VecList vl, const S *_
         mdot_chunk<S, kMdot>(vl, group * kMdot, w, e0, stride, N, acc);
     else
         mdot_chunk<S, NL>(vl, group * kMdot, w, e0, stride, N, acc);
-    block_reduce<kMdot + 1>(acc, lds);
-    if (threadIdx.x == 0) {
+    double v[2 * (kMdot + 1)];
 #pragma unroll
-        for (int i = 0; i <= kMdot; i++) partial[((size_t)chunk * ngroups + group) * (kMdot + 1) + i] = acc[i];
+    for (int i = 0; i <= kMdot; i++) {
+        v[2 * i] = acc[i].x;
+        v[2 * i + 1] = acc[i].y;
     }
+    const double t = group_sums(v, lds);
+    if (threadIdx.x < 2 * (kMdot + 1))
+        reinterpret_cast<double *>(partial + ((size_t)chunk * ngroups + group) * (kMdot + 1))[threadIdx.x] = t;
+}
+
+// Per work-group sum of entry `at` of n rows of `stride` entries, rows in order; thread 0 gets it
+__device__ __forceinline__ double2 sum_rows(const double2 *__restrict__ partial, int n, size_t stride, double *lds) {
+    double v[2] = {0.0, 0.0};
+    for (int c = threadIdx.x; c < n; c += blockDim.x) {
+        const double2 p = partial[c * stride];
+        v[0] += p.x;
+        v[1] += p.y;
+    }
+    const double t = group_sums(v, lds);
+    return make_double2(t, __shfl(t, 1, 64));
 }
 
 // out[i] (i < nv) = sum over chunks of the inner-product partials of vector i, out[nv].x = |w|^2; one work-group
-// per output, chunks summed in order
+// per output, chunks summed in order; scaled and host as in mdot_all
 __global__ __launch_bounds__(kRedThreads) void k_colsum_groups(const double2 *__restrict__ partial, int nchunks,
-                                                                int ngroups, int nv, double2 *__restrict__ out) {
-    __shared__ double2 lds[kRedThreads];
+                                                                int ngroups, int nv, double2 *__restrict__ out,
+                                                                ScaleList sl, double2 *__restrict__ scaled,
+                                                                double2 *__restrict__ host) {
+    __shared__ double lds[kRedThreads / 64 * 2];
     const int i = blockIdx.x;
     const int group = i < nv ? i / kMdot : 0, col = i < nv ? i % kMdot : kMdot;
-    double2 a[1] = {make_double2(0, 0)};
-    for (int c = threadIdx.x; c < nchunks; c += blockDim.x) {
-        const double2 p = partial[((size_t)c * ngroups + group) * (kMdot + 1) + col];
-        a[0].x += p.x;
-        a[0].y += p.y;
+    const double2 a = sum_rows(partial + (size_t)group * (kMdot + 1) + col, nchunks, (size_t)ngroups * (kMdot + 1), lds);
+    if (threadIdx.x == 0) {
+        out[i] = a;
+        if (host) host[i] = a;
+        if (scaled && i < nv) scaled[i] = make_double2(a.x * sl.s[i], a.y * sl.s[i]);
     }
-    block_reduce<1>(a, lds);
-    if (threadIdx.x == 0) out[i] = a[0];
 }
 
-// out[i] = sum over groups of partial[g][i], i < ncols (one work-group per i);
-// stride = number of columns per partial row
-__global__ __launch_bounds__(kRedThreads) void k_colsum(const double2 *__restrict__ partial, int ngroups, int stride,
-                                                        double2 *__restrict__ out) {
-    __shared__ double2 lds[kRedThreads];
-    double2 a[1] = {make_double2(0, 0)};
-    for (int g = threadIdx.x; g < ngroups; g += blockDim.x) {
-        double2 p = partial[(size_t)g * stride + blockIdx.x];
-        a[0].x += p.x;
-        a[0].y += p.y;
+// out[0] = sum over groups of partial[g]
+__global__ __launch_bounds__(kRedThreads) void k_colsum(const double2 *__restrict__ partial, int ngroups,
+                                                        double2 *__restrict__ out, double2 *__restrict__ host) {
+    __shared__ double lds[kRedThreads / 64 * 2];
+    const double2 a = sum_rows(partial, ngroups, 1, lds);
+    if (threadIdx.x == 0) {
+        out[0] = a;
+        if (host) host[0] = a;
     }
-    block_reduce<1>(a, lds);
-    if (threadIdx.x == 0) out[blockIdx.x] = a[0];
-}
-
-// cs[i] = coef[i] * sl.s[i], i < n (one work-group of kGS lanes)
-__global__ void k_scale_coef(const double2 *__restrict__ coef, ScaleList sl, int n, double2 *__restrict__ cs) {
-    const int i = threadIdx.x;
-    if (i < n) cs[i] = make_double2(coef[i].x * sl.s[i], coef[i].y * sl.s[i]);
 }
 
 // w -= sum_i cs[i] v_i over NV vectors (a template parameter: the loads of all NV vectors of an element are issued
@@ -151,8 +136,8 @@ template <typename S, int NV>
 __global__ __launch_bounds__(kRedThreads) void k_axpy_multi(VecList vl, const double2 *__restrict__ cs,
                                                              S *__restrict__ w, double2 *__restrict__ partial,
                                                              long long N) {
-    __shared__ double2 lds[kRedThreads];
-    double2 nrm[1] = {make_double2(0, 0)};
+    __shared__ double lds[kRedThreads / 64];
+    double nrm[1] = {0.0};
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < N; e += stride) {
         double2 we = Elem<S>::ld(w, e);
@@ -166,11 +151,11 @@ __global__ __launch_bounds__(kRedThreads) void k_axpy_multi(VecList vl, const do
             we.y -= c.x * vv[i].y + c.y * vv[i].x;
         }
         Elem<S>::st(w, e, we);
-        nrm[0].x += we.x * we.x + we.y * we.y;
+        nrm[0] += we.x * we.x + we.y * we.y;
     }
     if (partial) {
-        block_reduce<1>(nrm, lds);
-        if (threadIdx.x == 0) partial[blockIdx.x] = nrm[0];
+        const double t = group_sums(nrm, lds);
+        if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(t, 0.0);
     }
 }
 
@@ -191,17 +176,17 @@ __global__ __launch_bounds__(kRedThreads) void k_scale(const SI *__restrict__ in
 __global__ __launch_bounds__(kRedThreads) void k_residual(const double2 *__restrict__ b, const double2 *__restrict__ w,
                                                            double2 *__restrict__ r, double2 *__restrict__ partial,
                                                            long long N) {
-    __shared__ double2 lds[kRedThreads];
-    double2 nrm[1] = {make_double2(0, 0)};
+    __shared__ double lds[kRedThreads / 64];
+    double nrm[1] = {0.0};
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < N; e += stride) {
         double2 a = b[e], c = w[e];
         double2 d = make_double2(a.x - c.x, a.y - c.y);
         r[e] = d;
-        nrm[0].x += d.x * d.x + d.y * d.y;
+        nrm[0] += d.x * d.x + d.y * d.y;
     }
-    block_reduce<1>(nrm, lds);
-    if (threadIdx.x == 0) partial[blockIdx.x] = nrm[0];
+    const double t = group_sums(nrm, lds);
+    if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(t, 0.0);
 }
 
 // x += sum_i c_i z_i over NV vectors (x FP64, z of storage S; coefficients passed by value)
@@ -240,7 +225,7 @@ static int red_grid(long long N) {
 
 template <typename S>
 hipError_t mdot_all(const void *const *v, int nv, const void *w, long long N, double2 *partial, double2 *out,
-                    hipStream_t st) {
+                    hipStream_t st, const double *cscale, double2 *scaled, double2 *host) {
     const int nchunks = (red_grid(N) + 7) / 8 * 8;
     for (int i0 = 0; i0 < nv || i0 == 0; i0 += kGS) {
         VecList vl;
@@ -261,31 +246,27 @@ hipError_t mdot_all(const void *const *v, int nv, const void *w, long long N, do
         }
         const bool last = i0 + kGS >= nv;
         // outputs of this launch: its vl.n products, plus |w|^2 after the last one
+        ScaleList sl;
+        for (int i = 0; i < kGS; i++) sl.s[i] = (i < vl.n && cscale) ? cscale[i0 + i] : 1.0;
         hipLaunchKernelGGL(k_colsum_groups, dim3(vl.n + (last ? 1 : 0)), dim3(kRedThreads), 0, st, partial, nchunks,
-                           ngroups, vl.n, out + i0);
+                           ngroups, vl.n, out + i0, sl, scaled ? scaled + i0 : nullptr, host ? host + i0 : nullptr);
         if (last) break;
     }
     return hipGetLastError();
 }
 
 template <typename S>
-hipError_t axpy_multi(const void *const *v, int nv, const double2 *coef, const double *cscale, void *w, long long N,
-                      double2 *partial, double2 *norm_out, hipStream_t st) {
+hipError_t axpy_multi(const void *const *v, int nv, const double2 *coef, void *w, long long N, double2 *partial,
+                      double2 *norm_out, hipStream_t st, double2 *host) {
     const int G = red_grid(N);
     for (int i0 = 0; i0 < nv; i0 += kGS) {
         VecList vl;
-        ScaleList sl;
         vl.n = nv - i0 < kGS ? nv - i0 : kGS;
-        for (int i = 0; i < kGS; i++) {
-            vl.v[i] = i < vl.n ? v[i0 + i] : w;
-            sl.s[i] = (i < vl.n && cscale) ? cscale[i0 + i] : 1.0;
-        }
+        for (int i = 0; i < kGS; i++) vl.v[i] = i < vl.n ? v[i0 + i] : w;
         const bool last = i0 + kGS >= nv;
         double2 *pt = (last && norm_out) ? partial : (double2 *)nullptr;
         S *ws = static_cast<S *>(w);
-        // scaled coefficients after the first kRedBlocks entries of partial (the norm partials of this pass)
-        double2 *cs = partial + kRedBlocks;
-        hipLaunchKernelGGL(k_scale_coef, dim3(1), dim3(kGS), 0, st, coef + i0, sl, vl.n, cs);
+        const double2 *cs = coef + i0;
         switch (vl.n) {
 #define WD_AXPY_CASE(n) \
     case n: hipLaunchKernelGGL((k_axpy_multi<S, n>), dim3(G), dim3(kRedThreads), 0, st, vl, cs, ws, pt, N); break;
@@ -293,8 +274,7 @@ hipError_t axpy_multi(const void *const *v, int nv, const double2 *coef, const d
 #undef WD_AXPY_CASE
         default: return hipErrorInvalidValue;
         }
-        if (last && norm_out)
-            hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kRedThreads), 0, st, partial, G, 1, norm_out);
+        if (last && norm_out) hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kRedThreads), 0, st, partial, G, norm_out, host);
     }
     return hipGetLastError();
 }
@@ -308,10 +288,10 @@ hipError_t scale(const void *in, void *out, const double2 *sc, bool inv_sqrt, do
 }
 
 hipError_t residual(const double2 *b, const double2 *w, double2 *r, long long N, double2 *partial, double2 *norm_out,
-                    hipStream_t st) {
+                    hipStream_t st, double2 *host) {
     const int G = red_grid(N);
     hipLaunchKernelGGL(k_residual, dim3(G), dim3(kRedThreads), 0, st, b, w, r, partial, N);
-    hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kRedThreads), 0, st, partial, G, 1, norm_out);
+    hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kRedThreads), 0, st, partial, G, norm_out, host);
     return hipGetLastError();
 }
 
@@ -337,9 +317,9 @@ hipError_t update(const void *const *z, int nz, const double2 *coef, double2 *x,
 }
 
 template hipError_t mdot_all<double2>(const void *const *, int, const void *, long long, double2 *, double2 *,
-                                      hipStream_t);
-template hipError_t axpy_multi<double2>(const void *const *, int, const double2 *, const double *, void *, long long,
-                                        double2 *, double2 *, hipStream_t);
+                                      hipStream_t, const double *, double2 *, double2 *);
+template hipError_t axpy_multi<double2>(const void *const *, int, const double2 *, void *, long long, double2 *,
+                                        double2 *, hipStream_t, double2 *);
 template hipError_t scale<double2, double2>(const void *, void *, const double2 *, bool, double, long long,
                                             hipStream_t);
 template hipError_t update<double2>(const void *const *, int, const double2 *, double2 *, long long, hipStream_t);

@@ -12,9 +12,10 @@
 // their coefficients from device memory, so a whole cycle can be issued
 // without host decisions (and captured as a graph).
 //
-// Reductions are deterministic: a fixed grid of kRedBlocks work-groups, each
-// thread summing a fixed strided subset of sites, a fixed LDS tree per
-// work-group, then k_colsum adding the per-group partials in order.
+// Reductions are deterministic: a fixed grid of at most kRedBlocks work-groups
+// per right-hand side, each thread summing a fixed strided subset of sites,
+// group_sums per work-group; the inner cycle's state kernels add the per-group
+// partials in order.
 #include "blas.h"
 #include "spinor_io.h"
 
@@ -38,102 +39,87 @@ template <int P> struct SiteIO {
     }
 };
 
-template <int NV>
-__device__ __forceinline__ void reduce_block(double2 (&v)[NV], double2 *lds) {
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < NV; i++) lds[i * kRedThreads + t] = v[i];
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if (t < s) {
-#pragma unroll
-            for (int i = 0; i < NV; i++) {
-                double2 a = lds[i * kRedThreads + t], b = lds[i * kRedThreads + t + s];
-                lds[i * kRedThreads + t] = make_double2(a.x + b.x, a.y + b.y);
-            }
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-#pragma unroll
-        for (int i = 0; i < NV; i++) v[i] = lds[i * kRedThreads];
-    }
-}
+// the kernels' right-hand sides (blockIdx.y) and one pass of their vectors
+constexpr int kSiteBatch = 16;
+struct SiteRhs {
+    const void *v[kGSSite];
+    void *w;
+    double2 *partial;
+    const double2 *coef, *hdr;
+};
+struct SiteBatch {
+    SiteRhs r[kSiteBatch];
+};
 
 }  // namespace
 
-// partial[blk][i] = sum over the group's sites of v_i^H w (i < n), [kGSSite] = |w|^2
-template <int P>
-__global__ __launch_bounds__(kRedThreads) void k_site_mdot(VecList vl, const void *__restrict__ w,
-                                                            double2 *__restrict__ partial, const double2 *hdr, int V) {
-    if (hdr && hdr[0].y == 0.0) return;
-    __shared__ double2 lds[(kGSSite + 1) * kRedThreads];
-    double2 acc[kGSSite + 1];
+// columns i0 .. i0 + n of the partials (rows of nv + 1): sums of v_i^H w over the group's sites, with the last pass
+// (NORM) |w|^2 in column nv
+template <int P, int N, bool NORM>
+__global__ __launch_bounds__(kRedThreads) void k_site_mdot(SiteBatch b, int i0, int nv, int V) {
+    const SiteRhs &q = b.r[blockIdx.y];
+    if (q.hdr[0].y == 0.0) return;
+    constexpr int ND = 2 * N + (NORM ? 1 : 0);
+    __shared__ double lds[kRedThreads / 64 * ND];
+    double acc[ND];
 #pragma unroll
-    for (int i = 0; i <= kGSSite; i++) acc[i] = make_double2(0, 0);
+    for (int i = 0; i < ND; i++) acc[i] = 0.0;
     for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < V; s += gridDim.x * blockDim.x) {
         double2 wv[12];
-        SiteIO<P>::load(w, V, s, wv);
+        SiteIO<P>::load(q.w, V, s, wv);
+        if constexpr (NORM) {
 #pragma unroll
-        for (int k = 0; k < 12; k++) acc[kGSSite].x += wv[k].x * wv[k].x + wv[k].y * wv[k].y;
+            for (int k = 0; k < 12; k++) acc[2 * N] += wv[k].x * wv[k].x + wv[k].y * wv[k].y;
+        }
 #pragma unroll
-        for (int i = 0; i < kGSSite; i++) {
-            if (i < vl.n) {
-                double2 vv[12];
-                SiteIO<P>::load(vl.v[i], V, s, vv);
+        for (int i = 0; i < N; i++) {
+            double2 vv[12];
+            SiteIO<P>::load(q.v[i], V, s, vv);
 #pragma unroll
-                for (int k = 0; k < 12; k++) {
-                    acc[i].x += vv[k].x * wv[k].x + vv[k].y * wv[k].y;
-                    acc[i].y += vv[k].x * wv[k].y - vv[k].y * wv[k].x;
-                }
+            for (int k = 0; k < 12; k++) {
+                acc[2 * i] += vv[k].x * wv[k].x + vv[k].y * wv[k].y;
+                acc[2 * i + 1] += vv[k].x * wv[k].y - vv[k].y * wv[k].x;
             }
         }
     }
-    reduce_block<kGSSite + 1>(acc, lds);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int i = 0; i <= kGSSite; i++) partial[(size_t)blockIdx.x * (kGSSite + 1) + i] = acc[i];
-    }
+    const double t = group_sums(acc, lds);
+    if (threadIdx.x < ND) reinterpret_cast<double *>(q.partial + (size_t)blockIdx.x * (nv + 1) + i0)[threadIdx.x] = t;
 }
 
-// w = f (w - sum_i coef[i] v_i), coefficients on the device; f = hdr[1].x when
-// apply_f (last pass) and hdr are set, else 1.  partial[blk] = |w_new|^2 of the
-// re-encoded values' source (before rounding) when partial != null.
-template <int P>
-__global__ __launch_bounds__(kRedThreads) void k_site_axpy(VecList vl, const double2 *__restrict__ coef,
-                                                            void *__restrict__ w, double2 *__restrict__ partial,
-                                                            const double2 *hdr, int apply_f, int V) {
-    if (hdr && hdr[0].y == 0.0) return;
-    __shared__ double2 lds[kRedThreads];
-    const double f = (hdr && apply_f) ? hdr[1].x : 1.0;
-    double2 nrm[1] = {make_double2(0, 0)};
-    double2 c[kGSSite];
+// w = f (w - sum_i coef[i] v_i), coefficients on the device; f = hdr[1].x with the last pass, else 1, which also
+// leaves partial[blk] = |w_new|^2 of the re-encoded values' source (before rounding)
+template <int P, int N>
+__global__ __launch_bounds__(kRedThreads) void k_site_axpy(SiteBatch b, int i0, int last, int V) {
+    const SiteRhs &q = b.r[blockIdx.y];
+    if (q.hdr[0].y == 0.0) return;
+    __shared__ double lds[kRedThreads / 64];
+    const double f = last ? q.hdr[1].x : 1.0;
+    double nrm[1] = {0.0};
+    double2 c[N];
 #pragma unroll
-    for (int i = 0; i < kGSSite; i++) c[i] = i < vl.n ? coef[i] : make_double2(0, 0);
+    for (int i = 0; i < N; i++) c[i] = q.coef[i0 + i];
     for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < V; s += gridDim.x * blockDim.x) {
         double2 wv[12];
-        SiteIO<P>::load(w, V, s, wv);
+        SiteIO<P>::load(q.w, V, s, wv);
 #pragma unroll
-        for (int i = 0; i < kGSSite; i++) {
-            if (i < vl.n) {
-                double2 vv[12];
-                SiteIO<P>::load(vl.v[i], V, s, vv);
+        for (int i = 0; i < N; i++) {
+            double2 vv[12];
+            SiteIO<P>::load(q.v[i], V, s, vv);
 #pragma unroll
-                for (int k = 0; k < 12; k++) {
-                    wv[k].x -= c[i].x * vv[k].x - c[i].y * vv[k].y;
-                    wv[k].y -= c[i].x * vv[k].y + c[i].y * vv[k].x;
-                }
+            for (int k = 0; k < 12; k++) {
+                wv[k].x -= c[i].x * vv[k].x - c[i].y * vv[k].y;
+                wv[k].y -= c[i].x * vv[k].y + c[i].y * vv[k].x;
             }
         }
 #pragma unroll
         for (int k = 0; k < 12; k++) wv[k] = make_double2(wv[k].x * f, wv[k].y * f);
-        SiteIO<P>::store(w, V, s, wv);
+        SiteIO<P>::store(q.w, V, s, wv);
 #pragma unroll
-        for (int k = 0; k < 12; k++) nrm[0].x += wv[k].x * wv[k].x + wv[k].y * wv[k].y;
+        for (int k = 0; k < 12; k++) nrm[0] += wv[k].x * wv[k].x + wv[k].y * wv[k].y;
     }
-    if (partial) {
-        reduce_block<1>(nrm, lds);
-        if (threadIdx.x == 0) partial[blockIdx.x] = nrm[0];
+    if (last) {
+        const double t = group_sums(nrm, lds);
+        if (threadIdx.x == 0) q.partial[blockIdx.x] = make_double2(t, 0.0);
     }
 }
 
@@ -150,22 +136,21 @@ __global__ __launch_bounds__(kRedThreads) void k_site_scale(const void *__restri
     }
 }
 
-// x (native FP64) = keep * x + sum_{i < n} coef[i] z_i, z_i of precision P,
+// w (native FP64) = keep * w + sum_{i < n} coef[i] v_i, v_i of precision P,
 // n = min(kGSSite, count - i0) with count = hdr[0].x (device coefficients)
 template <int P>
-__global__ __launch_bounds__(kRedThreads) void k_site_combine(VecList vl, const double2 *__restrict__ coef,
-                                                               const double2 *hdr, int i0, double2 *__restrict__ x,
-                                                               int V) {
-    const int count = (int)hdr[0].x;
+__global__ __launch_bounds__(kRedThreads) void k_site_combine(SiteBatch b, int i0, int V) {
+    const SiteRhs &q = b.r[blockIdx.y];
+    const int count = (int)q.hdr[0].x;
     const int n = count - i0 < kGSSite ? count - i0 : kGSSite;
     if (i0 > 0 && n <= 0) return;
     double2 c[kGSSite];
 #pragma unroll
-    for (int i = 0; i < kGSSite; i++) c[i] = i < n ? coef[i] : make_double2(0, 0);
+    for (int i = 0; i < kGSSite; i++) c[i] = i < n ? q.coef[i0 + i] : make_double2(0, 0);
     for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < V; s += gridDim.x * blockDim.x) {
         double2 xv[12];
         if (i0 > 0) {
-            SiteIO<WDIRAC_F64>::load(x, V, s, xv);
+            SiteIO<WDIRAC_F64>::load(q.w, V, s, xv);
         } else {
 #pragma unroll
             for (int k = 0; k < 12; k++) xv[k] = make_double2(0, 0);
@@ -174,7 +159,7 @@ __global__ __launch_bounds__(kRedThreads) void k_site_combine(VecList vl, const 
         for (int i = 0; i < kGSSite; i++) {
             if (i < n) {
                 double2 zv[12];
-                SiteIO<P>::load(vl.v[i], V, s, zv);
+                SiteIO<P>::load(q.v[i], V, s, zv);
 #pragma unroll
                 for (int k = 0; k < 12; k++) {
                     xv[k].x += c[i].x * zv[k].x - c[i].y * zv[k].y;
@@ -182,7 +167,7 @@ __global__ __launch_bounds__(kRedThreads) void k_site_combine(VecList vl, const 
                 }
             }
         }
-        SiteIO<WDIRAC_F64>::store(x, V, s, xv);
+        SiteIO<WDIRAC_F64>::store(q.w, V, s, xv);
     }
 }
 
@@ -192,75 +177,98 @@ static int site_grid(int V) {
     const int g = (V + kRedThreads - 1) / kRedThreads;
     return g < kRedBlocks ? g : kRedBlocks;
 }
+int site_groups(int V) { return site_grid(V); }
+
+// vectors i0 .. i0 + n of items r0 ..
+static SiteBatch site_batch(const SiteItem *items, int r0, int nr, int i0, int n) {
+    SiteBatch b;
+    for (int r = 0; r < kSiteBatch; r++) {
+        const SiteItem &q = items[r0 + (r < nr ? r : 0)];
+        for (int i = 0; i < kGSSite; i++) b.r[r].v[i] = i < n ? q.v[i0 + i] : q.w;
+        b.r[r].w = q.w;
+        b.r[r].partial = q.partial;
+        b.r[r].coef = q.coef;
+        b.r[r].hdr = q.hdr;
+    }
+    return b;
+}
+
+#define WD_SITE_CASES(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+static_assert(kGSSite == 8, "WD_SITE_CASES lists 1 .. kGSSite");
 
 template <int P>
-static hipError_t site_mdot_p(const void *const *v, int nv, const void *w, int V, double2 *partial, double2 *out,
-                              const double2 *hdr, hipStream_t st) {
-    const int G = site_grid(V);
-    for (int i0 = 0;; i0 += kGSSite) {
-        VecList vl;
-        vl.n = nv - i0 < kGSSite ? nv - i0 : kGSSite;
-        if (vl.n < 0) vl.n = 0;
-        for (int i = 0; i < kGSSite; i++) vl.v[i] = i < vl.n ? v[i0 + i] : w;
-        hipLaunchKernelGGL(k_site_mdot<P>, dim3(G), dim3(kRedThreads), 0, st, vl, w, partial, hdr, V);
-        if (vl.n > 0)
-            hipLaunchKernelGGL(k_colsum, dim3(vl.n), dim3(kRedThreads), 0, st, partial, G, kGSSite + 1, out + i0);
-        if (i0 + kGSSite >= nv) {
-            hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kRedThreads), 0, st, partial + kGSSite, G, kGSSite + 1, out + nv);
-            break;
+static hipError_t site_mdot_p(const SiteItem *items, int nr, int nv, int V, hipStream_t st) {
+    for (int r0 = 0; r0 < nr; r0 += kSiteBatch) {
+        const int m = nr - r0 < kSiteBatch ? nr - r0 : kSiteBatch;
+        const dim3 grid(site_grid(V), m), blk(kRedThreads);
+        for (int i0 = 0; i0 < nv; i0 += kGSSite) {
+            const int n = nv - i0 < kGSSite ? nv - i0 : kGSSite;
+            const bool last = i0 + kGSSite >= nv;
+            const SiteBatch b = site_batch(items, r0, m, i0, n);
+            if (!last) {
+                hipLaunchKernelGGL((k_site_mdot<P, kGSSite, false>), grid, blk, 0, st, b, i0, nv, V);
+                continue;
+            }
+            switch (n) {
+#define WD_CASE(k) \
+    case k: hipLaunchKernelGGL((k_site_mdot<P, k, true>), grid, blk, 0, st, b, i0, nv, V); break;
+                WD_SITE_CASES(WD_CASE)
+#undef WD_CASE
+            }
         }
     }
     return hipGetLastError();
 }
 
 template <int P>
-static hipError_t site_axpy_p(const void *const *v, int nv, const double2 *coef, void *w, int V, double2 *partial,
-                              double2 *norm_out, const double2 *hdr, hipStream_t st) {
-    const int G = site_grid(V);
-    for (int i0 = 0; i0 < nv; i0 += kGSSite) {
-        VecList vl;
-        vl.n = nv - i0 < kGSSite ? nv - i0 : kGSSite;
-        for (int i = 0; i < kGSSite; i++) vl.v[i] = i < vl.n ? v[i0 + i] : w;
-        const bool last = i0 + kGSSite >= nv;
-        hipLaunchKernelGGL(k_site_axpy<P>, dim3(G), dim3(kRedThreads), 0, st, vl, coef + i0, w,
-                           (last && norm_out) ? partial : (double2 *)nullptr, hdr, last ? 1 : 0, V);
-        if (last && norm_out)
-            hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kRedThreads), 0, st, partial, G, 1, norm_out);
+static hipError_t site_axpy_p(const SiteItem *items, int nr, int nv, int V, hipStream_t st) {
+    for (int r0 = 0; r0 < nr; r0 += kSiteBatch) {
+        const int m = nr - r0 < kSiteBatch ? nr - r0 : kSiteBatch;
+        const dim3 grid(site_grid(V), m), blk(kRedThreads);
+        for (int i0 = 0; i0 < nv; i0 += kGSSite) {
+            const int n = nv - i0 < kGSSite ? nv - i0 : kGSSite;
+            const int last = i0 + kGSSite >= nv ? 1 : 0;
+            const SiteBatch b = site_batch(items, r0, m, i0, n);
+            switch (n) {
+#define WD_CASE(k) \
+    case k: hipLaunchKernelGGL((k_site_axpy<P, k>), grid, blk, 0, st, b, i0, last, V); break;
+                WD_SITE_CASES(WD_CASE)
+#undef WD_CASE
+            }
+        }
     }
     return hipGetLastError();
 }
 
 template <int P>
-static hipError_t site_combine_p(const void *const *z, int nmax, const double2 *coef, const double2 *hdr, double2 *x,
-                                 int V, hipStream_t st) {
-    for (int i0 = 0;; i0 += kGSSite) {
-        VecList vl;
-        vl.n = nmax - i0 < kGSSite ? nmax - i0 : kGSSite;
-        if (vl.n < 0) vl.n = 0;
-        for (int i = 0; i < kGSSite; i++) vl.v[i] = i < vl.n ? z[i0 + i] : nullptr;
-        hipLaunchKernelGGL(k_site_combine<P>, dim3(site_grid(V)), dim3(kRedThreads), 0, st, vl, coef + i0, hdr, i0,
-                           x, V);
-        if (i0 + kGSSite >= nmax) break;
+static hipError_t site_combine_p(const SiteItem *items, int nr, int nmax, int V, hipStream_t st) {
+    for (int r0 = 0; r0 < nr; r0 += kSiteBatch) {
+        const int m = nr - r0 < kSiteBatch ? nr - r0 : kSiteBatch;
+        for (int i0 = 0;; i0 += kGSSite) {
+            int n = nmax - i0 < kGSSite ? nmax - i0 : kGSSite;
+            if (n < 0) n = 0;
+            const SiteBatch b = site_batch(items, r0, m, i0, n);
+            hipLaunchKernelGGL(k_site_combine<P>, dim3(site_grid(V), m), dim3(kRedThreads), 0, st, b, i0, V);
+            if (i0 + kGSSite >= nmax) break;
+        }
     }
     return hipGetLastError();
 }
 
-hipError_t site_mdot(int prec, const void *const *v, int nv, const void *w, int V, double2 *partial, double2 *out,
-                     const double2 *hdr, hipStream_t st) {
+hipError_t site_mdot(int prec, const SiteItem *items, int n, int nv, int V, hipStream_t st) {
     switch (prec) {
-    case WDIRAC_F64: return site_mdot_p<WDIRAC_F64>(v, nv, w, V, partial, out, hdr, st);
-    case WDIRAC_F32: return site_mdot_p<WDIRAC_F32>(v, nv, w, V, partial, out, hdr, st);
-    case WDIRAC_F16S: return site_mdot_p<WDIRAC_F16S>(v, nv, w, V, partial, out, hdr, st);
+    case WDIRAC_F64: return site_mdot_p<WDIRAC_F64>(items, n, nv, V, st);
+    case WDIRAC_F32: return site_mdot_p<WDIRAC_F32>(items, n, nv, V, st);
+    case WDIRAC_F16S: return site_mdot_p<WDIRAC_F16S>(items, n, nv, V, st);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t site_axpy(int prec, const void *const *v, int nv, const double2 *coef, void *w, int V, double2 *partial,
-                     double2 *norm_out, const double2 *hdr, hipStream_t st) {
+hipError_t site_axpy(int prec, const SiteItem *items, int n, int nv, int V, hipStream_t st) {
     switch (prec) {
-    case WDIRAC_F64: return site_axpy_p<WDIRAC_F64>(v, nv, coef, w, V, partial, norm_out, hdr, st);
-    case WDIRAC_F32: return site_axpy_p<WDIRAC_F32>(v, nv, coef, w, V, partial, norm_out, hdr, st);
-    case WDIRAC_F16S: return site_axpy_p<WDIRAC_F16S>(v, nv, coef, w, V, partial, norm_out, hdr, st);
+    case WDIRAC_F64: return site_axpy_p<WDIRAC_F64>(items, n, nv, V, st);
+    case WDIRAC_F32: return site_axpy_p<WDIRAC_F32>(items, n, nv, V, st);
+    case WDIRAC_F16S: return site_axpy_p<WDIRAC_F16S>(items, n, nv, V, st);
     }
     return hipErrorInvalidValue;
 }
@@ -281,12 +289,11 @@ hipError_t site_scale(int pin, int pout, const void *in, void *out, double mult,
     return hipErrorInvalidValue;
 }
 
-hipError_t site_combine(int prec, const void *const *z, int nmax, const double2 *coef, const double2 *hdr, double2 *x,
-                        int V, hipStream_t st) {
+hipError_t site_combine(int prec, const SiteItem *items, int n, int nmax, int V, hipStream_t st) {
     switch (prec) {
-    case WDIRAC_F64: return site_combine_p<WDIRAC_F64>(z, nmax, coef, hdr, x, V, st);
-    case WDIRAC_F32: return site_combine_p<WDIRAC_F32>(z, nmax, coef, hdr, x, V, st);
-    case WDIRAC_F16S: return site_combine_p<WDIRAC_F16S>(z, nmax, coef, hdr, x, V, st);
+    case WDIRAC_F64: return site_combine_p<WDIRAC_F64>(items, n, nmax, V, st);
+    case WDIRAC_F32: return site_combine_p<WDIRAC_F32>(items, n, nmax, V, st);
+    case WDIRAC_F16S: return site_combine_p<WDIRAC_F16S>(items, n, nmax, V, st);
     }
     return hipErrorInvalidValue;
 }

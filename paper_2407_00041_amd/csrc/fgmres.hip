@@ -77,7 +77,9 @@ struct InnerDev {
     double2 *sn;          // [mi] rotation sines
     double2 *g;           // [mi + 1] rotated right-hand side beta e_1
     double2 *coef;        // [mi + 1] update coefficients of a step; at the end y_i / c_i
-    const double2 *hcol;  // [mi + 2] inner products of the current step (mdot / axpy results)
+    double2 *hcol;          // [mi + 2] inner products of the current step (mdot / axpy sums)
+    const double2 *partial; // work-group partials of the step's sums
+    double2 *host;          // host staging entry that receives hdr[0] at the cycle's end
 };
 
 size_t inner_state_bytes(int mi) {
@@ -86,7 +88,7 @@ size_t inner_state_bytes(int mi) {
     return n2 * sizeof(double2) + n1 * sizeof(double) + 64;
 }
 
-InnerDev carve_inner(char *base, int mi, const double2 *hcol) {
+InnerDev carve_inner(char *base, int mi, double2 *hcol, const double2 *partial, double2 *host) {
     InnerDev d;
     double2 *q = reinterpret_cast<double2 *>(base);
     d.hdr = q;
@@ -104,6 +106,8 @@ InnerDev carve_inner(char *base, int mi, const double2 *hcol) {
     r += mi + 1;
     d.cs = r;
     d.hcol = hcol;
+    d.partial = partial;
+    d.host = host;
     return d;
 }
 
@@ -139,15 +143,33 @@ __global__ void k_inner_init(InnerList L) {
     for (int i = 1; i <= L.mi; i++) d.g[i] = make_double2(0.0, 0.0);
 }
 
-// step k, after the inner products d_i = W_i^H w (i <= k) and |w|^2 of
-// w = D W_k: orthogonalisation coefficients d_i / c_i^2 and the factor f that
-// brings the orthogonalised vector near unit norm (Pythagorean estimate;
-// with severe cancellation f = 1/|w| instead)
-__global__ void k_inner_prep(InnerList L, int k) {
-    const int t = threadIdx.x;
-    if (t >= L.n) return;
-    const InnerDev &d = L.d[t];
+constexpr int kStateThreads = 256;
+
+// step k, after the inner-product partials (G rows of k + 2): their sums d_i = W_i^H w (i <= k) and |w|^2 of
+// w = D W_k, then the orthogonalisation coefficients d_i / c_i^2 and the factor f that brings the orthogonalised
+// vector near unit norm (Pythagorean estimate; with severe cancellation f = 1/|w| instead).  One work-group per
+// right-hand side, wave by wave over the sums.
+__global__ __launch_bounds__(kStateThreads) void k_inner_prep(InnerList L, int k, int G) {
+    const InnerDev &d = L.d[blockIdx.x];
     if (d.hdr[0].y == 0.0) return;
+    const int lane = threadIdx.x & 63;
+    for (int c = threadIdx.x >> 6; c < k + 2; c += kStateThreads / 64) {
+        double2 t = make_double2(0.0, 0.0);
+        for (int g = lane; g < G; g += 64) {
+            const double2 p = d.partial[(size_t)g * (k + 2) + c];
+            t.x += p.x;
+            // the |w|^2 column holds a real number
+            t.y += c <= k ? p.y : 0.0;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            t.x += __shfl_xor(t.x, o, 64);
+            t.y += __shfl_xor(t.y, o, 64);
+        }
+        if (lane == 0) d.hcol[c] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x) return;
     const double w2 = d.hcol[k + 1].x;
     double proj = 0.0;
     for (int i = 0; i <= k; i++) {
@@ -160,18 +182,22 @@ __global__ void k_inner_prep(InnerList L, int k) {
     d.hdr[1].x = rem > 1e-8 * w2 ? 1.0 / sqrt(rem) : (w2 > 0.0 ? 1.0 / sqrt(w2) : 1.0);
 }
 
-// step k, after the in-place orthogonalisation: Hessenberg column k, Givens
-// rotation, residual estimate |g_{k+1}|, termination test
-__global__ void k_inner_givens(InnerList L, int k, double tol, int maxit) {
-    const int t = threadIdx.x;
-    if (t >= L.n) return;
-    const InnerDev &d = L.d[t];
+// step k, after the in-place orthogonalisation (G partials of the new norm): Hessenberg column k, Givens rotation,
+// residual estimate |g_{k+1}|, termination test.  report: the host reads the cycle's state after this step
+__global__ __launch_bounds__(kStateThreads) void k_inner_givens(InnerList L, int k, double tol, int maxit, int G,
+                                                                int report) {
+    const InnerDev &d = L.d[blockIdx.x];
     if (d.hdr[0].y == 0.0) return;
+    __shared__ double lds[kStateThreads / 64];
+    double v[1] = {0.0};
+    for (int g = threadIdx.x; g < G; g += kStateThreads) v[0] += d.partial[g].x;
+    const double n2 = group_sums(v, lds);
+    if (threadIdx.x) return;
     const int ld = L.mi + 1;
     double2 *col = d.H + (size_t)k * ld;
     const double ck = d.ic[k];
     for (int i = 0; i <= k; i++) col[i] = c_scale(1.0 / (d.ic[i] * ck), d.hcol[i]);
-    const double nrm = sqrt(fmax(d.hcol[k + 1].x, 0.0));  // |W_{k+1}| = f c_k h_{k+1,k}
+    const double nrm = sqrt(fmax(n2, 0.0));  // |W_{k+1}| = f c_k h_{k+1,k}
     const double hn = nrm / (d.hdr[1].x * ck);
     for (int i = 0; i < k; i++) {
         const double2 a = col[i], b = col[i + 1];
@@ -204,6 +230,7 @@ __global__ void k_inner_givens(InnerList L, int k, double tol, int maxit) {
     const int j = k + 1;
     const bool stop = c_abs(d.g[k + 1]) < tol || j >= maxit || hn == 0.0;
     d.hdr[0] = make_double2((double)j, stop ? 0.0 : 1.0);
+    if (report) d.host[0] = d.hdr[0];
 }
 
 // cycle end: y = R^{-1} g (leading j x j triangle), coef_i = y_i / c_i
@@ -219,6 +246,7 @@ __global__ void k_inner_solve(InnerList L) {
         d.coef[i] = (dg.x == 0.0 && dg.y == 0.0) ? make_double2(0.0, 0.0) : c_div(s, dg);
     }
     for (int i = 0; i < j; i++) d.coef[i] = c_scale(1.0 / d.ic[i], d.coef[i]);
+    d.host[0] = d.hdr[0];
 }
 
 struct Layout {
@@ -243,7 +271,8 @@ long long system_sites(const dirac_op *op, const fgmres_params *p) { return p->s
 size_t partial_entries(const fgmres_params *p) {
     const int nv = std::min(p->restart + 1, kGS);
     const size_t outer = (size_t)kMdotChunks * ((nv + kMdot - 1) / kMdot) * (kMdot + 1);
-    return std::max(outer, (size_t)kRedBlocks * (kMdot + 1));
+    const size_t mi = is_mixed(p->mode) ? (size_t)p->inner_restart : 0;
+    return std::max(outer, (size_t)kRedBlocks * (mi + 2));
 }
 
 Layout layout(const dirac_op *op, const fgmres_params *p) {
@@ -340,6 +369,7 @@ struct Rhs {
     double2 *sapw = nullptr;   // SAP preconditioner's workspace
     InnerDev in;               // device state of the inner cycle
     double2 *partial = nullptr, *hcol = nullptr, *coef = nullptr, *hcol2 = nullptr, *nrm = nullptr;
+    double2 *host = nullptr;   // the right-hand side's entries of the host staging, written by the kernels
     // host
     Phase phase = Phase::Residual;
     Arnoldi outer;
@@ -362,8 +392,6 @@ struct Ctx {
     int V;        // its sites (V/2 for the even-odd reduced system)
     int apbc;
     bool schur;   // solve S x_e = bhat (even-odd reduction) instead of D x = b
-    double2 *pinned;  // host staging for scalar reads (hipHostMalloc)
-    size_t pinned_n;
 };
 
 // instantiated inner-cycle graphs of one solve, keyed by the right-hand sides they cover
@@ -405,24 +433,11 @@ hipError_t apply_many(const Ctx &c, int prec, const std::vector<ApplyItem> &item
         if (e_ != hipSuccess) return fail(WDIRAC_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-// Read device scalars (pointer, count) into the pinned staging buffer with
-// stream-ordered copies and ONE stream synchronisation.
-int fetch(const Ctx &c, const std::vector<std::pair<const double2 *, int>> &src, std::vector<std::vector<zc>> &out) {
-    out.assign(src.size(), {});
-    size_t off = 0;
-    for (size_t k = 0; k < src.size(); k++) {
-        if (off + src[k].second > c.pinned_n) return fail(WDIRAC_EINVAL, "internal: staging buffer too small");
-        WD_TRY(hipMemcpyAsync(c.pinned + off, src[k].first, src[k].second * sizeof(double2), hipMemcpyDeviceToHost,
-                              c.st));
-        off += src[k].second;
-    }
-    WD_TRY(hipStreamSynchronize(c.st));
-    off = 0;
-    for (size_t k = 0; k < src.size(); k++) {
-        for (int i = 0; i < src[k].second; i++) out[k].push_back(zc(c.pinned[off + i].x, c.pinned[off + i].y));
-        off += src[k].second;
-    }
-    return WDIRAC_OK;
+// `n` scalars that kernels of the stream left in the host staging, after a synchronisation
+std::vector<zc> staged(const double2 *p, int n) {
+    std::vector<zc> v(n);
+    for (int i = 0; i < n; i++) v[i] = zc(p[i].x, p[i].y);
+    return v;
 }
 
 std::vector<double2> to_d2(const std::vector<zc> &v) {
@@ -471,26 +486,23 @@ int issue_inner_body(const Ctx &c, const std::vector<Rhs *> &list, bool host_ste
         std::vector<ApplyItem> b;
         for (Rhs *r : act) b.push_back({r->Vi[k + 1], r->Vi[k], r->ti});
         WD_TRY(apply_many(c, prec, b, s));
-        for (Rhs *r : act)
-            WD_TRY(site_mdot(prec, r->Vi.data(), k + 1, r->Vi[k + 1], c.V, r->partial, r->hcol, r->in.hdr, s));
+        std::vector<SiteItem> items;
+        for (Rhs *r : act) items.push_back({r->Vi.data(), r->Vi[k + 1], r->partial, r->in.coef, r->in.hdr});
+        WD_TRY(site_mdot(prec, items.data(), (int)items.size(), k + 1, c.V, s));
+        const int G = site_groups(c.V);
         WD_TRY(launch_state_k(act, mi, s, [&](const InnerList &L) {
-            hipLaunchKernelGGL(k_inner_prep, dim3(1), dim3(64), 0, s, L, k);
+            hipLaunchKernelGGL(k_inner_prep, dim3(L.n), dim3(kStateThreads), 0, s, L, k, G);
         }));
-        for (Rhs *r : act)
-            WD_TRY(site_axpy(prec, r->Vi.data(), k + 1, r->in.coef, r->Vi[k + 1], c.V, r->partial, r->hcol + k + 1,
-                             r->in.hdr, s));
+        WD_TRY(site_axpy(prec, items.data(), (int)items.size(), k + 1, c.V, s));
         WD_TRY(launch_state_k(act, mi, s, [&](const InnerList &L) {
-            hipLaunchKernelGGL(k_inner_givens, dim3(1), dim3(64), 0, s, L, k, p.inner_tol, maxit);
+            hipLaunchKernelGGL(k_inner_givens, dim3(L.n), dim3(kStateThreads), 0, s, L, k, p.inner_tol, maxit, G,
+                               host_steps ? 1 : 0);
         }));
         if (!host_steps) continue;
-        std::vector<std::pair<const double2 *, int>> src;
-        for (Rhs *r : act) src.emplace_back(r->in.hdr, 1);
-        std::vector<std::vector<zc>> h;
-        int rc = fetch(c, src, h);
-        if (rc) return rc;
+        WD_TRY(hipStreamSynchronize(c.st));
         std::vector<Rhs *> next;
-        for (size_t q = 0; q < act.size(); q++)
-            if (h[q][0].imag() != 0.0) next.push_back(act[q]);
+        for (Rhs *r : act)
+            if (r->in.host[0].y != 0.0) next.push_back(r);
         act.swap(next);
     }
     WD_TRY(launch_state(k_inner_solve, list, mi, s));
@@ -532,9 +544,9 @@ int inner_solve(const Ctx &c, const std::vector<Rhs *> &list, GraphCache *gc, co
         }
         WD_TRY(hipGraphLaunch(it->second, c.st));
     }
-    for (Rhs *r : list)
-        WD_TRY(site_combine(prec, r->Vi.data(), maxit, r->in.coef, r->in.hdr, static_cast<double2 *>(r->Z[r->outer.j]),
-                            c.V, c.st));
+    std::vector<SiteItem> items;
+    for (Rhs *r : list) items.push_back({r->Vi.data(), r->Z[r->outer.j], nullptr, r->in.coef, r->in.hdr});
+    WD_TRY(site_combine(prec, items.data(), (int)items.size(), maxit, c.V, c.st));
     return WDIRAC_OK;
 }
 
@@ -549,7 +561,9 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
     const auto t0 = std::chrono::steady_clock::now();
     const Layout L = layout(op, p);
     const int kmax = kmax_of(p);
-    const size_t pinned_n = (size_t)nrhs * (kmax + 2);
+    const size_t slot = (size_t)kmax + 4;  // staging entries per right-hand side: a Hessenberg column, two norms, the
+                                           // inner cycle's state
+    const size_t pinned_n = (size_t)nrhs * slot;
     double2 *pinned = nullptr;
     if (hipHostMalloc((void **)&pinned, pinned_n * sizeof(double2), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -564,8 +578,7 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
         }
     } guard{pinned, stream};
     const long long Vs = system_sites(op, p);
-    Ctx c{op, p, stream, 12LL * Vs, (int)Vs, (op->flags & WDIRAC_ANTIPERIODIC_T) ? 1 : 0, p->schur != 0, pinned,
-          pinned_n};
+    Ctx c{op, p, stream, 12LL * Vs, (int)Vs, (op->flags & WDIRAC_ANTIPERIODIC_T) ? 1 : 0, p->schur != 0};
     const bool mixed = is_mixed(p->mode);          // preconditioner = inner GMRES
     const bool sapm = p->mode == FGMRES_SAP;       // preconditioner = SAP
     const bool amgm = p->mode == FGMRES_AMG;       // preconditioner = two-level multigrid
@@ -615,10 +628,11 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
         r.coef = r.hcol + kmax;
         r.hcol2 = r.coef + kmax;
         r.nrm = r.hcol2 + kmax;
+        r.host = pinned + (size_t)k * slot;
         char *end = reinterpret_cast<char *>(r.nrm + 1);
         if (mixed) {
             char *ib = s + align256(sizeof(double2) * (partial_entries(p) + 3 * (size_t)kmax + 8));
-            r.in = carve_inner(ib, p->inner_restart, r.hcol);
+            r.in = carve_inner(ib, p->inner_restart, r.hcol, r.partial, r.host + kmax + 2);
             end = ib + inner_state_bytes(p->inner_restart);
         }
         if (end > s + L.scal) return fail(WDIRAC_EINVAL, "internal: scalar block overflow");
@@ -640,41 +654,33 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
     // whose entries all lie below ~1e-162 in magnitude also reads as zero; its product is far below the FP64
     // resolution of any residual)
     {
-        std::vector<std::pair<const double2 *, int>> xs;
         const void *none = nullptr;
-        for (Rhs &r : R) {
-            WD_TRY(mdot_all<double2>(&none, 0, r.xu, 12LL * op->g.V, r.partial, r.nrm, c.st));
-            xs.emplace_back(r.nrm, 1);
-        }
-        std::vector<std::vector<zc>> got;
-        const int rc = fetch(c, xs, got);
-        if (rc) return rc;
-        for (size_t k = 0; k < R.size(); k++) R[k].x_zero = got[k][0].real() == 0.0;
+        for (Rhs &r : R)
+            WD_TRY(mdot_all<double2>(&none, 0, r.xu, 12LL * op->g.V, r.partial, r.nrm, c.st, nullptr, nullptr,
+                                     r.host + kmax));
+        WD_TRY(hipStreamSynchronize(c.st));
+        for (Rhs &r : R) r.x_zero = r.host[kmax].x == 0.0;
     }
     if (c.schur) {
         // |b - D x0| over both parities (the tolerance's reference, so that tol means the same as for D x = b),
         // then the reduced right-hand side bhat = b_e - H_eo A_oo^{-1} b_o
-        std::vector<std::pair<const double2 *, int>> src;
         for (Rhs &r : R) {
             double2 *xo = static_cast<double2 *>(r.V[0]), *bo = static_cast<double2 *>(r.V[1]);
             WD_TRY(parity_split_launch(op, WDIRAC_F64, r.x, xo, r.xu, 1, c.st));
             WD_TRY(parity_split_launch(op, WDIRAC_F64, r.bh, bo, r.bu, 1, c.st));
             // with x0 = 0 its zero halves stand for the zero halves of D x0
             if (!r.x_zero) WD_TRY(parity_launch(kParApply, WDIRAC_F64, false, op, 0, r.w, r.x, xo, 1, c.st));
-            WD_TRY(residual(r.bh, r.x_zero ? xo : r.w, static_cast<double2 *>(r.t64), c.N, r.partial, r.nrm, c.st));
+            WD_TRY(residual(r.bh, r.x_zero ? xo : r.w, static_cast<double2 *>(r.t64), c.N, r.partial, r.nrm, c.st,
+                            r.host + kmax));
             if (!r.x_zero) WD_TRY(parity_launch(kParApply, WDIRAC_F64, false, op, 1, r.w, xo, r.x, 1, c.st));
             WD_TRY(residual(bo, r.x_zero ? r.x : r.w, static_cast<double2 *>(r.t64), c.N, r.partial, r.hcol2,
-                            c.st));
+                            c.st, r.host + kmax + 1));
             WD_TRY(parity_launch(kParInvSelf, WDIRAC_F64, false, op, 1, r.t64, bo, nullptr, 1, c.st));
             WD_TRY(parity_launch(kParSelfSub, WDIRAC_F64, false, op, 0, r.bh, r.bh, r.t64, 1, c.st));
-            src.emplace_back(r.nrm, 1);
-            src.emplace_back(r.hcol2, 1);
         }
-        std::vector<std::vector<zc>> got;
-        int rc = fetch(c, src, got);
-        if (rc) return rc;
+        WD_TRY(hipStreamSynchronize(c.st));
         for (size_t k = 0; k < R.size(); k++) {
-            const double ne = got[2 * k][0].real(), no = got[2 * k + 1][0].real();
+            const double ne = R[k].host[kmax].x, no = R[k].host[kmax + 1].x;
             if (!std::isfinite(ne) || !std::isfinite(no)) {
                 // non-finite b or x0: no iteration can mean anything, the caller's x stays as it is
                 R[k].nonfinite = true;
@@ -721,7 +727,7 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
         for (Rhs *r : res) {
             r->applies++;  // counted also when x is still zero and x itself stands for the zero product
             WD_TRY(residual(r->b, r->x_zero ? r->x : r->w, static_cast<double2 *>(r->V[0]), c.N, r->partial,
-                            r->nrm, c.st));
+                            r->nrm, c.st, r->host + kmax));
             r->x_zero = false;  // the cycle's update changes x
         }
         for (Rhs *r : arn) {
@@ -731,23 +737,13 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
             const int j = r->outer.j;
             std::vector<double> ic2(j + 1);
             for (int i = 0; i <= j; i++) ic2[i] = 1.0 / (r->cw[i] * r->cw[i]);
-            WD_TRY(mdot_all<double2>(r->V.data(), j + 1, r->V[j + 1], c.N, r->partial, r->hcol, c.st));
-            WD_TRY(axpy_multi<double2>(r->V.data(), j + 1, r->hcol, ic2.data(), r->V[j + 1], c.N, r->partial,
-                                       r->hcol + j + 1, c.st));
+            WD_TRY(mdot_all<double2>(r->V.data(), j + 1, r->V[j + 1], c.N, r->partial, r->hcol, c.st, ic2.data(),
+                                     r->coef, r->host));
+            WD_TRY(axpy_multi<double2>(r->V.data(), j + 1, r->coef, r->V[j + 1], c.N, r->partial, r->hcol + j + 1,
+                                       c.st, r->host + j + 1));
         }
         WD_TRY(hipEventRecord(ev.e[3], c.st));
-        std::vector<std::pair<const double2 *, int>> src;
-        for (Rhs *r : res) src.emplace_back(r->nrm, 1);
-        for (Rhs *r : arn) src.emplace_back(r->hcol, r->outer.j + 2);
-        if (mixed)
-            for (Rhs *r : arn) src.emplace_back(r->in.hdr, 1);  // inner steps taken
-        std::vector<std::vector<zc>> got;
-        if (!src.empty()) {
-            int rc = fetch(c, src, got);
-            if (rc) return rc;
-        } else {
-            WD_TRY(hipStreamSynchronize(c.st));
-        }
+        WD_TRY(hipStreamSynchronize(c.st));
         {
             float ms[3] = {0, 0, 0};
             for (int k = 0; k < 3; k++) WD_TRY(hipEventElapsedTime(&ms[k], ev.e[k], ev.e[k + 1]));
@@ -758,7 +754,7 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
         // restarts: convergence test on the true residual
         for (size_t k = 0; k < res.size(); k++) {
             Rhs &r = *res[k];
-            const double n2 = got[k][0].real();
+            const double n2 = r.host[kmax].x;
             if (!std::isfinite(n2)) {
                 // NaN/Inf in b, x0 or the iterate: reported as its own outcome, never as convergence
                 r.nonfinite = true;
@@ -792,8 +788,8 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
         for (size_t k = 0; k < arn.size(); k++) {
             Rhs &r = *arn[k];
             const int j = r.outer.j;
-            const std::vector<zc> &hk = got[res.size() + k];
-            if (mixed) r.inner_applies += (long long)got[res.size() + arn.size() + k][0].real();
+            const std::vector<zc> hk = staged(r.host, j + 2);
+            if (mixed) r.inner_applies += (long long)r.in.host[0].x;
             bool finite = true;
             for (int i = 0; i <= j + 1; i++) finite = finite && std::isfinite(hk[i].real()) && std::isfinite(hk[i].imag());
             if (!finite) {
@@ -841,7 +837,6 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
     }
     if (c.schur) {
         // x_o = A_oo^{-1} (b_o - H_oe x_e), x = (x_e, x_o), and the true residual |b - D x| over both parities
-        std::vector<std::pair<const double2 *, int>> src;
         std::vector<Rhs *> fin;
         for (Rhs &r : R) {
             if (r.nonfinite) continue;  // the caller's x is left untouched
@@ -851,20 +846,14 @@ int solve(const dirac_op *op, double *x, const double *b, int nrhs, const fgmres
             WD_TRY(parity_split_launch(op, WDIRAC_F64, be, bo, r.bu, 1, c.st));
             WD_TRY(parity_launch(kParInvSelfSub, WDIRAC_F64, false, op, 1, xo, bo, r.x, 1, c.st));
             WD_TRY(parity_launch(kParApply, WDIRAC_F64, false, op, 0, r.w, r.x, xo, 1, c.st));
-            WD_TRY(residual(be, r.w, r.bh, c.N, r.partial, r.nrm, c.st));
+            WD_TRY(residual(be, r.w, r.bh, c.N, r.partial, r.nrm, c.st, r.host + kmax));
             WD_TRY(parity_launch(kParApply, WDIRAC_F64, false, op, 1, r.w, xo, r.x, 1, c.st));
-            WD_TRY(residual(bo, r.w, r.bh, c.N, r.partial, r.hcol2, c.st));
+            WD_TRY(residual(bo, r.w, r.bh, c.N, r.partial, r.hcol2, c.st, r.host + kmax + 1));
             WD_TRY(parity_merge_launch(op, WDIRAC_F64, r.xu, r.x, xo, 1, c.st));
-            src.emplace_back(r.nrm, 1);
-            src.emplace_back(r.hcol2, 1);
         }
-        std::vector<std::vector<zc>> got;
-        if (!src.empty()) {
-            int rc = fetch(c, src, got);
-            if (rc) return rc;
-        }
+        WD_TRY(hipStreamSynchronize(c.st));
         for (size_t k = 0; k < fin.size(); k++) {
-            const double ne = got[2 * k][0].real(), no = got[2 * k + 1][0].real();
+            const double ne = fin[k]->host[kmax].x, no = fin[k]->host[kmax + 1].x;
             if (!std::isfinite(ne) || !std::isfinite(no)) {
                 fin[k]->nonfinite = true;
                 fin[k]->converged = false;
