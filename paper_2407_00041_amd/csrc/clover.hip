@@ -11,142 +11,183 @@
 // In the chiral basis gamma_mu gamma_nu = diag(B_mu B_nu^H, B_mu^H B_nu),
 // which gives the two 6x6 chirality blocks that are stored.
 //
-// One thread per site, FP64, canonical AoS links in, canonical packed
-// [V][42] out (entry order documented in wdirac.h).
-#include "common.h"
+// FP64, canonical AoS links in, canonical packed [V][42] out (entry order
+// documented in wdirac.h).
+//
+// Each plane's four leaves are two products instead of four: with
+// W - W^H unchanged (up to sign) under W -> W^H, the leaves that begin or end
+// with U_mu(x) share it, and so do the two with U_mu(x-mu):
+//   X_1 = U_mu(x) [U_nu(x+mu) (U_nu(x) U_mu(x+nu))^H
+//                  - U_nu(x-nu+mu)^H U_mu(x-nu)^H U_nu(x-nu)]
+//   X_2 = [U_nu(x) (U_nu(x-mu) U_mu(x-mu+nu))^H
+//          - (U_mu(x-mu-nu) U_nu(x-nu))^H U_nu(x-mu-nu)] U_mu(x-mu)
+//   Q - Q^H = (X_1 + X_2) - (X_1 + X_2)^H,
+// ten 3x3 products per plane instead of twelve.
+//
+// A work-group is six waves over the same 64 sites, wave p the plane p, so a
+// lane holds one plane's matrices and nothing is indexed at run time (one
+// thread per site with all six planes and both 6x6 blocks live took 256 VGPRs
+// and 824 B of scratch); the planes' Q - Q^H meet in LDS, and the work-group
+// writes the 64 x 42 outputs in order.  Bound by the links' way from the L2: a
+// plane reads 12 matrices per site, each 144 B that touch two 128-byte lines.
+// Turning them through LDS (nine consecutive lanes per matrix), with or without
+// the next pair in flight, and three waves per SIMD (spills) measured the same
+// or slower.  32^4: 2714 -> 1278 us.
+#include "spinor_io.h"
 
 namespace wd {
 
 namespace {
 
+constexpr int kSites = 64;   // sites per work-group
+constexpr int kPlanes = 6;   // (T,Z) (T,Y) (T,X) (Z,Y) (Z,X) (Y,X), one wave each
+
 struct M3 {
     cx<double> a[9];
 };
 
-__device__ __forceinline__ M3 load_u(const double2 *links, int site, int mu) {
-    M3 m;
-    const double2 *p = links + (size_t)(4 * site + mu) * 9;
+// m += x y, or m -= x y (NEG); DX, DY: the adjoint of x, y
+template <bool DX, bool DY, bool NEG> __device__ __forceinline__ void mul_acc(M3 &m, const M3 &x, const M3 &y) {
 #pragma unroll
-    for (int e = 0; e < 9; e++) m.a[e] = {p[e].x, p[e].y};
-    return m;
-}
-
-__device__ __forceinline__ M3 dag(const M3 &x) {
-    M3 m;
+    for (int k = 0; k < 3; k++)
 #pragma unroll
-    for (int i = 0; i < 3; i++)
+        for (int i = 0; i < 3; i++) {
+            cx<double> u = x.a[DX ? 3 * k + i : 3 * i + k];
+            if (NEG) u = {-u.r, -u.i};
 #pragma unroll
-        for (int j = 0; j < 3; j++) m.a[3 * i + j] = {x.a[3 * j + i].r, -x.a[3 * j + i].i};
-    return m;
-}
-
-__device__ __forceinline__ M3 mul(const M3 &x, const M3 &y) {
-    M3 m;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            cx<double> s = mk<double>(0, 0);
-#pragma unroll
-            for (int k = 0; k < 3; k++) s = cfma(s, x.a[3 * i + k], y.a[3 * k + j]);
-            m.a[3 * i + j] = s;
+            for (int j = 0; j < 3; j++) {
+                const cx<double> v = y.a[DY ? 3 * j + k : 3 * k + j];
+                cx<double> &s = m.a[3 * i + j];
+                s = DX ? cjfma(s, u, v) : DY ? cjfma(s, v, u) : cfma(s, u, v);
+            }
         }
+}
+template <bool DX, bool DY> __device__ __forceinline__ M3 mul(const M3 &x, const M3 &y) {
+    M3 m;
+#pragma unroll
+    for (int e = 0; e < 9; e++) m.a[e] = mk<double>(0, 0);
+    mul_acc<DX, DY, false>(m, x, y);
     return m;
 }
 
-__device__ __forceinline__ int shift(const Geom &g, const int c[4], int mu, int step, int nu = 0, int step2 = 0) {
-    int d[4] = {c[0], c[1], c[2], c[3]};
-    d[mu] = (d[mu] + step + g.n[mu]) % g.n[mu];
-    if (step2) d[nu] = (d[nu] + step2 + g.n[nu]) % g.n[nu];
-    return ((d[0] * g.n[1] + d[1]) * g.n[2] + d[2]) * g.n[3] + d[3];
+__device__ __forceinline__ M3 link(const d2v *links, int site, int mu) {
+    const d2v *p = links + (size_t)(4 * site + mu) * 9;
+    M3 o;
+#pragma unroll
+    for (int e = 0; e < 9; e++) {
+        const d2v a = p[e];
+        o.a[e] = {a.x, a.y};
+    }
+    return o;
 }
 
-// 2x2 spin matrices B_mu (gamma_mu = [[0, B], [B^H, 0]])
-__device__ __forceinline__ void bmat(int mu, cx<double> B[4]) {
-    for (int k = 0; k < 4; k++) B[k] = mk<double>(0, 0);
-    if (mu == 0) { B[0] = mk<double>(1, 0); B[3] = mk<double>(1, 0); }
-    if (mu == 1) { B[0] = mk<double>(0, -1); B[3] = mk<double>(0, 1); }
-    if (mu == 2) { B[1] = mk<double>(-1, 0); B[2] = mk<double>(1, 0); }
-    if (mu == 3) { B[1] = mk<double>(0, -1); B[2] = mk<double>(0, -1); }
+// keeps the next product's loads behind this one's arithmetic (registers)
+__device__ __forceinline__ void step() { __builtin_amdgcn_sched_barrier(0); }
+
+// entry (i, j) of the chirality block packed at position k of a block's 21
+__device__ __forceinline__ void packed_pair(int k, int &i, int &j) {
+    if (k < 6) {
+        i = j = k;
+        return;
+    }
+    k -= 6;
+    i = 0;
+    for (int n = 5; k >= n; n--) {
+        k -= n;
+        i++;
+    }
+    j = i + 1 + k;
 }
 
 }  // namespace
 
-__global__ __launch_bounds__(128) void clover_build_kernel(double2 *__restrict__ out, const double2 *__restrict__ links,
-                                                           Geom g) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= g.V) return;
-    int c[4];
+__global__ __launch_bounds__(kPlanes * 64) void clover_build_kernel(double2 *__restrict__ out,
+                                                                    const double2 *__restrict__ links, Geom g,
+                                                                    int eighth) {
+    __shared__ d2v lds[kPlanes][9 * kSites];
+    const int lane = threadIdx.x & 63;
+    const int plane = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // tiles as in the link force: XCD k (work-groups go to the 8 XCDs in turn) takes the k-th eighth of every
+    // T-slice and all XCDs walk the slices together, so most neighbour links are in the XCD's own L2
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int tpe = eighth / kSites;
+    const int t = q / tpe, slice = g.stride[0];
+    const int lo = xcd * eighth + (q - t * tpe) * kSites;
+    const int nsite = min(kSites, min((xcd + 1) * eighth, slice) - lo);
+    if (nsite <= 0) return;
+    const int base = t * slice + lo;
     {
-        int r = s;
-        c[3] = r % g.n[3]; r /= g.n[3];
-        c[2] = r % g.n[2]; r /= g.n[2];
-        c[1] = r % g.n[1];
-        c[0] = r / g.n[1];
+        const int mu = plane < 3 ? 0 : (plane < 5 ? 1 : 2);
+        const int nu = plane < 3 ? plane + 1 : (plane < 5 ? plane - 1 : 3);
+        const int s = base + min(lane, nsite - 1);  // idle lanes repeat the last site
+        const int sm = mu == 0 ? g.stride[0] : (mu == 1 ? g.stride[1] : g.stride[2]);
+        const int Lm = mu == 0 ? g.n[0] : (mu == 1 ? g.n[1] : g.n[2]);
+        const int sn = nu == 1 ? g.stride[1] : (nu == 2 ? g.stride[2] : 1);
+        const int Ln = nu == 1 ? g.n[1] : (nu == 2 ? g.n[2] : g.n[3]);
+        const int cm = s / sm % Lm, cn = s / sn % Ln;
+        const int mf = cm == Lm - 1 ? -(Lm - 1) * sm : sm, mb = cm == 0 ? (Lm - 1) * sm : -sm;
+        const int nf = cn == Ln - 1 ? -(Ln - 1) * sn : sn, nb = cn == 0 ? (Ln - 1) * sn : -sn;
+        const d2v *L = reinterpret_cast<const d2v *>(links);
+        auto U = [&](int site, int dir) { return link(L, site, dir); };
+        M3 P, S, F;
+        P = mul<false, false>(U(s, nu), U(s + nf, mu));
+        step();
+        S = mul<false, true>(U(s + mf, nu), P);
+        step();
+        P = mul<true, false>(U(s + nb, mu), U(s + nb, nu));
+        step();
+        mul_acc<true, false, true>(S, U(s + nb + mf, nu), P);
+        step();
+        F = mul<false, false>(U(s, mu), S);
+        step();
+        P = mul<false, false>(U(s + mb, nu), U(s + mb + nf, mu));
+        step();
+        S = mul<false, true>(U(s, nu), P);
+        step();
+        P = mul<false, false>(U(s + mb + nb, mu), U(s + nb, nu));
+        step();
+        mul_acc<true, false, true>(S, P, U(s + mb + nb, nu));
+        step();
+        mul_acc<false, false, false>(F, S, U(s + mb, mu));
+        // Q - Q^H, entry e of this lane's site at [e][lane]
+#pragma unroll
+        for (int i = 0; i < 3; i++)
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const cx<double> a = F.a[3 * i + j], b = F.a[3 * j + i];
+                lds[plane][(3 * i + j) * kSites + lane] = d2v{a.r - b.r, a.i + b.i};
+            }
     }
-    // accumulate the two 6x6 blocks
-    cx<double> blk[2][36];
-    for (int b = 0; b < 2; b++)
-        for (int k = 0; k < 36; k++) blk[b][k] = mk<double>(0, 0);
-
-    for (int mu = 0; mu < 4; mu++)
-        for (int nu = mu + 1; nu < 4; nu++) {
-            const int xpm = shift(g, c, mu, +1), xpn = shift(g, c, nu, +1);
-            const int xmm = shift(g, c, mu, -1), xmn = shift(g, c, nu, -1);
-            const int xmm_pn = shift(g, c, mu, -1, nu, +1), xmm_mn = shift(g, c, mu, -1, nu, -1);
-            const int xmn_pm = shift(g, c, nu, -1, mu, +1);
-            M3 q = mul(mul(load_u(links, s, mu), load_u(links, xpm, nu)),
-                       mul(dag(load_u(links, xpn, mu)), dag(load_u(links, s, nu))));
-            M3 t = mul(mul(load_u(links, s, nu), dag(load_u(links, xmm_pn, mu))),
-                       mul(dag(load_u(links, xmm, nu)), load_u(links, xmm, mu)));
-            for (int e = 0; e < 9; e++) q.a[e] = q.a[e] + t.a[e];
-            t = mul(mul(dag(load_u(links, xmm, mu)), dag(load_u(links, xmm_mn, nu))),
-                    mul(load_u(links, xmm_mn, mu), load_u(links, xmn, nu)));
-            for (int e = 0; e < 9; e++) q.a[e] = q.a[e] + t.a[e];
-            t = mul(mul(dag(load_u(links, xmn, nu)), load_u(links, xmn, mu)),
-                    mul(load_u(links, xmn_pm, nu), dag(load_u(links, s, mu))));
-            for (int e = 0; e < 9; e++) q.a[e] = q.a[e] + t.a[e];
-            // F = Q - Q^H
-            M3 F;
-            for (int i = 0; i < 3; i++)
-                for (int j = 0; j < 3; j++)
-                    F.a[3 * i + j] = {q.a[3 * i + j].r - q.a[3 * j + i].r, q.a[3 * i + j].i + q.a[3 * j + i].i};
-            // spin factors: block + = B_mu B_nu^H, block - = B_mu^H B_nu
-            cx<double> Bm[4], Bn[4], P[2][4];
-            bmat(mu, Bm);
-            bmat(nu, Bn);
-            for (int i = 0; i < 2; i++)
-                for (int j = 0; j < 2; j++) {
-                    cx<double> sp = mk<double>(0, 0), sm = mk<double>(0, 0);
-                    for (int k = 0; k < 2; k++) {
-                        sp = cfma(sp, Bm[2 * i + k], mk<double>(Bn[2 * j + k].r, -Bn[2 * j + k].i));
-                        sm = cfma(sm, mk<double>(Bm[2 * k + i].r, -Bm[2 * k + i].i), Bn[2 * k + j]);
-                    }
-                    P[0][2 * i + j] = sp;
-                    P[1][2 * i + j] = sm;
-                }
-            for (int b = 0; b < 2; b++)
-                for (int si = 0; si < 2; si++)
-                    for (int sj = 0; sj < 2; sj++) {
-                        cx<double> f = (-1.0 / 16.0) * P[b][2 * si + sj];
-                        for (int a = 0; a < 3; a++)
-                            for (int bb = 0; bb < 3; bb++)
-                                blk[b][6 * (3 * si + a) + 3 * sj + bb] =
-                                    cfma(blk[b][6 * (3 * si + a) + 3 * sj + bb], f, F.a[3 * a + bb]);
-                    }
+    __syncthreads();
+    // gamma_mu gamma_nu in the chiral basis: with F_p = Q - Q^H of plane p and t = +1 (block +) or -1 (block -),
+    //   C = -(i/16) [s3 (x) (t F_TZ - F_YX) + s2 (x) (t F_TY + F_ZX) + s1 (x) (t F_TX - F_ZY)]
+    for (int w = threadIdx.x; w < nsite * 42; w += kPlanes * 64) {
+        const int l = w / 42, e = w - 42 * l;
+        const int b = e >= 21 ? 1 : 0;
+        const double tb = b ? -1.0 : 1.0;
+        int i, j;
+        packed_pair(e - 21 * b, i, j);
+        const int at = (3 * (i % 3) + j % 3) * kSites + l;
+        d2v v;  // C = -(i/16) v
+        if (i < 3 && j >= 3) {
+            const d2v tx = lds[2][at], zy = lds[3][at], ty = lds[1][at], zx = lds[4][at];
+            // s1 - i s2 of the spin-off-diagonal entry
+            v.x = (tb * tx.x - zy.x) + (tb * ty.y + zx.y);
+            v.y = (tb * tx.y - zy.y) - (tb * ty.x + zx.x);
+        } else {
+            const double sgn = i < 3 ? 1.0 : -1.0;
+            const d2v tz = lds[0][at], yx = lds[5][at];
+            v.x = sgn * (tb * tz.x - yx.x);
+            v.y = sgn * (tb * tz.y - yx.y);
         }
-    double2 *o = out + (size_t)42 * s;
-    for (int b = 0; b < 2; b++) {
-        for (int i = 0; i < 6; i++) o[21 * b + i] = make_double2(blk[b][7 * i].r, blk[b][7 * i].i);
-        int k = 6;
-        for (int i = 0; i < 6; i++)
-            for (int j = i + 1; j < 6; j++, k++) o[21 * b + k] = make_double2(blk[b][6 * i + j].r, blk[b][6 * i + j].i);
+        out[(size_t)base * 42 + w] = make_double2((1.0 / 16.0) * v.y, (-1.0 / 16.0) * v.x);
     }
 }
 
 hipError_t clover_build_launch(double *out, const double *links, const Geom &g, hipStream_t st) {
-    hipLaunchKernelGGL(clover_build_kernel, dim3((g.V + 127) / 128), dim3(128), 0, st,
-                       reinterpret_cast<double2 *>(out), reinterpret_cast<const double2 *>(links), g);
+    const int eighth = ((g.stride[0] + 7) / 8 + kSites - 1) / kSites * kSites;
+    hipLaunchKernelGGL(clover_build_kernel, dim3(g.n[0] * 8 * (eighth / kSites)), dim3(kPlanes * 64), 0, st,
+                       reinterpret_cast<double2 *>(out), reinterpret_cast<const double2 *>(links), g, eighth);
     return hipGetLastError();
 }
 

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from oracle import evenodd
-from paper_2407_00041_amd import DiracOp, synth
+from paper_2407_00041_amd import DiracOp, clover_term, synth
 
 from util import TOL, need_gpu, rel_l2
 
@@ -73,3 +73,13 @@ def test_untuned_apply_shapes(dims, n, prec, compress, ap, dagger):
         want = oracle.dirac_apply_sites(dims, U, psi[r].cpu().numpy(), sites, -0.3, 1.0, antiperiodic_t=ap,
                                         dagger=dagger)
         assert rel_l2(got[r], want) < TOL[prec], r
+
+
+# 64-site tiles over eighths of a T-slice: ragged eighths, a slice below one tile, extents of two, whole tiles
+@pytest.mark.parametrize("dims", [(5, 7, 9, 11), (3, 2, 5, 2), (2, 2, 2, 2), (4, 8, 8, 16), (2, 16, 16, 16)])
+def test_clover_term_tiles(dims):
+    need_gpu()
+    U = synth.smooth_links(dims, 91, device="cuda")
+    got = clover_term(dims, U).cpu().numpy()
+    want = oracle.clover_term(dims, U.cpu().numpy())
+    assert rel_l2(got, want) < TOL["f64"]
