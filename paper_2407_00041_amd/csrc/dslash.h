@@ -34,6 +34,7 @@ constexpr int kOrderZPlanes = 6;  // XCD k takes the (t, z) planes with z = k mo
 constexpr int kOrderZGroups = 7;  // link-stationary kernel only: as kOrderZPlanes over pairs of consecutive
                                   // z-planes, a work-group's two waves take the same 64 (y, x) sites of each;
                                   // optionally walked along T in (y, x) blocks of xyb tiles
+constexpr int kOrderSplit = 8;  // not a tile order: the small-lattice kernel (untuned launches only), T-slice tiles of 64
 constexpr int kPatchX = 16, kPatchY = 4;  // patch extent in X and Y; Z extent = block / 64
 constexpr int kStationaryBlock = 128;     // work-group size of the link-stationary kernel (LDS budget)
 constexpr int kMaxStationaryRhs = 64;     // right-hand sides per link-stationary launch

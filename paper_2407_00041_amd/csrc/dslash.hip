@@ -494,6 +494,133 @@ void dslash_stationary_kernel(RhsTable tab, OpData d, Geom g, TileMap m, int apb
     }
 }
 
+// Small lattices: a launch of a few hundred waves is one long chain of loads, eight hops after one another, on a chip
+// that is mostly idle.  Here a work-group of four waves takes 64 sites of one right-hand side; wave mu forms the two
+// products of direction mu (waves 2 and 3 also one block each of A(x) psi(x)) and leaves them in LDS, then wave s adds
+// spin s up in the site kernel's order, so the bits are the site kernel's.  us against the site kernel: 8^4 FP64
+// 7.8 -> 6.3, FP32 6.6 -> 4.9, FP16S 6.6 -> 5.0; 10^4 9.0 -> 7.0, 7.4 -> 5.6, 7.3 -> 5.4; FP64 12^4 10.5 -> 9.8 but
+// two right-hand sides 11.2 -> 16.3 (65 KB of LDS: two work-groups per CU), FP32 14^4 9.0 -> 8.7, two 11.6 -> 13.0.
+template <int P> struct SplitLds {
+    using T = typename Store<P>::T;
+    cx<T> chi[8][6][64];  // hop 2 mu (forward), 2 mu + 1 (backward)
+    T f[8][64];           // its factor times the neighbour's scale
+    cx<T> res[12][64];
+};
+
+template <int P, int MU, int S, int SPIN>
+__device__ __forceinline__ void split_add(const SplitLds<P> &m, int h, int l, cx<typename Store<P>::T> (&acc)[3]) {
+    using T = typename Store<P>::T;
+    const T f = m.f[h][l], w = (SPIN < 2 || S > 0) ? f : -f;
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const cx<T> c0 = m.chi[h][c][l], c1 = m.chi[h][3 + c][l];
+        cx<T> v;
+        if (SPIN == 0) v = c0;
+        else if (SPIN == 1) v = c1;
+        else if (SPIN == 2) v = MU == 0 ? c0 : MU == 1 ? times_i(c0) : MU == 2 ? c1 : times_i(c1);
+        else v = MU == 0 ? c1 : MU == 1 ? times_mi(c1) : MU == 2 ? mk<T>(-c0.r, -c0.i) : times_i(c0);
+        acc[c] = {fma(w, v.r, acc[c].r), fma(w, v.i, acc[c].i)};
+    }
+}
+
+template <int P, bool DAG, int SPIN> __device__ __forceinline__ void split_spin(SplitLds<P> &m, int l) {
+    using T = typename Store<P>::T;
+    constexpr int SF = DAG ? +1 : -1, SB = -SF;
+    cx<T> acc[3] = {m.res[3 * SPIN][l], m.res[3 * SPIN + 1][l], m.res[3 * SPIN + 2][l]};
+    split_add<P, 0, SF, SPIN>(m, 0, l, acc);
+    split_add<P, 0, SB, SPIN>(m, 1, l, acc);
+    split_add<P, 1, SF, SPIN>(m, 2, l, acc);
+    split_add<P, 1, SB, SPIN>(m, 3, l, acc);
+    split_add<P, 2, SF, SPIN>(m, 4, l, acc);
+    split_add<P, 2, SB, SPIN>(m, 5, l, acc);
+    split_add<P, 3, SF, SPIN>(m, 6, l, acc);
+    split_add<P, 3, SB, SPIN>(m, 7, l, acc);
+#pragma unroll
+    for (int c = 0; c < 3; c++) m.res[3 * SPIN + c][l] = acc[c];
+}
+
+template <int P, int MU, bool DAG, int ROWS>
+__device__ __forceinline__ void split_hops(SplitLds<P> &m, const void *in, const OpData &d, const Geom &g, int s, int l,
+                                           const Nbr &nb, bool apbc) {
+    using T = typename Store<P>::T;
+    constexpr int SF = DAG ? +1 : -1, SB = -SF;
+    cx<T> U[9], B[9], h[6], chi[6];
+    Raw<P> x, y;
+    Store<P>::load_link(d.links, g.V, MU, s, U, ROWS);
+    x.load(in, g.V, nb.fwd[MU]);
+    Store<P>::load_link(d.links, g.V, MU, nb.bwd[MU], B, ROWS);
+    y.load(in, g.V, nb.bwd[MU]);
+    project_raw<MU, SF>(x, h);
+    su3_mul<false>(U, h, chi);
+#pragma unroll
+    for (int k = 0; k < 6; k++) m.chi[2 * MU][k][l] = chi[k];
+    m.f[2 * MU][l] = x.weight((MU == 0 && apbc && nb.fwd_wrapT) ? T(0.5) : T(-0.5));
+    project_raw<MU, SB>(y, h);
+    su3_mul<true>(B, h, chi);
+#pragma unroll
+    for (int k = 0; k < 6; k++) m.chi[2 * MU + 1][k][l] = chi[k];
+    m.f[2 * MU + 1][l] = y.weight((MU == 0 && apbc && nb.bwd_wrapT) ? T(0.5) : T(-0.5));
+}
+
+template <int P, int B>
+__device__ __forceinline__ void split_self(SplitLds<P> &m, const void *in, const OpData &d, int V, int s, int l) {
+    using T = typename Store<P>::T;
+    cx<T> p[6], y[6];
+    Store<P>::load_half(in, V, s, B, p);
+    if (d.clover_compact) {
+        T cr[28];
+        Store<P>::load_clover_compact(d.clover, V, B, s, cr);
+        clover_block_compact((T)d.diag, cr, p, y);
+    } else {
+        T dd[6];
+        cx<T> uu[15];
+        Store<P>::load_clover(d.clover, V, B, s, dd, uu);
+        clover_block(dd, uu, p, y);
+    }
+#pragma unroll
+    for (int k = 0; k < 6; k++) m.res[6 * B + k][l] = y[k];
+}
+
+template <int P, bool DAG, int ROWS>
+__global__ __launch_bounds__(256) void dslash_split_kernel(ChunkTable<1> tab, OpData d, Geom g, TileMap m, int apbc) {
+    using T = typename Store<P>::T;
+    __shared__ SplitLds<P> lds;
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int vb = (q / tab.nchunks) * 8 + xcd;
+    const int c = q - (q / tab.nchunks) * tab.nchunks;
+    int lo, hi;
+    tile_range(m, vb, lo, hi);
+    if (lo >= hi) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int s = min(lo + l, hi - 1);  // idle lanes repeat the last site and store nothing
+    const void *in = tab.c[c].in[0];
+    const Nbr nb = neighbours(g, s);
+    switch (wave) {
+    case 0: split_hops<P, 0, DAG, ROWS>(lds, in, d, g, s, l, nb, apbc != 0); break;
+    case 1: split_hops<P, 1, DAG, ROWS>(lds, in, d, g, s, l, nb, apbc != 0); break;
+    case 2:
+        split_self<P, 0>(lds, in, d, g.V, s, l);
+        split_hops<P, 2, DAG, ROWS>(lds, in, d, g, s, l, nb, apbc != 0);
+        break;
+    default:
+        split_self<P, 1>(lds, in, d, g.V, s, l);
+        split_hops<P, 3, DAG, ROWS>(lds, in, d, g, s, l, nb, apbc != 0);
+    }
+    __syncthreads();
+    switch (wave) {
+    case 0: split_spin<P, DAG, 0>(lds, l); break;
+    case 1: split_spin<P, DAG, 1>(lds, l); break;
+    case 2: split_spin<P, DAG, 2>(lds, l); break;
+    default: split_spin<P, DAG, 3>(lds, l);
+    }
+    __syncthreads();
+    if (lo + l >= hi) return;
+    cx<T> v[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) v[k] = lds.res[k][l];
+    Store<P>::store_part(tab.c[c].out[0], g.V, s, v, wave);
+}
+
 // ---------------------------------------------------------------------------
 // host side
 
@@ -656,8 +783,28 @@ static hipError_t launch_nr(const std::pair<const void *, void *> *rhs, size_t n
 }
 
 template <int P, bool DAG, int ROWS>
+static hipError_t launch_split(const std::vector<std::pair<const void *, void *>> &rhs, const OpData &d, const Geom &g,
+                               int apbc, hipStream_t st) {
+    const TileMap m = make_tilemap(g, kOrderTSweep, 64, 1);
+    for (size_t c0 = 0; c0 < rhs.size(); c0 += kMaxChunks) {
+        ChunkTable<1> tab;
+        tab.nchunks = (int)std::min(rhs.size() - c0, (size_t)kMaxChunks);
+        for (int i = 0; i < tab.nchunks; i++) {
+            tab.c[i].in[0] = rhs[c0 + i].first;
+            tab.c[i].out[0] = rhs[c0 + i].second;
+        }
+        hipLaunchKernelGGL((dslash_split_kernel<P, DAG, ROWS>), dim3(m.nslots * tab.nchunks), dim3(256), 0, st, tab, d,
+                           g, m, apbc);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <int P, bool DAG, int ROWS>
 static hipError_t launch_rows(const std::vector<std::pair<const void *, void *>> &rhs, const OpData &d, const Geom &g,
                               int apbc, bool persistent, const LaunchCfg &cfg, hipStream_t st) {
+    if (cfg.order == kOrderSplit) return launch_split<P, DAG, ROWS>(rhs, d, g, apbc, st);
     if (cfg.nr >= 4 && !is_column_order(cfg.order))
         return launch_nr<P, DAG, ROWS, 4>(rhs.data(), rhs.size(), d, g, apbc, persistent, cfg, st);
     if (cfg.nr >= 2)
@@ -769,9 +916,11 @@ hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, b
 // lane halve the waves: site kernel from 2^17 site-right-hand-sides (FP32 16^4, two: one per lane 12.9, four: pairs
 // 22.8; 8^4: pairs 11.9 against 8), FP64 columns from 2^21 (48 x 24^3, two: one per lane 307, pairs 316; 32^4, two:
 // pairs 445).  The link-stationary kernel (the site kernel's order and bits) takes six and more FP32 right-hand sides
-// between 16^4 and 2^18 sites: 12 at 16^4 67 -> 54; at 12^4 25 against 49.
+// between 16^4 and 2^18 sites: 12 at 16^4 67 -> 54; at 12^4 25 against 49.  Up to 2^14 site-right-hand-sides at FP64,
+// 2^15 else, the small-lattice kernel (measured there; same bits as the site kernel).
 static LaunchCfg default_cfg(int V, int prec, int n, int rows) {
     const long long w = (long long)V * n;
+    if (w <= (prec == WDIRAC_F64 ? 1 << 14 : 1 << 15)) return {kOrderSplit, 256, 1, 1};
     if (prec == WDIRAC_F64 && V > 1 << 17) return {kOrderColumn, 256, 4, w >= 1 << 21 ? 2 : 1};
     if (prec == WDIRAC_F32 && V >= 1 << 18) return {kOrderColumn, 256, w >= 1 << 21 ? 8 : 4, n > 1 ? 2 : 1};
     if (prec == WDIRAC_F32 && rows == 2 && n >= 6 && V >= 1 << 16) return {kOrderStationary, kStationaryBlock, 1, 2};

@@ -68,6 +68,15 @@ template <> struct Store<WDIRAC_F64> {
             __builtin_nontemporal_store(a, &p[(size_t)k * V + s]);
         }
     }
+    // the part-th of four shares of store_spinor
+    static __device__ __forceinline__ void store_part(void *base, int V, int s, const cx<T> v[12], int part) {
+        d2v *p = static_cast<d2v *>(base);
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            d2v a = {v[k].r, v[k].i};
+            if ((k & 3) == part) __builtin_nontemporal_store(a, &p[(size_t)k * V + s]);
+        }
+    }
     static __device__ __forceinline__ void load_link(const void *base, int V, int mu, int s, cx<T> U[9],
                                                      int rows = 3) {
         const double2 *p = static_cast<const double2 *>(base);
@@ -143,6 +152,14 @@ template <> struct Store<WDIRAC_F32> {
             __builtin_nontemporal_store(a, &p[(size_t)k * V + s]);
         }
     }
+    static __device__ __forceinline__ void store_part(void *base, int V, int s, const cx<T> v[12], int part) {
+        f4v *p = static_cast<f4v *>(base);
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            f4v a = {v[2 * k].r, v[2 * k].i, v[2 * k + 1].r, v[2 * k + 1].i};
+            if ((k & 3) == part) __builtin_nontemporal_store(a, &p[(size_t)k * V + s]);
+        }
+    }
     static __device__ __forceinline__ void load_link(const void *base, int V, int mu, int s, cx<T> U[9],
                                                      int rows = 3) {
         if (rows == 2) {
@@ -216,12 +233,11 @@ template <> struct Store<WDIRAC_F16S> {
 #pragma unroll
         for (int k = 0; k < 6; k++) v[k] = h ? w[6 + k] : w[k];
     }
-    static __device__ __forceinline__ void store_spinor(void *base, int V, int s, const cx<T> v[12]) {
-        half8 *p = static_cast<half8 *>(base);
+    // stored values and (returned) scale of a site
+    static __device__ __forceinline__ float encode(const cx<T> v[12], half8 a[3]) {
         float m = 0.f;
 #pragma unroll
         for (int k = 0; k < 12; k++) m = fmaxf(m, fmaxf(fabsf(v[k].r), fabsf(v[k].i)));
-        half8 a[3];
         if (m >= 0x1p-60f && m <= 0x1p+100f) {
             // v / m as the division rounds it, without 24 divisions: y = 1/m correctly rounded by one Newton step,
             // then quotient, exact remainder and correction (Markstein); the bounds keep every step normal.  The
@@ -247,10 +263,27 @@ template <> struct Store<WDIRAC_F16S> {
                 a[k >> 2][2 * (k & 3) + 1] = m > 0.f ? (_Float16)(v[k].i / m) : (_Float16)0.f;
             }
         }
+        return m;
+    }
+    static __device__ __forceinline__ void store_spinor(void *base, int V, int s, const cx<T> v[12]) {
+        half8 a[3];
+        const float m = encode(v, a);
+        half8 *p = static_cast<half8 *>(base);
 #pragma unroll
         for (int k = 0; k < 3; k++) __builtin_nontemporal_store(a[k], &p[(size_t)k * V + s]);
         float *sp = reinterpret_cast<float *>(static_cast<char *>(base) + (size_t)48 * V);
         __builtin_nontemporal_store(m, &sp[s]);
+    }
+    static __device__ __forceinline__ void store_part(void *base, int V, int s, const cx<T> v[12], int part) {
+        half8 a[3];
+        const float m = encode(v, a);
+        half8 *p = static_cast<half8 *>(base);
+        if (part < 3) {
+            __builtin_nontemporal_store(part == 0 ? a[0] : part == 1 ? a[1] : a[2], &p[(size_t)part * V + s]);
+        } else {
+            float *sp = reinterpret_cast<float *>(static_cast<char *>(base) + (size_t)48 * V);
+            __builtin_nontemporal_store(m, &sp[s]);
+        }
     }
     static __device__ __forceinline__ void load_link(const void *base, int V, int mu, int s, cx<T> U[9],
                                                      int rows = 3) {

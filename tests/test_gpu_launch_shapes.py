@@ -47,12 +47,15 @@ def test_reduced_operator_shapes(dims, n, prec, compress, ap):
         assert rel_l2(got[r], want) < TOL[prec], r
 
 
-# applies neither tuned nor set: 12^4 one right-hand side per lane up to 6, pairs at 7 (past 2^17 site-right-hand-
-# sides); 16^4 pairs, at FP32 with two-row links link-stationary from 6; 24 x 16^2 x 24 FP64 columns; 32 x 16^2 x 32
-# FP32 columns too, in pairs with a lone last one; odd extents
-@pytest.mark.parametrize("dims,n", [((12, 12, 12, 12), 6), ((12, 12, 12, 12), 7), ((16, 16, 16, 16), 3),
-                                    ((16, 16, 16, 16), 6), ((24, 16, 16, 24), 2), ((32, 16, 16, 32), 3),
-                                    ((17, 19, 21, 23), 1)])
+# applies neither tuned nor set. The small-lattice kernel (V n up to 2^14 at FP64, 2^15 else): ragged tiles at
+# 3 x 5 x 7 x 9, extents of two, 8^4 with 4 and 8 on the two lines and 5 and 9 past them. 12^4: one right-hand side
+# per lane up to 6, pairs at 7 (past 2^17 site-right-hand-sides). 16^4: pairs, at FP32 with two-row links
+# link-stationary from 6. 24 x 16^2 x 24: FP64 columns. 32 x 16^2 x 32: FP32 columns too, in pairs with a lone last
+# one. Odd extents.
+@pytest.mark.parametrize("dims,n", [((3, 5, 7, 9), 2), ((2, 2, 2, 2), 1), ((8, 8, 8, 8), 4), ((8, 8, 8, 8), 5),
+                                    ((8, 8, 8, 8), 8), ((8, 8, 8, 8), 9), ((12, 12, 12, 12), 6),
+                                    ((12, 12, 12, 12), 7), ((16, 16, 16, 16), 3), ((16, 16, 16, 16), 6),
+                                    ((24, 16, 16, 24), 2), ((32, 16, 16, 32), 3), ((17, 19, 21, 23), 1)])
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
 @pytest.mark.parametrize("compress,ap,dagger", [(True, False, False), (False, True, True)])
 def test_untuned_apply_shapes(dims, n, prec, compress, ap, dagger):
