@@ -24,8 +24,14 @@ def _prec(p) -> int:
     return PRECS[p] if isinstance(p, str) else int(p)
 
 
+# raw handle of a device's current stream, without a Stream object around it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
@@ -84,11 +90,15 @@ class DiracOp:
         check(self.lib.dirac_create(ctypes.byref(h), d, L.ctypes.data, None if C is None else C.ctypes.data,
                                     self.m0, self.csw, flags), "dirac_create")
         self.handle = h
+        # bytes of one right-hand side per precision (field, parity field): asked once, not per call
+        self._rhs_bytes = {p: int(self.lib.dirac_field_bytes(h, p, 1)) for p in PRECS.values()}
+        self._parity_rhs_bytes = {p: int(self.lib.dirac_parity_field_bytes(h, p, 1)) for p in PRECS.values()}
 
     def close(self):
         if getattr(self, "handle", None):
             self.lib.dirac_destroy(self.handle)
             self.handle = None
+            self._rhs_bytes = self._parity_rhs_bytes = {}
 
     def __del__(self):
         try:
@@ -98,7 +108,7 @@ class DiracOp:
 
     # ---------------------------------------------------------------- fields
     def field_bytes(self, prec="f64", nrhs: int = 1) -> int:
-        return int(self.lib.dirac_field_bytes(self.handle, _prec(prec), int(nrhs)))
+        return self._rhs_bytes.get(_prec(prec), 0) * max(int(nrhs), 0)
 
     def empty(self, prec="f64", nrhs: int = 1, device="cuda") -> torch.Tensor:
         """Native field buffer (uint8 tensor of field_bytes)."""
@@ -129,7 +139,7 @@ class DiracOp:
 
     # ------------------------------------------------------------- even-odd
     def parity_field_bytes(self, prec="f64", nrhs: int = 1) -> int:
-        return int(self.lib.dirac_parity_field_bytes(self.handle, _prec(prec), int(nrhs)))
+        return self._parity_rhs_bytes.get(_prec(prec), 0) * max(int(nrhs), 0)
 
     def empty_parity(self, prec="f64", nrhs: int = 1, device="cuda") -> torch.Tensor:
         """Native parity-field buffer (V/2 sites) of parity_field_bytes."""

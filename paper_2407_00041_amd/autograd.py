@@ -29,10 +29,11 @@ class DiracApply(torch.autograd.Function):
         gx = gU = None
         g = g.contiguous()
         nrhs = x.numel() // (12 * op.V)
+        gn = op.pack(g.reshape(nrhs, op.V, 12), "f64")  # for both gradients
         if ctx.needs_input_grad[0]:
-            gx = op.apply(g, "f64", dagger=True)
+            y = op.empty("f64", nrhs, g.device)
+            gx = op.unpack(op.apply_native(y, gn, nrhs, "f64", True), "f64", nrhs).reshape(g.shape)
         if ctx.needs_input_grad[1]:
-            gn = op.pack(g.reshape(nrhs, op.V, 12), "f64")
             xn = op.pack(x.reshape(nrhs, op.V, 12), "f64")
             gU = op.force(gn, xn, nrhs, raw=True)
         return gx, gU, None, None, None, None, None

@@ -68,6 +68,7 @@ void load_cache_locked() {
 bool tuned_cfg(const Geom &g, int prec, int nrhs, int rows, int compact, LaunchCfg &out) {
     std::lock_guard<std::mutex> lk(g_mu);
     load_cache_locked();
+    if (g_table.empty()) return false;
     auto it = g_table.find(key_of(g, prec, nrhs, rows, compact));
     if (it == g_table.end()) return false;
     out = it->second;
