@@ -13,8 +13,9 @@
 // and at FP32 the block's forward links are staged in LDS and its compact
 // clover blocks held in registers, so the MR steps read no memory at all.
 // The residual r_B = (b - D x)_B that starts a block solve is computed by the
-// same kernel from the full operator (neighbour values of x from the other
-// colour's blocks in memory).  One launch per colour (red-black) or one for all
+// same kernel from the full operator: the block's own x staged in the same LDS
+// slots, neighbour values from other blocks read from memory by the lanes on a
+// face.  One launch per colour (red-black) or one for all
 // blocks (additive) per cycle; x is FP64 in memory, the block arithmetic is
 // FP64 or FP32 (the operator data of that precision), dot products are
 // accumulated in FP64.
@@ -25,6 +26,7 @@
 // the coordinate sum has parity c.
 #include <algorithm>
 
+#include "blas.h"
 #include "sap.h"
 #include "stencil.h"
 
@@ -35,9 +37,6 @@ namespace {
 constexpr int kSapMaxBlock = 256;
 
 template <int P> using TOf = typename Store<P>::T;
-
-// keeps the compiler from hoisting one hop's loads above the previous hop's arithmetic (register pressure)
-__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
 // FP64 field value at site s, converted to the arithmetic type
 template <typename T> __device__ __forceinline__ void load_x(const double2 *f, int V, int s, cx<T> v[12]) {
@@ -97,24 +96,127 @@ template <int P, bool REGC> struct SiteTerm {
 };
 
 // deterministic sum over the work-group of three doubles (every lane gets the totals)
-__device__ __forceinline__ void group_sum3(double v[3], double (*red)[3]) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int k = 0; k < 3; k++) v[k] += __shfl_xor(v[k], o, 64);
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int k = 0; k < 3; k++) red[w][k] = v[k];
+__device__ __forceinline__ void group_sum3(double (&v)[3], double (*red)[3]) {
+    int index = 0, count = 3;
+    const double t = lane_sums<3, 32>(v, index, count);
+    if (count > 0) red[threadIdx.x >> 6][index] = t;
     __syncthreads();
+    const int nw = blockDim.x >> 6;
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-        double t = 0.0;
-        for (int q = 0; q < nw; q++) t += red[q][k];
-        v[k] = t;
+        v[k] = 0.0;
+        for (int q = 0; q < nw; q++) v[k] += red[q][k];
     }
 }
 
+// One lane's place in its block: sites, neighbours and boundary crossings
+struct SapSite {
+    int s, l;
+    int nf[4], nbk[4];  // in-block neighbours (local index, or -1 when the hop leaves the block)
+    bool wf, wb;        // in-block hops that cross the T boundary
+};
+
+// q += the hops of direction MU that stay inside the block, of the field in LDS
+template <int P, bool LDSL, int MU, int NL>
+__device__ __forceinline__ void block_hops(const cx<TOf<P>> (*f_lds)[kSapMaxBlock], const f4v (*link_lds)[NL],
+                                           const OpData &d, const Geom &g, const SapGeom &sg, const SapSite &a,
+                                           bool apbc, cx<TOf<P>> q[12]) {
+    using T = TOf<P>;
+    auto link = [&](int n, cx<T> U[9]) {
+        if constexpr (LDSL) {
+#pragma unroll
+            for (int e = 0; e < 3; e++) {
+                const f4v u = link_lds[3 * MU + e][n];
+                U[2 * e] = {u.x, u.y};
+                U[2 * e + 1] = {u.z, u.w};
+            }
+            third_row(U);
+        } else {
+            Store<P>::load_link(d.links, g.V, MU, a.s + (n - a.l) / sg.lstr[MU] * g.stride[MU], U, d.rows);
+        }
+    };
+    if (a.nf[MU] >= 0) {
+        cx<T> U[9], p[12], h[6], chi[6];
+        link(a.l, U);
+#pragma unroll
+        for (int k = 0; k < 12; k++) p[k] = f_lds[k][a.nf[MU]];
+        project_unit<MU, -1>(p, h);
+        su3_mul<false>(U, h, chi);
+        reconstruct_scaled<MU, -1>(q, chi, (MU == 0 && apbc && a.wf) ? T(0.5) : T(-0.5));
+    }
+    if (a.nbk[MU] >= 0) {
+        cx<T> U[9], p[12], h[6], chi[6];
+        link(a.nbk[MU], U);
+#pragma unroll
+        for (int k = 0; k < 12; k++) p[k] = f_lds[k][a.nbk[MU]];
+        project_unit<MU, +1>(p, h);
+        su3_mul<true>(U, h, chi);
+        reconstruct_scaled<MU, +1>(q, chi, (MU == 0 && apbc && a.wb) ? T(0.5) : T(-0.5));
+    }
+}
+
+// The hop of a lane that leaves the block along one direction, as loaded.  With two-row FP32 links the values stay
+// as loaded until they are used, so the arithmetic between load and add runs while they are on their way.
+template <int P, bool LDSL> struct HaloHop {
+    using T = TOf<P>;
+    double2 x[12];
+    f4v u[LDSL ? 3 : 1];
+    int sn, sl;  // the neighbour, the site that holds the link
+    T f, sign;   // factor and projector sign (forward -1, backward +1)
+    __device__ __forceinline__ void load(const double2 *xin, const OpData &d, const Geom &g, int mu, int s, int coord,
+                                         bool forward, bool apbc) {
+        const int st = g.stride[mu], L = g.n[mu];
+        const bool wrap = coord == (forward ? L - 1 : 0);
+        const int step = wrap ? (L - 1) * st : st;
+        sn = (forward != wrap) ? s + step : s - step;
+        sl = forward ? s : sn;
+        f = (mu == 0 && apbc && wrap) ? T(0.5) : T(-0.5);
+        sign = forward ? T(-1) : T(1);
+#pragma unroll
+        for (int k = 0; k < 12; k++) x[k] = xin[(size_t)k * g.V + sn];
+        if constexpr (LDSL) {
+            const f4v *q = static_cast<const f4v *>(d.links);
+#pragma unroll
+            for (int e = 0; e < 3; e++) u[e] = q[op_idx(3 * mu + e, 12, sl)];
+        }
+    }
+    template <int MU> __device__ __forceinline__ void add(const OpData &d, const Geom &g, cx<T> acc[12]) const {
+        cx<T> U[9], W[9], p[12], h[6], chi[6];
+        if constexpr (LDSL) {
+#pragma unroll
+            for (int e = 0; e < 3; e++) {
+                U[2 * e] = {u[e].x, u[e].y};
+                U[2 * e + 1] = {u[e].z, u[e].w};
+            }
+            third_row(U);
+        } else {
+            Store<P>::load_link(d.links, g.V, MU, sl, U, d.rows);
+        }
+        const bool fw = sign < T(0);
+#pragma unroll
+        for (int i = 0; i < 3; i++)
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const cx<T> v = U[3 * i + j], w = U[3 * j + i];
+                W[3 * i + j] = {fw ? v.r : w.r, fw ? v.i : -w.i};
+            }
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            const T c = k < 6 ? T(1) : sign;
+            p[k] = {c * (T)x[k].x, c * (T)x[k].y};
+        }
+        project_unit<MU, +1>(p, h);
+        su3_mul<false>(W, h, chi);
+        reconstruct_parts<MU>(acc, chi, f, f * sign);
+    }
+};
+
+// What bounds it, at 32 x 16^2 x 32 and FP32 (512 blocks of 4^4 per colour, two per CU, one round of work-groups): an
+// MR step takes 6 us, the FP32 issue rate of its 1900 instructions per site; the rest of a pass is its memory traffic,
+// 128-byte lines of which a colour uses half.  Two cycles of red-black with four steps: 409 us with every neighbour of
+// x read from memory, 290 now; FP64 902 -> 777 (an MR step 34 us: one work-group per CU, registers).  Loading the next
+// direction's face hop one direction ahead gained nothing (300).
+//
 // One Schwarz pass: every block of the pass (colour c, or all blocks for c < 0) computes its residual
 // r_B = (b - D x)_B, solves D_B e = r_B approximately by nmr MR steps and writes x_out = x_in + e on its
 // sites.  xzero: x_in is zero everywhere (r = b); own_zero: x_in is zero on the pass's blocks (their
@@ -126,9 +228,9 @@ __global__ __launch_bounds__(kSapMaxBlock) void sap_pass_kernel(const double2 *_
                                                                 SapGeom sg, int colour, int xzero, int own_zero,
                                                                 int nmr, int apbc, double bscale) {
     using T = TOf<P>;
-    constexpr int SF = -1, SB = +1;  // forward / backward projector signs of D
+    constexpr int NL = LDSL ? kSapMaxBlock : 1;
     __shared__ cx<T> rho_lds[12][kSapMaxBlock];
-    __shared__ f4v link_lds[LDSL ? 12 : 1][LDSL ? kSapMaxBlock : 1];
+    __shared__ f4v link_lds[LDSL ? 12 : 1][NL];
     __shared__ double red[kSapMaxBlock / 64][3];
     // FP64: the correction e is kept in the lane's LDS slot too (registers hold the hop in flight)
     constexpr bool ELDS = P == WDIRAC_F64;
@@ -142,7 +244,10 @@ __global__ __launch_bounds__(kSapMaxBlock) void sap_pass_kernel(const double2 *_
     xout += blockIdx.y * rhs_stride;
 
     int bc[4];
-    block_coords(sg, colour, blockIdx.x, bc);
+    // consecutive blocks on one XCD, which read each other's faces and halves of the same 128-byte lines through one
+    // L2 (work-group i runs on XCD i mod 8); additive, two cycles: 347 -> 229 us
+    const int per = (int)(gridDim.x >> 3), part = (int)(blockIdx.x >> 3);
+    block_coords(sg, colour, part < per ? (int)(blockIdx.x & 7) * per + part : (int)blockIdx.x, bc);
     int lc[4], s = 0;
     {
         int r = active ? l : 0;
@@ -153,19 +258,17 @@ __global__ __launch_bounds__(kSapMaxBlock) void sap_pass_kernel(const double2 *_
 #pragma unroll
         for (int mu = 0; mu < 4; mu++) s += (bc[mu] * sg.b[mu] + lc[mu]) * g.stride[mu];
     }
-    // in-block neighbours (local index, or -1 when the hop leaves the block) and T-boundary crossings
-    int nf[4], nbk[4];
-    bool wf = false, wb = false;
+    SapSite at;
+    at.s = s;
+    at.l = l;
 #pragma unroll
     for (int mu = 0; mu < 4; mu++) {
         const int st = sg.lstr[mu], B = sg.b[mu];
-        nf[mu] = lc[mu] + 1 < B ? l + st : (sg.span[mu] ? l - (B - 1) * st : -1);
-        nbk[mu] = lc[mu] > 0 ? l - st : (sg.span[mu] ? l + (B - 1) * st : -1);
+        at.nf[mu] = lc[mu] + 1 < B ? l + st : (sg.span[mu] ? l - (B - 1) * st : -1);
+        at.nbk[mu] = lc[mu] > 0 ? l - st : (sg.span[mu] ? l + (B - 1) * st : -1);
     }
-    if (sg.span[0]) {
-        wf = lc[0] == sg.b[0] - 1;
-        wb = lc[0] == 0;
-    }
+    at.wf = sg.span[0] && lc[0] == sg.b[0] - 1;
+    at.wb = sg.span[0] && lc[0] == 0;
 
     SiteTerm<P, REGC> A;
     if (active) A.init(d, V, s);
@@ -177,55 +280,48 @@ __global__ __launch_bounds__(kSapMaxBlock) void sap_pass_kernel(const double2 *_
         }
     }
 
-    // ---- residual r = b - D x at the own site, straight into the lane's LDS slot
+    // ---- residual r = b - D x.  The block's own x is read once, into the LDS slots that will hold rho: the hops
+    // inside the block read it there, and only the lanes on a face read neighbours from memory, their loads in
+    // flight during that direction's hops inside the block.  Then r goes into the lane's slot.
     {
-        cx<T> acc[12];
+        cx<T> accs[1][12];
+        cx<T>(&acc)[12] = accs[0];
 #pragma unroll
         for (int k = 0; k < 12; k++) acc[k] = mk<T>(0, 0);
-        if (active && !xzero) {
-            if (!own_zero) {
+        const bool inner = !xzero && !own_zero;
+        if (inner) {
+            if (active) {
                 cx<T> xs[12];
                 load_x<T>(xin, V, s, xs);
+#pragma unroll
+                for (int k = 0; k < 12; k++) rho_lds[k][l] = xs[k];
                 A.apply(d, V, s, xs, acc);
             }
-            // global neighbours of s
-            int c[4] = {bc[0] * sg.b[0] + lc[0], bc[1] * sg.b[1] + lc[1], bc[2] * sg.b[2] + lc[2],
-                        bc[3] * sg.b[3] + lc[3]};
+            __syncthreads();
+        }
+        if (!xzero) {
 #define WD_SAP_RES_HOP(MU)                                                                                        \
             {                                                                                                     \
-                const int st = g.stride[MU], L = g.n[MU];                                                         \
-                if (!own_zero || nf[MU] < 0) {                                                                    \
-                    const int sn = c[MU] == L - 1 ? s - (L - 1) * st : s + st;                                   \
-                    const T f = (MU == 0 && apbc && c[0] == L - 1) ? T(0.5) : T(-0.5);                            \
-                    cx<T> U[9], p[12], h[6], chi[6];                                                              \
-                    Store<P>::load_link(d.links, V, MU, s, U, d.rows);                                            \
-                    load_x<T>(xin, V, sn, p);                                                                     \
-                    project<MU, SF>(p, h, f);                                                                     \
-                    su3_mul<false>(U, h, chi);                                                                    \
-                    reconstruct<MU, SF>(acc, chi);                                                                \
+                const int c = bc[MU] * sg.b[MU] + lc[MU];                                                         \
+                const bool lf = active && at.nf[MU] < 0, lb = active && at.nbk[MU] < 0;                           \
+                HaloHop<P, LDSL> halo;                                                                            \
+                if (lf || lb) halo.load(xin, d, g, MU, s, c, lf, apbc);                                           \
+                if (inner && active) block_hops<P, LDSL, MU, NL>(rho_lds, link_lds, d, g, sg, at, apbc, acc);     \
+                if (lf || lb) halo.template add<MU>(d, g, acc);                                                   \
+                if (lf && lb) { /* a block of extent one */                                                       \
+                    halo.load(xin, d, g, MU, s, c, false, apbc);                                                  \
+                    halo.template add<MU>(d, g, acc);                                                             \
                 }                                                                                                 \
-                if (!own_zero || nbk[MU] < 0) {                                                                   \
-                    const int sn = c[MU] == 0 ? s + (L - 1) * st : s - st;                                       \
-                    const T f = (MU == 0 && apbc && c[0] == 0) ? T(0.5) : T(-0.5);                                \
-                    cx<T> U[9], p[12], h[6], chi[6];                                                              \
-                    Store<P>::load_link(d.links, V, MU, sn, U, d.rows);                                           \
-                    load_x<T>(xin, V, sn, p);                                                                     \
-                    project<MU, SB>(p, h, f);                                                                     \
-                    su3_mul<true>(U, h, chi);                                                                     \
-                    reconstruct<MU, SB>(acc, chi);                                                                \
-                }                                                                                                 \
-            }
-            sched_fence();
+            }                                                                                                     \
+            hop_boundary<T, 1>(accs);
+            hop_boundary<T, 1>(accs);
             WD_SAP_RES_HOP(0)
-            sched_fence();
             WD_SAP_RES_HOP(1)
-            sched_fence();
             WD_SAP_RES_HOP(2)
-            sched_fence();
             WD_SAP_RES_HOP(3)
-            sched_fence();
 #undef WD_SAP_RES_HOP
         }
+        if (inner) __syncthreads();  // every lane has read its neighbours' x
 #pragma unroll
         for (int k = 0; k < 12; k++) {
             cx<T> r = mk<T>(0, 0);
@@ -245,10 +341,10 @@ __global__ __launch_bounds__(kSapMaxBlock) void sap_pass_kernel(const double2 *_
         if constexpr (ELDS) e_lds[k][l] = mk<T>(0, 0);
         else e[k] = mk<T>(0, 0);
     }
-    const T fh = T(-0.5);
     for (int it = 0; it < nmr; it++) {
         __syncthreads();
-        cx<T> q[12];
+        cx<T> qs[1][12];
+        cx<T>(&q)[12] = qs[0];
 #pragma unroll
         for (int k = 0; k < 12; k++) q[k] = mk<T>(0, 0);
         if (active) {
@@ -258,56 +354,15 @@ __global__ __launch_bounds__(kSapMaxBlock) void sap_pass_kernel(const double2 *_
                 for (int k = 0; k < 12; k++) own[k] = rho_lds[k][l];
                 A.apply(d, V, s, own, q);
             }
-#define WD_SAP_BLK_HOP(MU)                                                                                        \
-            if (nf[MU] >= 0) {                                                                                    \
-                const int n = nf[MU];                                                                             \
-                const T f = (MU == 0 && apbc && wf) ? T(0.5) : fh;                                                \
-                cx<T> U[9], p[12], h[6], chi[6];                                                                  \
-                if constexpr (LDSL) {                                                                             \
-                    _Pragma("unroll") for (int e3 = 0; e3 < 3; e3++) {                                            \
-                        const f4v a = link_lds[3 * MU + e3][l];                                                   \
-                        U[2 * e3] = {a.x, a.y};                                                                   \
-                        U[2 * e3 + 1] = {a.z, a.w};                                                               \
-                    }                                                                                             \
-                    third_row(U);                                                                                 \
-                } else {                                                                                          \
-                    Store<P>::load_link(d.links, V, MU, s, U, d.rows);                                            \
-                }                                                                                                 \
-                _Pragma("unroll") for (int k = 0; k < 12; k++) p[k] = rho_lds[k][n];                              \
-                project<MU, SF>(p, h, f);                                                                         \
-                su3_mul<false>(U, h, chi);                                                                        \
-                reconstruct<MU, SF>(q, chi);                                                                      \
-            }                                                                                                     \
-            if (nbk[MU] >= 0) {                                                                                   \
-                const int n = nbk[MU];                                                                            \
-                const T f = (MU == 0 && apbc && wb) ? T(0.5) : fh;                                                \
-                cx<T> U[9], p[12], h[6], chi[6];                                                                  \
-                if constexpr (LDSL) {                                                                             \
-                    _Pragma("unroll") for (int e3 = 0; e3 < 3; e3++) {                                            \
-                        const f4v a = link_lds[3 * MU + e3][n];                                                   \
-                        U[2 * e3] = {a.x, a.y};                                                                   \
-                        U[2 * e3 + 1] = {a.z, a.w};                                                               \
-                    }                                                                                             \
-                    third_row(U);                                                                                 \
-                } else {                                                                                          \
-                    const int sn = s + (n - l) / sg.lstr[MU] * g.stride[MU];                                      \
-                    Store<P>::load_link(d.links, V, MU, sn, U, d.rows);                                           \
-                }                                                                                                 \
-                _Pragma("unroll") for (int k = 0; k < 12; k++) p[k] = rho_lds[k][n];                              \
-                project<MU, SB>(p, h, f);                                                                         \
-                su3_mul<true>(U, h, chi);                                                                         \
-                reconstruct<MU, SB>(q, chi);                                                                      \
-            }
-            sched_fence();
-            WD_SAP_BLK_HOP(0)
-            sched_fence();
-            WD_SAP_BLK_HOP(1)
-            sched_fence();
-            WD_SAP_BLK_HOP(2)
-            sched_fence();
-            WD_SAP_BLK_HOP(3)
-            sched_fence();
-#undef WD_SAP_BLK_HOP
+            hop_boundary<T, 1>(qs);
+            block_hops<P, LDSL, 0, NL>(rho_lds, link_lds, d, g, sg, at, apbc, q);
+            hop_boundary<T, 1>(qs);
+            block_hops<P, LDSL, 1, NL>(rho_lds, link_lds, d, g, sg, at, apbc, q);
+            hop_boundary<T, 1>(qs);
+            block_hops<P, LDSL, 2, NL>(rho_lds, link_lds, d, g, sg, at, apbc, q);
+            hop_boundary<T, 1>(qs);
+            block_hops<P, LDSL, 3, NL>(rho_lds, link_lds, d, g, sg, at, apbc, q);
+            hop_boundary<T, 1>(qs);
         }
         // <q, rho> and <q, q> over the block, accumulated in FP64
         double v[3] = {0.0, 0.0, 0.0};

@@ -94,10 +94,9 @@ template <int MU, int S> __device__ __forceinline__ void project_half(const half
     }
 }
 
-// upper += f chi; lower += f S B_mu^H chi
-template <int MU, int S, typename T>
-__device__ __forceinline__ void reconstruct_scaled(cx<T> acc[12], const cx<T> chi[6], T f) {
-    const T g = S > 0 ? f : -f;
+// upper += f chi; lower += g B_mu^H chi
+template <int MU, typename T>
+__device__ __forceinline__ void reconstruct_parts(cx<T> acc[12], const cx<T> chi[6], T f, T g) {
 #pragma unroll
     for (int c = 0; c < 3; c++) {
         const cx<T> c0 = chi[c], c1 = chi[3 + c];
@@ -111,6 +110,12 @@ __device__ __forceinline__ void reconstruct_scaled(cx<T> acc[12], const cx<T> ch
         acc[6 + c] = {fma(g, l0.r, acc[6 + c].r), fma(g, l0.i, acc[6 + c].i)};
         acc[9 + c] = {fma(g, l1.r, acc[9 + c].r), fma(g, l1.i, acc[9 + c].i)};
     }
+}
+
+// upper += f chi; lower += f S B_mu^H chi
+template <int MU, int S, typename T>
+__device__ __forceinline__ void reconstruct_scaled(cx<T> acc[12], const cx<T> chi[6], T f) {
+    reconstruct_parts<MU>(acc, chi, f, S > 0 ? f : -f);
 }
 
 // A neighbour's spinor as loaded: FP64 and FP32 values, or FP16S halves and

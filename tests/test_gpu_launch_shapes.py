@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from oracle import evenodd
+from oracle import evenodd, sap as osap
 from paper_2407_00041_amd import DiracOp, clover_term, synth
 
 from util import TOL, need_gpu, rel_l2
@@ -86,3 +86,26 @@ def test_clover_term_tiles(dims):
     got = clover_term(dims, U).cpu().numpy()
     want = oracle.clover_term(dims, U.cpu().numpy())
     assert rel_l2(got, want) < TOL["f64"]
+
+
+# Schwarz blocks whose residual takes its own sites from LDS and the rest from faces: extents of one (a site leaves
+# the block both ways; with T also across the antiperiodic boundary), three-site blocks, block counts that are no
+# multiple of eight, a block that spans directions, 256 sites
+@pytest.mark.parametrize("dims,block,additive", [
+    ((4, 4, 6, 8), (1, 2, 3, 2), False), ((6, 6, 2, 4), (1, 1, 2, 4), False), ((6, 6, 2, 4), (1, 3, 1, 2), True),
+    ((2, 2, 2, 4), (1, 1, 1, 1), False), ((8, 4, 8, 8), (4, 4, 4, 4), True), ((4, 10, 2, 6), (4, 5, 1, 3), False)])
+@pytest.mark.parametrize("compress,ap", [(True, True), (False, False)])
+def test_schwarz_faces(dims, block, additive, compress, ap):
+    need_gpu()
+    U = synth.smooth_links(dims, 101).numpy()
+    b = synth.gaussian_spinor(dims, 102)
+    op = DiracOp(dims, U, -0.3, 1.0, antiperiodic_t=ap, precisions=("f64", "f32"), compress_links=compress,
+                 compress_clover=compress)
+    cycles, mr = 2, 2
+    want = osap.Schwarz(dims, U, -0.3, 1.0, block, antiperiodic_t=ap).apply(b, cycles, mr, additive=additive)
+    bn = op.pack(torch.from_numpy(b).cuda(), "f64")
+    kw = dict(block=block, cycles=cycles, mr_iters=mr, additive=additive)
+    for prec in ("f64", "f32"):
+        got = op.unpack(op.sap(bn, prec=prec, **kw), "f64").cpu().numpy()[0]
+        # one apply's bound for each application that a site's result has passed through
+        assert rel_l2(got, want) < TOL[prec] * cycles * 2 * (mr + 1), prec
