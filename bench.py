@@ -178,6 +178,12 @@ def traffic_from_profile(pattern="dslash_column_kernel<0, false, 1>"):
     return float(b.group(1))
 
 
+def kernel_regex(label):
+    """Regex of a kernel label of the suite: the full-lattice stencil's instantiations also name their link rows
+    (<precision, dagger, rows, right-hand sides per lane>), which the labels leave out."""
+    return re.sub(r"^(dslash_(?:column_)?kernel<\d, \w+), (\d)>$", r"\1, (?:[23], )?\2>", label)
+
+
 def time_launches(torch, fn, steps, warmup, stream):
     for _ in range(warmup):
         fn()
@@ -753,7 +759,7 @@ def kernel_suite(torch, manifest_path, dims=(96, 48, 48, 48)):
         for _ in range(3):
             op.apply_schur_native(out, e, tmp, 2, p, stream=st)
         bo, be = SCHUR_PAIR_BYTES_HALF[p]
-        kern = "parity_column_kernel" if p != "f16s" else "parity_kernel"
+        kern = "parity_column_kernel" if p == "f64" else "parity_kernel"
         i = PREC_ID[p]
         add(kern + rf"<(P,DAG,SELF,HOP,INV,ROWS = )?{i}, false, 0, true, true", 3, 3 * bo * V / 2,
             f"S (pair), odd launch A_oo^-1 H_oe, {p}")
@@ -811,8 +817,8 @@ def kernel_suite(torch, manifest_path, dims=(96, 48, 48, 48)):
     axpy = sum(sum(site_pass_bytes(k + 1, f16, 1)) for k in range(10)) * steps
     nmd = sum(len(site_pass_bytes(k + 1, f16, 0)) for k in range(10)) * steps
     add(r"dslash_kernel<2, false, 1>", 10 * steps, 10 * steps * BYTES_SITE["f16s"] * V, "inner FP16S applies")
-    add(r"k_site_mdot<2>", nmd, mdot, "inner inner products (FP16S fields)")
-    add(r"k_site_axpy<2>", nmd, axpy, "inner orthogonalisation (FP16S fields)")
+    add(r"k_site_mdot<2\b", nmd, mdot, "inner inner products (FP16S fields)")
+    add(r"k_site_axpy<2\b", nmd, axpy, "inner orthogonalisation (FP16S fields)")
     add(r"k_site_combine<2>", 2 * steps, steps * (10 * 52 + 192 + 2 * 192) * V, "inner solution into Z (FP64)")
     add(r"k_site_scale<0, 2>", steps, steps * (192 + 52) * V, "outer v_j to the inner FP16S start vector")
     del x, bn
@@ -925,7 +931,7 @@ def summarize_profile(manifest_path, trace_dir, fetch_dir, write_dir, out_md, co
         return items[-n:] if e.get("select") == "last" else items[:n]
 
     for pat, e in man.items():
-        rx = re.compile(pat)
+        rx = re.compile(kernel_regex(pat))
         durs = pick([(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-9 for r in kt
                      if rx.search(r["Kernel_Name"])], e)
         fk = pick([v for k, v in fetch if rx.search(k)], e)
@@ -1272,8 +1278,8 @@ def main():
                    "clover_storage": "per chirality block (A_00 - A_11)/2 and A_01 (27 of 36 reals)"},
         "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": gbs / HBM_PEAK_GBS, "traffic": traffic_from_profile(),
-                     "kernel": ("wd::dslash_column_kernel<0, false, 1>" if tuned["f64"]["order"] == 3
-                                else "wd::dslash_kernel<0, false, 1>"),
+                     "kernel": ("wd::dslash_column_kernel<0, false, 2, 1>" if tuned["f64"]["order"] == 3
+                                else "wd::dslash_kernel<0, false, 2, 1>"),
                      "alg_bytes_per_site": BYTES_SITE["f64"], "alg_bytes_per_launch": BYTES_SITE["f64"] * V,
                      "kernel_source_sha256_16": kernel_hash()},
         "extra": extra,
