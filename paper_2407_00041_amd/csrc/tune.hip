@@ -116,7 +116,7 @@ extern "C" int dirac_autotune(const dirac_op *op, int prec, int nrhs, int cfg_ou
                     if (nr > 1 && nr > nrhs) continue;
                     if (nrhs == 1 && nr > 1) continue;
                     if (order == kOrderZPlanes && nrhs == 1) continue;  // measured slower for one RHS
-                    if (is_column_order(order) && prec == WDIRAC_F64 && nr > 2) continue;
+                    if (is_column_order(order) && nr > 2) continue;  // the column kernels take at most two
                     cands.push_back({order, block, tchunk, nr});
                 }
             }
