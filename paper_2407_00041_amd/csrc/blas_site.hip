@@ -80,6 +80,9 @@ __global__ __launch_bounds__(kRedThreads) void k_site_mdot(SiteBatch b, int i0, 
                 acc[2 * i] += vv[k].x * wv[k].x + vv[k].y * wv[k].y;
                 acc[2 * i + 1] += vv[k].x * wv[k].y - vv[k].y * wv[k].x;
             }
+            // one vector's loads behind the last one's sums: 48^3 x 96 FP16S 706 -> 568 us per pass (every two: 634)
+            asm volatile("" : "+v"(acc[2 * i]), "+v"(acc[2 * i + 1]) : : "memory");
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     const double t = group_sums(acc, lds);
