@@ -241,13 +241,14 @@ template <> struct Store<WDIRAC_F16S> {
         if (m >= 0x1p-60f && m <= 0x1p+100f) {
             // v / m as the division rounds it, without 24 divisions: y = 1/m correctly rounded by one Newton step,
             // then quotient, exact remainder and correction (Markstein); the bounds keep every step normal.  The
+            // remainder is taken as q m - x, so that a zero keeps its sign (x - q m of x = -0 is +0).  The
             // empty asm keeps the correction and the conversion to fp16 two roundings, as after a division: left to
             // itself the compiler makes one mixed-precision multiply-add of them in some kernels and not in others
             const float y0 = __builtin_amdgcn_rcpf(m);
             const float y = __builtin_fmaf(__builtin_fmaf(-m, y0, 1.f), y0, y0);
             auto quot = [&](float x) {
                 const float q = x * y;
-                float z = __builtin_fmaf(__builtin_fmaf(-q, m, x), y, q);
+                float z = __builtin_fmaf(-__builtin_fmaf(q, m, -x), y, q);
                 asm("" : "+v"(z));
                 return (_Float16)z;
             };

@@ -73,7 +73,8 @@ __device__ __forceinline__ void reconstruct(cx<T> acc[12], const cx<T> chi[6]) {
 }
 
 // h = u + S B_mu d of a stored FP16S site without its scale.  Each component is one multiply-add on two fp16
-// operands (exact: the sum of two fp16 values in FP32); `one` is opaque so that it stays one.
+// operands (their sum, rounded once to FP32: exact unless they are more than 13 binary places apart); `one` is opaque
+// so that it stays one.
 template <int MU, int S> __device__ __forceinline__ void project_half(const half8 q[3], cx<float> h[6]) {
     float one;
     asm("s_mov_b32 %0, 1.0" : "=s"(one));
