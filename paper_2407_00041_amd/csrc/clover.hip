@@ -32,7 +32,7 @@
 // plane reads 12 matrices per site, each 144 B that touch two 128-byte lines.
 // Turning them through LDS (nine consecutive lanes per matrix), with or without
 // the next pair in flight, and three waves per SIMD (spills) measured the same
-// or slower.  32^4: 2714 -> 1278 us.
+// or slower.  32^4: 2714 -> 1272 us.
 #include "spinor_io.h"
 
 namespace wd {
@@ -104,9 +104,11 @@ __device__ __forceinline__ void packed_pair(int k, int &i, int &j) {
 
 }  // namespace
 
+// SLABS: the tiles' eighths are of a slab of several T-slices, the last slab possibly a shorter one, not of one slice
+template <bool SLABS>
 __global__ __launch_bounds__(kPlanes * 64) void clover_build_kernel(double2 *__restrict__ out,
                                                                     const double2 *__restrict__ links, Geom g,
-                                                                    int eighth) {
+                                                                    int eighth, int slab) {
     __shared__ d2v lds[kPlanes][9 * kSites];
     const int lane = threadIdx.x & 63;
     const int plane = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -114,11 +116,12 @@ __global__ __launch_bounds__(kPlanes * 64) void clover_build_kernel(double2 *__r
     // T-slice and all XCDs walk the slices together, so most neighbour links are in the XCD's own L2
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int tpe = eighth / kSites;
-    const int t = q / tpe, slice = g.stride[0];
+    const int t = q / tpe, slice = SLABS ? slab : g.stride[0];
     const int lo = xcd * eighth + (q - t * tpe) * kSites;
-    const int nsite = min(kSites, min((xcd + 1) * eighth, slice) - lo);
-    if (nsite <= 0) return;
     const int base = t * slice + lo;
+    int nsite = min(kSites, min((xcd + 1) * eighth, slice) - lo);
+    if (SLABS) nsite = min(nsite, g.V - base);
+    if (nsite <= 0) return;
     {
         const int mu = plane < 3 ? 0 : (plane < 5 ? 1 : 2);
         const int nu = plane < 3 ? plane + 1 : (plane < 5 ? plane - 1 : 3);
@@ -188,9 +191,17 @@ __global__ __launch_bounds__(kPlanes * 64) void clover_build_kernel(double2 *__r
 }
 
 hipError_t clover_build_launch(double *out, const double *links, const Geom &g, hipStream_t st) {
-    const int eighth = ((g.stride[0] + 7) / 8 + kSites - 1) / kSites * kSites;
-    hipLaunchKernelGGL(clover_build_kernel, dim3(g.n[0] * 8 * (eighth / kSites)), dim3(kPlanes * 64), 0, st,
-                       reinterpret_cast<double2 *>(out), reinterpret_cast<const double2 *>(links), g, eighth);
+    // slices of less than a tile per eighth, in slabs of up to 4096 sites: by slices the 64 sites of a 4^3 slice are
+    // one XCD's (1024 x 4^3: 480 us, in slabs 69; 96 x 6^3: 57, 35)
+    const int q = g.stride[0] < 8 * kSites ? slab_slices(g.n[0], g.stride[0], 4096) : 1, slab = q * g.stride[0];
+    const int eighth = ((slab + 7) / 8 + kSites - 1) / kSites * kSites;
+    const dim3 grid((g.n[0] + q - 1) / q * 8 * (eighth / kSites)), blk(kPlanes * 64);
+    double2 *o = reinterpret_cast<double2 *>(out);
+    const double2 *l = reinterpret_cast<const double2 *>(links);
+    if (q > 1)
+        hipLaunchKernelGGL(clover_build_kernel<true>, grid, blk, 0, st, o, l, g, eighth, slab);
+    else
+        hipLaunchKernelGGL(clover_build_kernel<false>, grid, blk, 0, st, o, l, g, eighth, slab);
     return hipGetLastError();
 }
 

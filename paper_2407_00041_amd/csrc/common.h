@@ -35,6 +35,15 @@ struct Geom {
 
 Geom make_geom(const int dims[4]);
 
+// T-slices per slab: as many consecutive slices as fit in `sites` (of `slice` sites each; at least one), evened out
+// over the nT slices.  The kernels that deal eighths of a slice to the XCDs deal eighths of a slab, so that a slice of
+// a few sites does not leave lanes and whole XCDs idle.
+inline int slab_slices(int nT, int slice, int sites) {
+    const int q = sites / slice < 1 ? 1 : (sites / slice > nT ? nT : sites / slice);
+    const int slabs = (nT + q - 1) / q;
+    return (nT + slabs - 1) / slabs;
+}
+
 // ---------------------------------------------------------------------------
 // complex arithmetic in the compute type T (float or double)
 template <typename T> struct cx {

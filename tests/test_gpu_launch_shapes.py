@@ -88,6 +88,18 @@ def test_clover_term_tiles(dims):
     assert rel_l2(got, want) < TOL["f64"]
 
 
+# slices below 512 sites, dealt in slabs of several: a shorter last slab (17 x 4^3 in one slab, 130 x 4^3 in three of
+# 44, 600 x 2^3 in two), slices that are no multiple of a tile, and 8^3 (512 sites), dealt by slices
+@pytest.mark.parametrize("dims", [(17, 4, 4, 4), (130, 4, 4, 4), (600, 2, 2, 2), (11, 5, 7, 9), (14, 7, 9, 8),
+                                  (9, 8, 8, 8)])
+def test_clover_term_slabs(dims):
+    need_gpu()
+    U = synth.smooth_links(dims, 92, device="cuda")
+    got = clover_term(dims, U).cpu().numpy()
+    want = oracle.clover_term(dims, U.cpu().numpy())
+    assert rel_l2(got, want) < TOL["f64"]
+
+
 # Schwarz blocks whose residual takes its own sites from LDS and the rest from faces: extents of one (a site leaves
 # the block both ways; with T also across the antiperiodic boundary), three-site blocks, block counts that are no
 # multiple of eight, a block that spans directions, 256 sites
