@@ -47,6 +47,15 @@ def test_reduced_operator_shapes(dims, n, prec, compress, ap):
         assert rel_l2(got[r], want) < TOL[prec], r
 
 
+# slices of less than 256 half-lattice sites, dealt in slabs of several: a shorter last slab (34 x 4^3 in slabs of 12,
+# 22 x 4 x 6 x 8 of 5), one slab for all, and 6 x 8^3 (256), dealt by slices
+@pytest.mark.parametrize("dims,n", [((34, 4, 4, 4), 3), ((22, 4, 6, 8), 2), ((70, 2, 2, 2), 1), ((6, 8, 8, 8), 1)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("compress,ap", [(True, False), (False, True)])
+def test_reduced_operator_slabs(dims, n, prec, compress, ap):
+    test_reduced_operator_shapes(dims, n, prec, compress, ap)
+
+
 # applies neither tuned nor set. The small-lattice kernel (V n up to 2^14 at FP64, 2^15 else): ragged tiles at
 # 3 x 5 x 7 x 9, extents of two, 8^4 with 4 and 8 on the two lines and 5 and 9 past them. 12^4: one right-hand side
 # per lane up to 6, pairs at 7 (past 2^17 site-right-hand-sides). 16^4: pairs, at FP32 with two-row links
