@@ -62,8 +62,14 @@ __device__ __forceinline__ int parity_site(const Geom &g, int i, int p, int c[4]
 //    Four per lane gained 4 % at 48^3 x 96 and lost up to 15 % below.
 // The arithmetic of a right-hand side is the same in every shape (explicit multiply-adds), so results do not depend
 // on how right-hand sides are grouped.
+//  - odd counts: the last right-hand side runs in the pairs' launch, one per lane (a kernel of its own instantiation:
+//    the second path costs even FP32 counts up to 2 %), on the site kernel in its tile's turn, on the column walk
+//    after all pairs, where it fills their last round (in turn: FP64 24 x 16^2 x 24 213).  As a launch of its own it
+//    left the chip to itself: S of three, us, 24 x 16^2 x 24 FP64 187 -> 168, FP16S 64 -> 49; 32 x 16^2 x 32 FP32
+//    143 -> 118.
 constexpr int kParMax = 16;  // right-hand sides per launch
 constexpr int kParChunk = 4;  // T-slices per chunk of the column walk (kParChunk / 2 sites per lane)
+static_assert(kParChunk > 2, "the column walk carries a hop from a lane's site to its next");
 constexpr long long kParPairs = 1LL << 18;
 inline int rhs_per_lane(long long V, size_t n) { return n >= 2 && V * (long long)n > kParPairs ? 2 : 1; }
 // FP64 above 2^17 sites walks T columns (parity_column_kernel); below it the columns leave the chip idle: S of a
@@ -130,29 +136,16 @@ __device__ __forceinline__ void parity_hops(const OpData &d, const Geom &g, cons
 
 // SELF: 0 none, 1 the input, 2 A(x) times the input.  HOP: add fh * 2 * H hop
 // (fh = -1/2 adds H, +1/2 subtracts it).  INV: multiply the sum by A(x)^{-1}.
+// LONE: an odd count, whose last right-hand side is one lane's of its own.
 // ROWS: stored rows per link (a compile-time constant: a run-time choice
 // between the two link formats costs the FP64 kernels spills).  NR: right-
 // hand sides per lane (register block).
 template <int P, bool DAG, int SELF, bool HOP, bool INV, int ROWS, int NR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(parity_waves<P, NR>())))
-void parity_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int parity, int apbc, typename Store<P>::T fh,
-                   int slices, int tpr) {
+__device__ __forceinline__ void parity_site_apply(const ParityTable &tab, const OpData &d, const void *cinv,
+                                                  const Geom &g, int parity, int apbc, typename Store<P>::T fh, int i,
+                                                  int r0) {
     using T = typename Store<P>::T;
     const int Vh = g.V >> 1;
-    int i, r0;
-    {
-        // block -> (XCD k, slab t of `slices` T-slices, tile within the slab's k-th eighth), the right-hand sides of a
-        // tile in turn
-        const int hs = Vh / g.n[0] * slices;
-        const int groups = tab.n / NR;
-        const int k = blockIdx.x & 7, jj = blockIdx.x >> 3, j = jj / groups;
-        r0 = (jj - j * groups) * NR;
-        const int t = j / tpr, tile = j - t * tpr;
-        const int lo = t * hs + (int)(((long long)k * hs) >> 3);
-        const int hi = min(t * hs + (int)(((long long)(k + 1) * hs) >> 3), Vh);
-        i = lo + tile * (int)blockDim.x + (int)threadIdx.x;
-        if (i >= hi) return;
-    }
     int c[4];
     const int s = parity_site(g, i, parity, c);
     cx<T> acc[NR][12];
@@ -217,6 +210,31 @@ void parity_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int pari
         Store<P>::store_spinor(tab.out[r0 + r], Vh, i, acc[r]);
 }
 
+template <int P, bool DAG, int SELF, bool HOP, bool INV, int ROWS, int NR, bool LONE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(parity_waves<P, NR>())))
+void parity_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int parity, int apbc, typename Store<P>::T fh,
+                   int slices, int tpr) {
+    const int Vh = g.V >> 1;
+    int i, r0;
+    {
+        // block -> (XCD k, slab t of `slices` T-slices, tile within the slab's k-th eighth), the register blocks of a
+        // tile in turn
+        const int hs = Vh / g.n[0] * slices;
+        const int groups = (tab.n + (LONE ? 1 : 0)) / NR;
+        const int k = blockIdx.x & 7, jj = blockIdx.x >> 3, j = jj / groups;
+        r0 = (jj - j * groups) * NR;
+        const int t = j / tpr, tile = j - t * tpr;
+        const int lo = t * hs + (int)(((long long)k * hs) >> 3);
+        const int hi = min(t * hs + (int)(((long long)(k + 1) * hs) >> 3), Vh);
+        i = lo + tile * (int)blockDim.x + (int)threadIdx.x;
+        if (i >= hi) return;
+    }
+    if (LONE && r0 + 1 == tab.n)
+        parity_site_apply<P, DAG, SELF, HOP, INV, ROWS, 1>(tab, d, cinv, g, parity, apbc, fh, i, r0);
+    else
+        parity_site_apply<P, DAG, SELF, HOP, INV, ROWS, NR>(tab, d, cinv, g, parity, apbc, fh, i, r0);
+}
+
 // Column walk of the parity kernel: a lane takes one (z, y, x) column and the
 // sites of the output parity in a T-chunk of kParChunk slices, i.e. every
 // second t.  The forward T neighbour psi(t+1) it loads at step t is also the
@@ -224,27 +242,15 @@ void parity_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int pari
 // U_T(t+1)^H (1 + s gamma_T) psi(t+1) is formed once and carried in registers
 // (one spinor load per site saved).  Work-groups are dealt as in the T-sweep
 // above: each XCD takes 1/8 of the columns of every T-chunk.
-template <int P, bool DAG, int SELF, bool HOP, bool INV, int ROWS, int NR, int CH>
-__global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpData d, const void *cinv, Geom g,
-                                                            int parity, int apbc, typename Store<P>::T fh,
-                                                            int tpr) {
+template <int P, bool DAG, int SELF, bool INV, int ROWS, int NR>
+__device__ __forceinline__ void parity_column_apply(const ParityTable &tab, const OpData &d, const void *cinv,
+                                                    const Geom &g, int parity, int apbc, typename Store<P>::T fh,
+                                                    int col, int t0, int r0) {
     using T = typename Store<P>::T;
-    static_assert(HOP, "the column walk carries T hops");
     constexpr int SF = DAG ? +1 : -1;
     constexpr int SB = -SF;
     const int Vh = g.V >> 1, C = g.stride[0], nT = g.n[0];
-    int col, t0, r0;
-    {
-        const int groups = tab.n / NR;
-        const int k = blockIdx.x & 7, jj = blockIdx.x >> 3, j = jj / groups;
-        r0 = (jj - j * groups) * NR;
-        const int tc = j / tpr, tile = j - tc * tpr;
-        const int q0 = (int)(((long long)k * C) >> 3), q1 = (int)(((long long)(k + 1) * C) >> 3);
-        col = q0 + tile * (int)blockDim.x + (int)threadIdx.x;
-        if (col >= q1) return;
-        t0 = tc * CH;
-    }
-    const int t1 = min(t0 + CH, nT);
+    const int t1 = min(t0 + kParChunk, nT);
     int c[4];
     c[3] = col % g.n[3];
     c[2] = (col / g.n[3]) % g.n[2];
@@ -309,7 +315,7 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
             const bool wrap = (t == nT - 1);
             const int tp = wrap ? 0 : t + 1;
             const T ff = (apbc && wrap) ? -fh : fh;
-            const bool next = CH > 2 && t + 2 < t1;  // chunks of 2 slices: one site per lane, nothing carried
+            const bool next = t + 2 < t1;
             cx<T> U[9], Un[9];
             Store<P>::load_link(d.links, g.V, 0, s, U, ROWS);
             if (next) Store<P>::load_link(d.links, g.V, 0, tp * C + col, Un, ROWS);
@@ -353,8 +359,32 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
     }
 }
 
-// one launch, NR right-hand sides per lane; tab.n is a multiple of NR
-template <int P, bool DAG, int SELF, bool HOP, bool INV, int NR>
+template <int P, bool DAG, int SELF, bool INV, int ROWS, int NR, bool LONE>
+__global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpData d, const void *cinv, Geom g,
+                                                            int parity, int apbc, typename Store<P>::T fh,
+                                                            int tpr) {
+    const int C = g.stride[0];
+    int col, t0, r0;
+    {
+        const int groups = tab.n / NR, lone = LONE ? (int)gridDim.x / (groups + 1) * groups : (int)gridDim.x;
+        const int k = blockIdx.x & 7, jj = blockIdx.x >> 3;
+        const bool last = LONE && (int)blockIdx.x >= lone;
+        const int j = last ? jj - (lone >> 3) : jj / groups;
+        r0 = last ? tab.n - 1 : (jj - j * groups) * NR;
+        const int tc = j / tpr, tile = j - tc * tpr;
+        const int q0 = (int)(((long long)k * C) >> 3), q1 = (int)(((long long)(k + 1) * C) >> 3);
+        col = q0 + tile * (int)blockDim.x + (int)threadIdx.x;
+        if (col >= q1) return;
+        t0 = tc * kParChunk;
+    }
+    if (LONE && r0 + 1 == tab.n)
+        parity_column_apply<P, DAG, SELF, INV, ROWS, 1>(tab, d, cinv, g, parity, apbc, fh, col, t0, r0);
+    else
+        parity_column_apply<P, DAG, SELF, INV, ROWS, NR>(tab, d, cinv, g, parity, apbc, fh, col, t0, r0);
+}
+
+// one launch, NR right-hand sides per lane; LONE: tab.n is odd, else a multiple of NR
+template <int P, bool DAG, int SELF, bool HOP, bool INV, int NR, bool LONE>
 hipError_t launch_nr(const dirac_op *op, int parity, const ParityTable &tab, double fh, hipStream_t st) {
     using T = typename Store<P>::T;
     const Geom &g = op->g;
@@ -364,47 +394,46 @@ hipError_t launch_nr(const dirac_op *op, int parity, const ParityTable &tab, dou
         if (column_walk(P, g.V)) {
             // T-chunks of kParChunk slices, each XCD 1/8 of the columns
             const int tpc = ((g.stride[0] + 7) / 8 + 255) / 256;
-            const dim3 grid((g.n[0] + kParChunk - 1) / kParChunk * 8 * tpc * (tab.n / NR));
+            const dim3 grid((g.n[0] + kParChunk - 1) / kParChunk * 8 * tpc * ((tab.n + NR - 1) / NR));
             if (rows2)
-                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 2, NR, kParChunk>), grid, dim3(256),
-                                   0, st, tab, op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
+                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, INV, 2, NR, LONE>), grid, dim3(256), 0, st, tab,
+                                   op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
             else
-                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 3, NR, kParChunk>), grid, dim3(256),
-                                   0, st, tab, op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
+                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, INV, 3, NR, LONE>), grid, dim3(256), 0, st, tab,
+                                   op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
             return hipGetLastError();
         }
     }
-    // an eighth of a slice below 32 sites: slabs of as many T-slices as keep an eighth within one wave (1024 x 4^3, two right-hand
-    // sides, FP32: by slices 119 us, in slabs 22)
+    // an eighth of a slice below 32 sites: slabs of as many T-slices as keep an eighth within one wave (1024 x 4^3, two
+    // right-hand sides, FP32: by slices 119 us, in slabs 22)
     const int hs = (g.V >> 1) / g.n[0], q = hs < 256 ? slab_slices(g.n[0], hs, 512) : 1;
     const int tpr = ((q * hs + 7) / 8 + 255) / 256;  // 256-site tiles per eighth of a slab
-    const dim3 grid((g.n[0] + q - 1) / q * 8 * tpr * (tab.n / NR));
+    const dim3 grid((g.n[0] + q - 1) / q * 8 * tpr * ((tab.n + NR - 1) / NR));
     if (rows2)
-        hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 2, NR>), grid, dim3(256), 0, st, tab, op->data(P),
-                           op->cinv(P), g, parity, apbc, (T)fh, q, tpr);
+        hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 2, NR, LONE>), grid, dim3(256), 0, st, tab,
+                           op->data(P), op->cinv(P), g, parity, apbc, (T)fh, q, tpr);
     else
-        hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 3, NR>), grid, dim3(256), 0, st, tab, op->data(P),
-                           op->cinv(P), g, parity, apbc, (T)fh, q, tpr);
+        hipLaunchKernelGGL((parity_kernel<P, DAG, SELF, HOP, INV, 3, NR, LONE>), grid, dim3(256), 0, st, tab,
+                           op->data(P), op->cinv(P), g, parity, apbc, (T)fh, q, tpr);
     return hipGetLastError();
 }
 
 template <int P, bool DAG, int SELF, bool HOP, bool INV>
 hipError_t launch_mode(const dirac_op *op, int parity, const ParityItem *items, size_t nitems, double fh,
                        hipStream_t st) {
-    const int nrmax = rhs_per_lane(op->g.V, nitems);
-    for (size_t a = 0; a < nitems;) {
-        const size_t left = nitems - a;
-        const int nr = left >= 2 ? nrmax : 1;
+    const int nr = rhs_per_lane(op->g.V, nitems);
+    for (size_t a = 0; a < nitems; a += kParMax) {
         ParityTable tab;
-        tab.n = (int)std::min<size_t>(kParMax, left / nr * nr);
+        tab.n = (int)std::min<size_t>(kParMax, nitems - a);
         for (int q = 0; q < tab.n; q++) {
             tab.out[q] = items[a + q].out;
             tab.self[q] = items[a + q].self;
             tab.hop[q] = items[a + q].hop;
         }
-        a += tab.n;
-        const hipError_t e = nr == 2 ? launch_nr<P, DAG, SELF, HOP, INV, 2>(op, parity, tab, fh, st)
-                                     : launch_nr<P, DAG, SELF, HOP, INV, 1>(op, parity, tab, fh, st);
+        hipError_t e;
+        if (nr == 1 || tab.n == 1) e = launch_nr<P, DAG, SELF, HOP, INV, 1, false>(op, parity, tab, fh, st);
+        else if (tab.n % 2) e = launch_nr<P, DAG, SELF, HOP, INV, 2, true>(op, parity, tab, fh, st);
+        else e = launch_nr<P, DAG, SELF, HOP, INV, 2, false>(op, parity, tab, fh, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -56,6 +56,14 @@ def test_reduced_operator_slabs(dims, n, prec, compress, ap):
     test_reduced_operator_shapes(dims, n, prec, compress, ap)
 
 
+# odd counts in pairs: the last right-hand side in the pairs' launch, and after a full launch of sixteen
+@pytest.mark.parametrize("dims,n", [((16, 16, 16, 16), 17), ((16, 16, 16, 34), 3)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("compress,ap", [(True, False), (False, True)])
+def test_reduced_operator_odd_counts(dims, n, prec, compress, ap):
+    test_reduced_operator_shapes(dims, n, prec, compress, ap)
+
+
 # applies neither tuned nor set. The small-lattice kernel (V n up to 2^14 at FP64, 2^15 else): ragged tiles at
 # 3 x 5 x 7 x 9, extents of two, 8^4 with 4 and 8 on the two lines and 5 and 9 past them. 12^4: one right-hand side
 # per lane up to 6, pairs at 7 (past 2^17 site-right-hand-sides). 16^4: pairs, at FP32 with two-row links
