@@ -72,10 +72,20 @@ constexpr int kParChunk = 4;  // T-slices per chunk of the column walk (kParChun
 static_assert(kParChunk > 2, "the column walk carries a hop from a lane's site to its next");
 constexpr long long kParPairs = 1LL << 18;
 inline int rhs_per_lane(long long V, size_t n) { return n >= 2 && V * (long long)n > kParPairs ? 2 : 1; }
-// FP64 above 2^17 sites walks T columns (parity_column_kernel); below it the columns leave the chip idle: S of a
-// pair at 16^4 96 us against 47, at 32 x 16^2 x 32 185 against 204.  At FP32 the column walk is slower than the
-// site kernel with four hops in flight (64 x 32^3 pair 674 against 619), at FP16S too.
-inline bool column_walk(int prec, int V) { return prec == WDIRAC_F64 && V > 1 << 17; }
+// FP64 walks T columns (parity_column_kernel) above 2^17 sites, and below them where the pairs' waves (V / 256 per
+// pair, one per SIMD by their registers) fill whole rounds of the chip's 1024 SIMDs.  The two give the same bits.  us,
+// two-row links, site kernel against columns: 32 x 8 x 16 x 32 (512 waves a pair) two 99 / 111, four 187 / 156, five
+// 247 / 231, six 244 / 239, eight 310 / 283; 16^4 (256) two 43 / 94, five 104 / 107, six 107 / 111, eight 142 / 130,
+// twelve 196 / 214, sixteen 254 / 230; 16 x 12 x 24^2 (432) four 138 / 129, six 203 / 215, twelve 340 / 331, sixteen
+// 408 / 430.  At FP32 the column walk is slower than the site kernel with four hops in flight (64 x 32^3 pair 674
+// against 619), at FP16S too.
+inline bool column_walk(int prec, int V, size_t n) {
+    if (prec != WDIRAC_F64) return false;
+    if (V > 1 << 17) return true;
+    const long long waves = (long long)V * ((n + 1) / 2) / 256, rounds = (waves + 1023) / 1024;
+    const int percent = V == 1 << 17 ? 75 : rounds > 3 ? 95 : 80;
+    return n > 2 && 100 * waves >= percent * rounds * 1024;
+}
 // hops between two fences
 template <int P, int NR> constexpr int parity_fence() {
     return P == WDIRAC_F64 ? (NR == 1 ? 2 : 1) : (P == WDIRAC_F16S && NR == 1) ? 8 : 4;
@@ -385,13 +395,14 @@ __global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpD
 
 // one launch, NR right-hand sides per lane; LONE: tab.n is odd, else a multiple of NR
 template <int P, bool DAG, int SELF, bool HOP, bool INV, int NR, bool LONE>
-hipError_t launch_nr(const dirac_op *op, int parity, const ParityTable &tab, double fh, hipStream_t st) {
+hipError_t launch_nr(const dirac_op *op, int parity, const ParityTable &tab, double fh, bool column,
+                     hipStream_t st) {
     using T = typename Store<P>::T;
     const Geom &g = op->g;
     const int apbc = (op->flags & WDIRAC_ANTIPERIODIC_T) ? 1 : 0;
     const bool rows2 = op->link_rows == 2 || !HOP;
     if constexpr (HOP && P == WDIRAC_F64) {
-        if (column_walk(P, g.V)) {
+        if (column) {
             // T-chunks of kParChunk slices, each XCD 1/8 of the columns
             const int tpc = ((g.stride[0] + 7) / 8 + 255) / 256;
             const dim3 grid((g.n[0] + kParChunk - 1) / kParChunk * 8 * tpc * ((tab.n + NR - 1) / NR));
@@ -422,6 +433,7 @@ template <int P, bool DAG, int SELF, bool HOP, bool INV>
 hipError_t launch_mode(const dirac_op *op, int parity, const ParityItem *items, size_t nitems, double fh,
                        hipStream_t st) {
     const int nr = rhs_per_lane(op->g.V, nitems);
+    const bool column = column_walk(P, op->g.V, nitems);
     for (size_t a = 0; a < nitems; a += kParMax) {
         ParityTable tab;
         tab.n = (int)std::min<size_t>(kParMax, nitems - a);
@@ -431,9 +443,9 @@ hipError_t launch_mode(const dirac_op *op, int parity, const ParityItem *items, 
             tab.hop[q] = items[a + q].hop;
         }
         hipError_t e;
-        if (nr == 1 || tab.n == 1) e = launch_nr<P, DAG, SELF, HOP, INV, 1, false>(op, parity, tab, fh, st);
-        else if (tab.n % 2) e = launch_nr<P, DAG, SELF, HOP, INV, 2, true>(op, parity, tab, fh, st);
-        else e = launch_nr<P, DAG, SELF, HOP, INV, 2, false>(op, parity, tab, fh, st);
+        if (nr == 1 || tab.n == 1) e = launch_nr<P, DAG, SELF, HOP, INV, 1, false>(op, parity, tab, fh, column, st);
+        else if (tab.n % 2) e = launch_nr<P, DAG, SELF, HOP, INV, 2, true>(op, parity, tab, fh, column, st);
+        else e = launch_nr<P, DAG, SELF, HOP, INV, 2, false>(op, parity, tab, fh, column, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -64,6 +64,14 @@ def test_reduced_operator_odd_counts(dims, n, prec, compress, ap):
     test_reduced_operator_shapes(dims, n, prec, compress, ap)
 
 
+# FP64 below 2^17 sites: columns where the pairs' waves fill whole rounds (16^4 of eight, 16 x 12 x 24^2 of three), the
+# same bits as the site kernel of a single right-hand side
+@pytest.mark.parametrize("dims,n", [((16, 16, 16, 16), 8), ((16, 12, 24, 24), 3)])
+@pytest.mark.parametrize("compress,ap", [(True, False), (False, True)])
+def test_reduced_operator_rounds(dims, n, compress, ap):
+    test_reduced_operator_shapes(dims, n, "f64", compress, ap)
+
+
 # applies neither tuned nor set. The small-lattice kernel (V n up to 2^14 at FP64, 2^15 else): ragged tiles at
 # 3 x 5 x 7 x 9, extents of two, 8^4 with 4 and 8 on the two lines and 5 and 9 past them. 12^4: one right-hand side
 # per lane up to 6, pairs at 7 (past 2^17 site-right-hand-sides). 16^4: pairs, at FP32 with two-row links
