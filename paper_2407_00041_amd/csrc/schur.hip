@@ -90,6 +90,11 @@ inline bool column_walk(int prec, int V, size_t n) {
 template <int P, int NR> constexpr int parity_fence() {
     return P == WDIRAC_F64 ? (NR == 1 ? 2 : 1) : (P == WDIRAC_F16S && NR == 1) ? 8 : 4;
 }
+// The same for the column walk, which runs one wave per SIMD at most: a single right-hand side's registers would allow
+// two, whose columns then displace each other's neighbours from the L2 (S of one, us, hops between fences 1 / 2 / 4:
+// 32^4 one wave 468 / 466 / 474, two 539 / 528 / 511; 48 x 24^3 309 / 309 / 311, 344 / 340 / 328; 48^3 x 96 4953 / 4947
+// / 4987, 5173 / 5144 / 5096; 32 x 16^2 x 32 118 / 118 / 118, 118 / 118 / 119)
+template <int NR> constexpr int column_fence() { return NR == 1 ? 2 : 4; }
 // waves per SIMD the registers must allow: with these the kernels just do not spill
 template <int P, int NR> constexpr int parity_waves() {
     return P == WDIRAC_F64 ? 2 : P == WDIRAC_F32 ? (NR == 1 ? 4 : 2) : 3;
@@ -344,9 +349,9 @@ __device__ __forceinline__ void parity_column_apply(const ParityTable &tab, cons
             }
         }
         hop_boundary<T, NR>(acc);
-        parity_hops<P, 1, DAG, ROWS, NR, 4>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
-        parity_hops<P, 2, DAG, ROWS, NR, 4>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
-        parity_hops<P, 3, DAG, ROWS, NR, 4>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 1, DAG, ROWS, NR, column_fence<NR>()>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 2, DAG, ROWS, NR, column_fence<NR>()>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
+        parity_hops<P, 3, DAG, ROWS, NR, column_fence<NR>()>(d, g, tab, r0, Vh, s, c, apbc != 0, fh, acc);
         if (INV) {
 #pragma unroll
             for (int b = 0; b < 2; b++) {
@@ -370,9 +375,9 @@ __device__ __forceinline__ void parity_column_apply(const ParityTable &tab, cons
 }
 
 template <int P, bool DAG, int SELF, bool INV, int ROWS, int NR, bool LONE>
-__global__ __launch_bounds__(256) void parity_column_kernel(ParityTable tab, OpData d, const void *cinv, Geom g,
-                                                            int parity, int apbc, typename Store<P>::T fh,
-                                                            int tpr) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void parity_column_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int parity, int apbc,
+                          typename Store<P>::T fh, int tpr) {
     const int C = g.stride[0];
     int col, t0, r0;
     {
