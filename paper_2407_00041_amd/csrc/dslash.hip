@@ -149,7 +149,7 @@ __device__ __forceinline__ void site_apply(const Chunk<NR> &ch, const OpData &d,
 // in registers, so no T-neighbour spinor or backward T link is re-read.
 template <int P, bool DAG, int ROWS, int NR, int FENCE>
 __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &d, const Geom &g, int c, int t0,
-                                             int t1, bool apbc) {
+                                             int t1, bool apbc, cx<typename Store<P>::T> (*ut_lds)[9]) {
     using T = typename Store<P>::T;
     constexpr int SF = DAG ? +1 : -1;
     constexpr int SB = -SF;
@@ -195,7 +195,6 @@ __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &
         const bool last = (t == nT - 1);
         // U_T(s) serves both T hops of the step; the copy parked in the lane's LDS slot between them spares a
         // second load through the L2, which by then has often evicted it (measured: -75 B read per site)
-        __shared__ cx<T> ut_lds[256][9];
         {
             const T f = (apbc && last) ? T(0.5) : T(-0.5);
             cx<T> U[9];
@@ -324,39 +323,114 @@ void dslash_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int apbc) {
     }
 }
 
+// right-hand sides k .. k + N of a register block as a block of their own
+template <int N, int NR> __device__ __forceinline__ Chunk<N> sub_chunk(const Chunk<NR> &c, int k) {
+    Chunk<N> o;
+#pragma unroll
+    for (int r = 0; r < N; r++) {
+        o.in[r] = c.in[k + r];
+        o.out[r] = c.out[k + r];
+    }
+    return o;
+}
+
+// dslash_kernel with a last register block of `rest` < NR right-hand sides, tab.c[tab.nchunks].  As launches of their own
+// the last few left most of the chip idle (us, three right-hand sides, 16^4 FP32 25.4 -> 18.5, 24 x 16^2 x 24 FP32 59.9
+// -> 51.4; seven at 12^4 FP64 43 -> 31).  FP64 and FP32 take it in its tile's turn (after all whole blocks: 51.4 -> 61.1),
+// FP16S after all whole blocks (32^4, three: 183, in turn 200).  A kernel of its own, since the second path would change
+// the whole blocks' registers.
+template <int P, bool DAG, int ROWS, int NR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(occupancy<P, NR>())))
+void dslash_rest_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int apbc, int rest) {
+    constexpr bool in_turn = P != WDIRAC_F16S;
+    const int blocks = tab.nchunks + (in_turn ? 1 : 0), nitems = m.nslots * (tab.nchunks + 1);
+    for (int w = blockIdx.x; w < nitems; w += gridDim.x) {
+        const bool after = !in_turn && w >= m.nslots * blocks;  // nslots is a multiple of 8
+        const int xcd = w & 7, q = w >> 3;
+        const int vb = after ? w - m.nslots * blocks : (q / blocks) * 8 + xcd;
+        const int c = after ? tab.nchunks : q - (q / blocks) * blocks;
+        int lo, hi;
+        tile_range(m, vb, lo, hi);
+        const int s = lo + (int)threadIdx.x;
+        if (s >= hi) continue;
+        if (c < tab.nchunks) {
+            site_apply<P, DAG, ROWS, NR, site_fence<P, NR>()>(tab.c[c], d, g, s, apbc != 0);
+            continue;
+        }
+        const Chunk<NR> &ch = tab.c[tab.nchunks];
+        if (NR == 4 && (rest & 2))
+            site_apply<P, DAG, ROWS, 2, site_fence<P, 2>()>(sub_chunk<2>(ch, 0), d, g, s, apbc != 0);
+        if (rest & 1)
+            site_apply<P, DAG, ROWS, 1, site_fence<P, 1>()>(sub_chunk<1>(ch, rest - 1), d, g, s, apbc != 0);
+    }
+}
+
 // the same for the column kernel, which carries psi(t+1) and the T half-spinors
 template <int P, int NR> constexpr int column_fence() {
     return P == WDIRAC_F64 ? (NR == 1 ? 2 : 4) : P == WDIRAC_F32 ? 4 : 8;
 }
 template <int P, int NR> constexpr int occupancy_col() { return NR == 1 ? 2 : 1; }
 
+// column and T range of a lane of tile slot vb: the columns of XCD k's 1/8 of a slice (or of its patches), T-chunk tc;
+// -1: none
+__device__ __forceinline__ int tile_column(const TileMap &m, const Geom &g, int vb, int &t0, int &t1) {
+    const int k = vb & 7, j = vb >> 3;
+    const int tc = j / m.tiles_per_range, tile = j - tc * m.tiles_per_range;
+    t0 = tc * m.tchunk;
+    t1 = min(t0 + m.tchunk, g.n[0]);
+    int col = -1;
+    if (m.order == kOrderPatch) {
+        const int p0 = (int)(((long long)k * m.patches) >> 3), p1 = (int)(((long long)(k + 1) * m.patches) >> 3);
+        const int pi = p0 + tile;
+        const int lx = (int)threadIdx.x % kPatchX, ly = ((int)threadIdx.x / kPatchX) % kPatchY,
+                  lz = (int)threadIdx.x / (kPatchX * kPatchY);
+        const int px = pi % m.npx, py = (pi / m.npx) % m.npy, pzi = pi / (m.npx * m.npy);
+        const int x = px * kPatchX + lx, y = py * kPatchY + ly, z = pzi * m.pz + lz;
+        if (pi < p1 && x < g.n[3] && y < g.n[2] && z < g.n[1]) col = (z * g.n[2] + y) * g.n[3] + x;
+    } else {
+        const int r0 = (int)(((long long)k * m.slice) >> 3), r1 = (int)(((long long)(k + 1) * m.slice) >> 3);
+        const int cc = r0 + tile * m.block + (int)threadIdx.x;
+        if (cc < r1) col = cc;
+    }
+    return t0 < t1 ? col : -1;
+}
+
 template <int P, bool DAG, int ROWS, int NR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(occupancy_col<P, NR>())))
 void dslash_column_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int apbc) {
+    __shared__ cx<typename Store<P>::T> ut_lds[256][9];
     const int nitems = m.nslots * tab.nchunks;
     for (int w = blockIdx.x; w < nitems; w += gridDim.x) {
         const int xcd = w & 7, q = w >> 3;
         const int vb = (q / tab.nchunks) * 8 + xcd;
         const int c = q - (q / tab.nchunks) * tab.nchunks;
-        // columns of XCD k's 1/8 of a slice (or of its patches), T-chunk tc
-        const int k = vb & 7, j = vb >> 3;
-        const int tc = j / m.tiles_per_range, tile = j - tc * m.tiles_per_range;
-        const int t0 = tc * m.tchunk, t1 = min(t0 + m.tchunk, g.n[0]);
-        int col = -1;
-        if (m.order == kOrderPatch) {
-            const int p0 = (int)(((long long)k * m.patches) >> 3), p1 = (int)(((long long)(k + 1) * m.patches) >> 3);
-            const int pi = p0 + tile;
-            const int lx = (int)threadIdx.x % kPatchX, ly = ((int)threadIdx.x / kPatchX) % kPatchY,
-                      lz = (int)threadIdx.x / (kPatchX * kPatchY);
-            const int px = pi % m.npx, py = (pi / m.npx) % m.npy, pzi = pi / (m.npx * m.npy);
-            const int x = px * kPatchX + lx, y = py * kPatchY + ly, z = pzi * m.pz + lz;
-            if (pi < p1 && x < g.n[3] && y < g.n[2] && z < g.n[1]) col = (z * g.n[2] + y) * g.n[3] + x;
-        } else {
-            const int r0 = (int)(((long long)k * m.slice) >> 3), r1 = (int)(((long long)(k + 1) * m.slice) >> 3);
-            const int cc = r0 + tile * m.block + (int)threadIdx.x;
-            if (cc < r1) col = cc;
-        }
-        if (col >= 0 && t0 < t1) column_sweep<P, DAG, ROWS, NR, column_fence<P, NR>()>(tab.c[c], d, g, col, t0, t1, apbc != 0);
+        int t0, t1;
+        const int col = tile_column(m, g, vb, t0, t1);
+        if (col >= 0)
+            column_sweep<P, DAG, ROWS, NR, column_fence<P, NR>()>(tab.c[c], d, g, col, t0, t1, apbc != 0, ut_lds);
+    }
+}
+
+// the same with a lone last right-hand side, tab.c[tab.nchunks], after all pairs: its work-groups fill the pairs' last
+// round (us, as a launch of its own and now: 48 x 24^3 five FP64 750 -> 682, FP32 397 -> 343)
+template <int P, bool DAG, int ROWS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(occupancy_col<P, 2>())))
+void dslash_column_rest_kernel(ChunkTable<2> tab, OpData d, Geom g, TileMap m, int apbc) {
+    __shared__ cx<typename Store<P>::T> ut_lds[256][9];
+    const int pairs = m.nslots * tab.nchunks, nitems = pairs + m.nslots;  // nslots is a multiple of 8
+    for (int w = blockIdx.x; w < nitems; w += gridDim.x) {
+        const int xcd = w & 7, q = w >> 3;
+        const bool lone = w >= pairs;
+        const int vb = lone ? w - pairs : (q / tab.nchunks) * 8 + xcd;
+        int t0, t1;
+        const int col = tile_column(m, g, vb, t0, t1);
+        if (col < 0) continue;
+        if (lone)
+            column_sweep<P, DAG, ROWS, 1, column_fence<P, 1>()>(sub_chunk<1>(tab.c[tab.nchunks], 0), d, g, col, t0, t1,
+                                                                apbc != 0, ut_lds);
+        else
+            column_sweep<P, DAG, ROWS, 2, column_fence<P, 2>()>(tab.c[q - (q / tab.nchunks) * tab.nchunks], d, g, col,
+                                                                t0, t1, apbc != 0, ut_lds);
     }
 }
 
@@ -680,16 +754,14 @@ Tuning tuning_snapshot() {
 }
 
 // Work-groups of one kernel instance that fit on the device at once.
-template <int P, bool DAG, int ROWS, int NR>
-static int resident_blocks(int block) {
+template <auto Kernel> static int resident_blocks(int block) {
     static int cached[5] = {0, 0, 0, 0, 0};
     const int slot = block / 64;
     if (!cached[slot]) {
         int dev = 0, cus = 0, per_cu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, dslash_kernel<P, DAG, ROWS, NR>, block, 0) != hipSuccess ||
-            cus * per_cu < 8) {
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, Kernel, block, 0) != hipSuccess || cus * per_cu < 8) {
             (void)hipGetLastError();
             return 8;
         }
@@ -698,87 +770,68 @@ static int resident_blocks(int block) {
     return cached[slot];
 }
 
-template <int P, bool DAG, int ROWS, int NR>
-static int resident_blocks_col(int block) {
-    static int cached[5] = {0, 0, 0, 0, 0};
-    const int slot = block / 64;
-    if (!cached[slot]) {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, dslash_column_kernel<P, DAG, ROWS, NR>, block, 0) !=
-                hipSuccess ||
-            cus * per_cu < 8) {
-            (void)hipGetLastError();
-            return 8;
-        }
-        cached[slot] = cus * per_cu / 8 * 8;
-    }
-    return cached[slot];
-}
-
-template <int P, bool DAG, int ROWS, int NR>
-static hipError_t launch_chunks(const std::vector<Chunk<NR>> &chunks, const OpData &d, const Geom &g, int apbc,
-                                bool persistent, const LaunchCfg &cfg, hipStream_t st) {
+// One launch of `blocks` register blocks over the tiles of m.  A persistent grid has at most the resident work-groups,
+// each striding through the item list (by default the hardware dispatcher hands out one work-group per item in order,
+// which measured faster).
+template <auto Kernel, typename Tab, typename... Rest>
+static hipError_t launch_items(int blocks, const Tab &tab, const OpData &d, const Geom &g, const TileMap &m, int apbc,
+                               bool persistent, const LaunchCfg &cfg, hipStream_t st, Rest... rest) {
     const Tuning tu = tuning_snapshot();
+    long long grid = (long long)m.nslots * blocks;
+    if ((persistent && tu.persistent_blocks > 0) || cfg.persistent) {
+        long long cap = resident_blocks<Kernel>(cfg.block);
+        if (tu.persistent_blocks > 0 && tu.persistent_blocks < cap) cap = tu.persistent_blocks / 8 * 8;
+        if (cap < 8) cap = 8;
+        if (grid > cap) grid = cap;
+    }
+    if (grid > (1LL << 30)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(Kernel, dim3((unsigned)grid), dim3(cfg.block), 0, st, tab, d, g, m, apbc, rest...);
+    return hipGetLastError();
+}
+
+// Group the right-hand sides of all batches, in order, into register blocks
+// of NR (a block may span batches), the remainder into a smaller last one.
+template <int P, bool DAG, int ROWS, int NR>
+static hipError_t launch_nr(const std::pair<const void *, void *> *rhs, size_t n, const OpData &d, const Geom &g,
+                            int apbc, bool persistent, const LaunchCfg &cfg, hipStream_t st) {
     constexpr int NRC = NR > 2 ? 2 : NR;  // the column kernels take at most two right-hand sides per lane
     const TileMap m = make_tilemap(g, cfg.order, cfg.block, cfg.tchunk);
     const bool column = is_column_order(m.order);
     if (column && NR != NRC) return hipErrorInvalidValue;
-    for (size_t c0 = 0; c0 < chunks.size(); c0 += kMaxChunks) {
+    size_t rest = n % NR;
+    for (size_t k = 0; k + NR <= n;) {
         ChunkTable<NR> tab;
-        tab.nchunks = (int)std::min(chunks.size() - c0, (size_t)kMaxChunks);
-        for (int i = 0; i < tab.nchunks; i++) tab.c[i] = chunks[c0 + i];
-        const long long items = (long long)m.nslots * tab.nchunks;
-        long long grid = items;
-        if ((persistent && tu.persistent_blocks > 0) || cfg.persistent) {
-            // a persistent grid: at most the resident work-groups, each striding
-            // through the item list (by default the hardware dispatcher hands
-            // out one work-group per item in order, which measured faster)
-            long long cap = column ? resident_blocks_col<P, DAG, ROWS, NRC>(cfg.block)
-                                   : resident_blocks<P, DAG, ROWS, NR>(cfg.block);
-            if (tu.persistent_blocks > 0 && tu.persistent_blocks < cap) cap = tu.persistent_blocks / 8 * 8;
-            if (cap < 8) cap = 8;
-            if (grid > cap) grid = cap;
+        tab.nchunks = (int)std::min((n - k) / NR, (size_t)kMaxChunks);
+        for (int i = 0; i < tab.nchunks * NR; i++, k++) {
+            tab.c[i / NR].in[i % NR] = rhs[k].first;
+            tab.c[i / NR].out[i % NR] = rhs[k].second;
         }
-        if (grid > (1LL << 30)) return hipErrorInvalidValue;
-        if constexpr (NR == NRC) {
-            if (column) {
-                hipLaunchKernelGGL((dslash_column_kernel<P, DAG, ROWS, NR>), dim3((unsigned)grid), dim3(cfg.block), 0,
-                                   st, tab, d, g, m, apbc);
-                const hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return e;
-                continue;
+        hipError_t e = hipSuccess;
+        if constexpr (NR > 1) {
+            if (rest && k + rest == n && tab.nchunks < kMaxChunks) {
+                for (size_t i = 0; i < rest; i++) {
+                    tab.c[tab.nchunks].in[i] = rhs[k + i].first;
+                    tab.c[tab.nchunks].out[i] = rhs[k + i].second;
+                }
+                if (!column)
+                    return launch_items<&dslash_rest_kernel<P, DAG, ROWS, NR>>(tab.nchunks + 1, tab, d, g, m, apbc,
+                                                                               persistent, cfg, st, (int)rest);
+                if constexpr (NR == 2)
+                    return launch_items<&dslash_column_rest_kernel<P, DAG, ROWS>>(tab.nchunks + 1, tab, d, g, m, apbc,
+                                                                                  persistent, cfg, st);
             }
         }
-        hipLaunchKernelGGL((dslash_kernel<P, DAG, ROWS, NR>), dim3((unsigned)grid), dim3(cfg.block), 0, st, tab, d, g,
-                           m, apbc);
-        hipError_t e = hipGetLastError();
+        if (!column)
+            e = launch_items<&dslash_kernel<P, DAG, ROWS, NR>>(tab.nchunks, tab, d, g, m, apbc, persistent, cfg, st);
+        else if constexpr (NR == NRC)
+            e = launch_items<&dslash_column_kernel<P, DAG, ROWS, NR>>(tab.nchunks, tab, d, g, m, apbc, persistent, cfg,
+                                                                      st);
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
-}
-
-// Group the right-hand sides of all batches, in order, into register blocks
-// of NR (a block may span batches), the remainder into smaller ones.
-template <int P, bool DAG, int ROWS, int NR>
-static hipError_t launch_nr(const std::pair<const void *, void *> *rhs, size_t n, const OpData &d, const Geom &g,
-                            int apbc, bool persistent, const LaunchCfg &cfg, hipStream_t st) {
-    std::vector<Chunk<NR>> chunks(n / NR);
-    for (size_t q = 0; q < chunks.size(); q++)
-        for (int r = 0; r < NR; r++) {
-            chunks[q].in[r] = rhs[q * NR + r].first;
-            chunks[q].out[r] = rhs[q * NR + r].second;
-        }
-    if (!chunks.empty()) {
-        const hipError_t e = launch_chunks<P, DAG, ROWS, NR>(chunks, d, g, apbc, persistent, cfg, st);
-        if (e != hipSuccess) return e;
-    }
-    if constexpr (NR > 1) {
-        const size_t done = n / NR * NR;
-        if (done < n)
-            return launch_nr<P, DAG, ROWS, NR / 2>(rhs + done, n - done, d, g, apbc, persistent, cfg, st);
-    }
+    // fewer than one block, or the table was full
+    if constexpr (NR > 1)
+        if (rest)
+            return launch_nr<P, DAG, ROWS, NR / 2>(rhs + (n - rest), rest, d, g, apbc, persistent, cfg, st);
     return hipSuccess;
 }
 

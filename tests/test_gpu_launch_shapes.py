@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from oracle import evenodd, sap as osap
-from paper_2407_00041_amd import DiracOp, clover_term, synth
+from paper_2407_00041_amd import DiracOp, clover_term, synth, tune_get, tune_set
 
 from util import TOL, need_gpu, rel_l2
 
@@ -101,6 +101,40 @@ def test_untuned_apply_shapes(dims, n, prec, compress, ap, dagger):
         want = oracle.dirac_apply_sites(dims, U, psi[r].cpu().numpy(), sites, -0.3, 1.0, antiperiodic_t=ap,
                                         dagger=dagger)
         assert rel_l2(got[r], want) < TOL[prec], r
+
+
+# counts that the register block does not divide, knobs set: the rest in the whole blocks' launch (9 in pairs; 5, 6, 7 in
+# fours), alone (3 in fours) and after a full table of 24 blocks (49 in pairs, 99 in fours); and more right-hand sides
+# than a table of the small-lattice kernel (26, neither tuned nor set)
+@pytest.mark.parametrize("order,nr,n", [(2, 2, 9), (3, 2, 9), (2, 2, 49), (3, 2, 49), (2, 4, 3), (2, 4, 5), (2, 4, 6),
+                                        (2, 4, 7), (6, 4, 7), (2, 4, 99), (None, 1, 26)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("compress", [True, False])
+def test_register_block_rests(order, nr, n, prec, compress):
+    need_gpu()
+    dims = (4, 6, 2, 6)
+    U = synth.smooth_links(dims, 84).numpy()
+    op = DiracOp(dims, U, -0.3, 1.0, antiperiodic_t=True, compress_links=compress, compress_clover=compress)
+    psi = synth.gaussian_spinor(dims, 85, nrhs=n)
+    x = op.pack(torch.from_numpy(psi).cuda(), prec)
+    out, one = op.empty(prec, n).zero_(), op.empty(prec, 1).zero_()
+    saved = {k: tune_get(k) for k in ("order", "nr_" + prec, "explicit")}
+    try:
+        if order is not None:
+            tune_set("order", order)
+            tune_set("nr_" + prec, nr)
+        op.apply_native(out, x, n, prec)
+        rb = op.field_bytes(prec, 1)
+        for r in range(n):
+            op.apply_native(one, x[r * rb:(r + 1) * rb], 1, prec)
+            assert torch.equal(one, out[r * rb:(r + 1) * rb]), r
+    finally:
+        for k, v in saved.items():
+            tune_set(k, v)
+    got = op.unpack(out, prec, n).cpu().numpy()
+    want = oracle.dirac_apply(dims, U, psi, -0.3, 1.0, antiperiodic_t=True)
+    for r in range(n):
+        assert rel_l2(got[r], want[r]) < TOL[prec], r
 
 
 # 64-site tiles over eighths of a T-slice: ragged eighths, a slice below one tile, extents of two, whole tiles
