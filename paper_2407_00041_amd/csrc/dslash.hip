@@ -244,7 +244,7 @@ __device__ __forceinline__ void column_sweep(const Chunk<NR> &ch, const OpData &
     }
 }
 
-// site range [lo, hi) of tile slot vb (see TileMap in dslash.h)
+// site range [lo, hi) of tile slot vb (see TileMap in dslash.h); hi may lie before lo
 __device__ __forceinline__ void tile_range(const TileMap &m, int vb, int &lo, int &hi) {
     if (m.order == kOrderTSweep) {
         const int k = vb & 7, j = vb >> 3;
@@ -253,7 +253,7 @@ __device__ __forceinline__ void tile_range(const TileMap &m, int vb, int &lo, in
         const int r0 = base + (int)(((long long)k * m.slice) >> 3);
         const int r1 = base + (int)(((long long)(k + 1) * m.slice) >> 3);
         lo = r0 + tile * m.block;
-        hi = min(lo + m.block, r1);
+        hi = min(lo + m.block, min(r1, m.V));
     } else if (m.order == kOrderZPlanes) {
         const int k = vb & 7, j = vb >> 3;
         const int q = j / m.plane_tiles, tile = j - q * m.plane_tiles;
@@ -412,7 +412,7 @@ void dslash_column_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int a
 }
 
 // the same with a lone last right-hand side, tab.c[tab.nchunks], after all pairs: its work-groups fill the pairs' last
-// round (us, as a launch of its own and now: 48 x 24^3 five FP64 750 -> 682, FP32 397 -> 343)
+// round (us, as a launch of its own and now: 48 x 24^3 five FP64 751 -> 697, FP32 396 -> 321)
 template <int P, bool DAG, int ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(occupancy_col<P, 2>())))
 void dslash_column_rest_kernel(ChunkTable<2> tab, OpData d, Geom g, TileMap m, int apbc) {
@@ -732,9 +732,13 @@ TileMap make_tilemap(const Geom &g, int order, int block, int tchunk) {
         m.plane_tiles = (m.slice / m.nz + block - 1) / block;
         m.ntiles = (m.nz + 7) / 8 * m.nt * m.plane_tiles * 8;
     } else if (order == kOrderTSweep) {
+        // an eighth of a slice below 48 sites: slabs of as many T-slices as keep an eighth within one wave (us, 1024 x
+        // 4^3, one right-hand side, by slices and in slabs: FP64 67 -> 19, FP32 37 -> 9.8)
+        const int q = m.slice < 384 ? slab_slices(g.n[0], m.slice, 512) : 1;
+        m.slice *= q;
         const int per_range = (m.slice + 7) / 8;
         m.tiles_per_range = (per_range + block - 1) / block;
-        m.ntiles = g.n[0] * 8 * m.tiles_per_range;
+        m.ntiles = (g.n[0] + q - 1) / q * 8 * m.tiles_per_range;
     } else {
         m.tiles_per_range = 0;
         m.ntiles = (g.V + block - 1) / block;
@@ -971,12 +975,24 @@ hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, b
 // pairs 445).  The link-stationary kernel (the site kernel's order and bits) takes six and more FP32 right-hand sides
 // between 16^4 and 2^18 sites: 12 at 16^4 67 -> 54; at 12^4 25 against 49.  Up to 2^14 site-right-hand-sides at FP64,
 // 2^15 else, the small-lattice kernel (measured there; same bits as the site kernel).
-static LaunchCfg default_cfg(int V, int prec, int n, int rows) {
+// Thin lattices: columns and z-pairs only where the maps keep the lanes busy.  4096 x 4^3 has eight columns an XCD (FP64,
+// us, one right-hand side: columns 349, site kernel in slabs 95); 512 x 8^3 has 64, one wave of a work-group whose LDS is
+// for four, which pairs, one wave per SIMD, do not make up for (eight: pairs 967, one per lane 449); 64 x 4 x 16^2 has two
+// z-pairs for eight XCDs (FP32 of eight: link-stationary 105, site kernel 52).
+static LaunchCfg default_cfg(const Geom &g, int prec, int n, int rows) {
+    const int V = g.V;
     const long long w = (long long)V * n;
     if (w <= (prec == WDIRAC_F64 ? 1 << 14 : 1 << 15)) return {kOrderSplit, 256, 1, 1};
-    if (prec == WDIRAC_F64 && V > 1 << 17) return {kOrderColumn, 256, 4, w >= 1 << 21 ? 2 : 1};
-    if (prec == WDIRAC_F32 && V >= 1 << 18) return {kOrderColumn, 256, w >= 1 << 21 ? 8 : 4, n > 1 ? 2 : 1};
-    if (prec == WDIRAC_F32 && rows == 2 && n >= 6 && V >= 1 << 16) return {kOrderStationary, kStationaryBlock, 1, 2};
+    // whether work-groups of `lanes` lanes keep three quarters of them busy
+    const auto full = [&](const TileMap &m, int lanes) { return 4LL * V >= 3LL * m.ntiles * lanes; };
+    const bool columns = full(make_tilemap(g, kOrderColumn, 64, 1), 64);
+    if (prec == WDIRAC_F64 && V > 1 << 17 && columns)
+        return {kOrderColumn, 256, 4, w >= 1 << 21 && full(make_tilemap(g, kOrderColumn, 256, 1), 256) ? 2 : 1};
+    if (prec == WDIRAC_F32 && V >= 1 << 18 && columns)
+        return {kOrderColumn, 256, w >= 1 << 21 ? 8 : 4, n > 1 ? 2 : 1};
+    if (prec == WDIRAC_F32 && rows == 2 && n >= 6 && V >= 1 << 16 &&
+        full(make_tilemap(g, kOrderZGroups, kStationaryBlock, 0), kStationaryBlock))
+        return {kOrderStationary, kStationaryBlock, 1, 2};
     return {kOrderTSweep, 256, 4, w > 1 << 17 ? 2 : 1};
 }
 
@@ -990,7 +1006,7 @@ hipError_t dslash_launch_batches(const dirac_batch *batches, int nbatch, int pre
     const Tuning tu = tuning_snapshot();
     LaunchCfg cfg{tu.order, tu.block, tu.tchunk, (prec >= 0 && prec < 3) ? tu.nr[prec] : 1};
     if (!tu.explicit_launch && !tuned_cfg(g, prec, total, d.rows, d.clover_compact, cfg))
-        cfg = default_cfg(g.V, prec, total, d.rows);
+        cfg = default_cfg(g, prec, total, d.rows);
     return dslash_launch_cfg(batches, nbatch, prec, dagger, d, g, apbc, persistent, cfg, st);
 }
 

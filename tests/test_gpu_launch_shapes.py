@@ -103,6 +103,31 @@ def test_untuned_apply_shapes(dims, n, prec, compress, ap, dagger):
         assert rel_l2(got[r], want) < TOL[prec], r
 
 
+# thin lattices: T-slices dealt in slabs (130 x 4^3 in slabs of eight, the last one shorter; 600 x 2^3; 90 x 5 x 6 x 7 by
+# slices of 210 in slabs of two), z-planes too few for the link-stationary kernel (64 x 4 x 16^2, FP32 of six), slices
+# too small for pairs of FP64 columns (512 x 8^3 of eight)
+@pytest.mark.parametrize("dims,n", [((130, 4, 4, 4), 5), ((600, 2, 2, 2), 8), ((90, 5, 6, 7), 3), ((64, 4, 16, 16), 6),
+                                    ((512, 8, 8, 8), 8)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("compress,ap,dagger", [(True, False, False), (False, True, True)])
+def test_untuned_apply_thin(dims, n, prec, compress, ap, dagger):
+    need_gpu()
+    U = synth.smooth_links(dims, 86, device="cuda").cpu().numpy()
+    op = DiracOp(dims, U, -0.3, 1.0, antiperiodic_t=ap, compress_links=compress, compress_clover=compress)
+    psi = synth.gaussian_spinor(dims, 87, nrhs=n, device="cuda")
+    x = op.pack(psi, prec)
+    out, one = op.empty(prec, n).zero_(), op.empty(prec, 1).zero_()
+    op.apply_native(out, x, n, prec, dagger)
+    op.apply_native(one, x[-op.field_bytes(prec, 1):], 1, prec, dagger)
+    assert torch.equal(one, out[-op.field_bytes(prec, 1):])
+    sites = synth.random_sites(dims, 64, 88)
+    got = op.unpack(out, prec, n)[:, torch.from_numpy(sites).cuda()].cpu().numpy()
+    for r in range(n):
+        want = oracle.dirac_apply_sites(dims, U, psi[r].cpu().numpy(), sites, -0.3, 1.0, antiperiodic_t=ap,
+                                        dagger=dagger)
+        assert rel_l2(got[r], want) < TOL[prec], r
+
+
 # counts that the register block does not divide, knobs set: the rest in the whole blocks' launch (9 in pairs; 5, 6, 7 in
 # fours), alone (3 in fours) and after a full table of 24 blocks (49 in pairs, 99 in fours); and more right-hand sides
 # than a table of the small-lattice kernel (26, neither tuned nor set)
