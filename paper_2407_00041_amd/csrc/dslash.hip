@@ -975,6 +975,9 @@ hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, b
 // pairs 445).  The link-stationary kernel (the site kernel's order and bits) takes six and more FP32 right-hand sides
 // between 16^4 and 2^18 sites: 12 at 16^4 67 -> 54; at 12^4 25 against 49.  Up to 2^14 site-right-hand-sides at FP64,
 // 2^15 else, the small-lattice kernel (measured there; same bits as the site kernel).
+// The FP64 site kernel takes three right-hand sides and, with full links, any odd count one per lane: the last of their
+// pairs shares no links (us, one per lane against pairs: 16^4 three 43 / 50, full links seven 99 / 122; 64 x 4 x 12^2 full
+// links five 54 / 63).
 // Thin lattices: columns and z-pairs only where the maps keep the lanes busy.  4096 x 4^3 has eight columns an XCD (FP64,
 // us, one right-hand side: columns 349, site kernel in slabs 95); 512 x 8^3 has 64, one wave of a work-group whose LDS is
 // for four, which pairs, one wave per SIMD, do not make up for (eight: pairs 967, one per lane 449); 64 x 4 x 16^2 has two
@@ -993,7 +996,8 @@ static LaunchCfg default_cfg(const Geom &g, int prec, int n, int rows) {
     if (prec == WDIRAC_F32 && rows == 2 && n >= 6 && V >= 1 << 16 &&
         full(make_tilemap(g, kOrderZGroups, kStationaryBlock, 0), kStationaryBlock))
         return {kOrderStationary, kStationaryBlock, 1, 2};
-    return {kOrderTSweep, 256, 4, w > 1 << 17 ? 2 : 1};
+    const bool lone = prec == WDIRAC_F64 && n % 2 && (n == 3 || rows == 3);
+    return {kOrderTSweep, 256, 4, w > 1 << 17 && !lone ? 2 : 1};
 }
 
 // The configuration of a launch: the autotuned one for this lattice,
