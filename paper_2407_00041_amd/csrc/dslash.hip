@@ -370,7 +370,11 @@ template <int P, int NR> constexpr int column_fence() {
     return P == WDIRAC_F64 ? (NR == 1 ? 2 : 4) : P == WDIRAC_F32 ? 4 : 8;
 }
 template <int P, int NR> constexpr int occupancy_col() { return NR == 1 ? 2 : 1; }
-
+// One FP32 right-hand side with two-row links: two hops between fences and three waves per SIMD at most.  Its registers
+// allow four, whose columns displace each other's neighbours from the L2; two are too few where the columns are just more
+// than two per SIMD (us, four hops and four waves, this, four hops and two waves: 48^3 x 96 T-chunk 2 1385 / 1348 / 1339,
+// 64 x 32^3 286 / 273 / 265, 48 x 24^3 82 / 84 / 93).  With full links it gains nothing (32^4 170 / 172 / 182).
+template <int P, int ROWS, int NR> constexpr bool column_few() { return P == WDIRAC_F32 && ROWS == 2 && NR == 1; }
 // column and T range of a lane of tile slot vb: the columns of XCD k's 1/8 of a slice (or of its patches), T-chunk tc;
 // -1: none
 __device__ __forceinline__ int tile_column(const TileMap &m, const Geom &g, int vb, int &t0, int &t1) {
@@ -396,7 +400,8 @@ __device__ __forceinline__ int tile_column(const TileMap &m, const Geom &g, int 
 }
 
 template <int P, bool DAG, int ROWS, int NR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(occupancy_col<P, NR>())))
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(occupancy_col<P, NR>(), column_few<P, ROWS, NR>() ? 3 : 8)))
 void dslash_column_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int apbc) {
     __shared__ cx<typename Store<P>::T> ut_lds[256][9];
     const int nitems = m.nslots * tab.nchunks;
@@ -407,7 +412,8 @@ void dslash_column_kernel(ChunkTable<NR> tab, OpData d, Geom g, TileMap m, int a
         int t0, t1;
         const int col = tile_column(m, g, vb, t0, t1);
         if (col >= 0)
-            column_sweep<P, DAG, ROWS, NR, column_fence<P, NR>()>(tab.c[c], d, g, col, t0, t1, apbc != 0, ut_lds);
+            column_sweep<P, DAG, ROWS, NR, column_few<P, ROWS, NR>() ? 2 : column_fence<P, NR>()>(
+                tab.c[c], d, g, col, t0, t1, apbc != 0, ut_lds);
     }
 }
 
