@@ -978,12 +978,16 @@ hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, b
 // together: FP64 walks columns from 2^17 sites on (the lanes fill the chip), FP32 from 2^18, FP16S never.  Pairs per
 // lane halve the waves: site kernel from 2^17 site-right-hand-sides (FP32 16^4, two: one per lane 12.9, four: pairs
 // 22.8; 8^4: pairs 11.9 against 8), FP64 columns from 2^21 (48 x 24^3, two: one per lane 307, pairs 316; 32^4, two:
-// pairs 445).  The link-stationary kernel (the site kernel's order and bits) takes six and more FP32 right-hand sides
+// pairs 445; three 64 x 32^3 1349 against 1360).  T-chunks of 8 for one or two FP32 right-hand sides from 2^21 on (32^4
+// one 119 against 134, two 200 against 206), else 4 (48 x 24^3 four 238 against 291).  The link-stationary kernel (the site kernel's order and bits) takes six and more FP32 right-hand sides
 // between 16^4 and 2^18 sites: 12 at 16^4 67 -> 54; at 12^4 25 against 49.  Up to 2^14 site-right-hand-sides at FP64,
 // 2^15 else, the small-lattice kernel (measured there; same bits as the site kernel).
-// The FP64 site kernel takes three right-hand sides and, with full links, any odd count one per lane: the last of their
-// pairs shares no links (us, one per lane against pairs: 16^4 three 43 / 50, full links seven 99 / 122; 64 x 4 x 12^2 full
-// links five 54 / 63).
+// The FP64 site kernel takes two or three right-hand sides and, with full links, any odd count one per lane (us, one per
+// lane against pairs: 16 x 12 x 24^2 two 55 / 58, 20 x 32 x 20 x 24 two 138 / 159; 16^4 three 43 / 50, full links seven
+// 99 / 122; 64 x 4 x 12^2 full links five 54 / 63).
+// Columns whose waves, four sites long, are just more than the chip's 1024 SIMDs leave half of them idle in the second
+// round: the site kernel then (us, site kernel against columns, 20 x 32 x 20 x 24, 1200 waves: FP64 one 84 / 91, full links
+// 98 / 113, FP32 full links one 47 / 56, four 125 / 142; 28 x 24^3, 1512: FP64 one 116 / 103, FP32 full links 65 / 61).
 // Thin lattices: columns and z-pairs only where the maps keep the lanes busy.  4096 x 4^3 has eight columns an XCD (FP64,
 // us, one right-hand side: columns 349, site kernel in slabs 95); 512 x 8^3 has 64, one wave of a work-group whose LDS is
 // for four, which pairs, one wave per SIMD, do not make up for (eight: pairs 967, one per lane 449); 64 x 4 x 16^2 has two
@@ -994,16 +998,18 @@ static LaunchCfg default_cfg(const Geom &g, int prec, int n, int rows) {
     if (w <= (prec == WDIRAC_F64 ? 1 << 14 : 1 << 15)) return {kOrderSplit, 256, 1, 1};
     // whether work-groups of `lanes` lanes keep three quarters of them busy
     const auto full = [&](const TileMap &m, int lanes) { return 4LL * V >= 3LL * m.ntiles * lanes; };
-    const bool columns = full(make_tilemap(g, kOrderColumn, 64, 1), 64);
+    const int waves = make_tilemap(g, kOrderColumn, 64, 4).ntiles;  // of columns, per right-hand side
+    const bool columns = full(make_tilemap(g, kOrderColumn, 64, 1), 64) && (waves <= 1024 || waves >= 1400);
     if (prec == WDIRAC_F64 && V > 1 << 17 && columns)
-        return {kOrderColumn, 256, 4, w >= 1 << 21 && full(make_tilemap(g, kOrderColumn, 256, 1), 256) ? 2 : 1};
+        return {kOrderColumn, 256, 4,
+                w >= (n == 3 ? 1 << 24 : 1 << 21) && full(make_tilemap(g, kOrderColumn, 256, 1), 256) ? 2 : 1};
     if (prec == WDIRAC_F32 && V >= 1 << 18 && columns)
-        return {kOrderColumn, 256, w >= 1 << 21 ? 8 : 4, n > 1 ? 2 : 1};
+        return {kOrderColumn, 256, w >= 1 << 21 && n < 3 ? 8 : 4, n > 1 ? 2 : 1};
     if (prec == WDIRAC_F32 && rows == 2 && n >= 6 && V >= 1 << 16 &&
         full(make_tilemap(g, kOrderZGroups, kStationaryBlock, 0), kStationaryBlock))
         return {kOrderStationary, kStationaryBlock, 1, 2};
-    const bool lone = prec == WDIRAC_F64 && n % 2 && (n == 3 || rows == 3);
-    return {kOrderTSweep, 256, 4, w > 1 << 17 && !lone ? 2 : 1};
+    const bool single = prec == WDIRAC_F64 && (n < 4 || (n % 2 && rows == 3));
+    return {kOrderTSweep, 256, 4, w > 1 << 17 && !single ? 2 : 1};
 }
 
 // The configuration of a launch: the autotuned one for this lattice,
