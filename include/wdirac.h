@@ -234,7 +234,9 @@ int dirac_tune_get(const char *key, int *value);
  * launch or groups of 4, 6, 8, 12 or 16 right-hand sides, over plane or
  * z-pair tiles), work-groups of 128/256,
  * T-chunks 2/4/8, register blocks 1/2/4 and, for several right-hand sides, a
- * persistent grid.  The choice is appended to the JSON-lines file named by
+ * persistent grid; and what an untuned launch takes, on small lattices the
+ * small-lattice kernel (reported as order 2, "split": 1 in the file; the
+ * knobs of dirac_tune_set do not select it).  The choice is appended to the JSON-lines file named by
  * the environment variable WDIRAC_TUNE_CACHE when it is set; that file is
  * read back the first time a configuration is looked up.  Synchronous;
  * allocates.

@@ -34,7 +34,8 @@ constexpr int kOrderZPlanes = 6;  // XCD k takes the (t, z) planes with z = k mo
 constexpr int kOrderZGroups = 7;  // link-stationary kernel only: as kOrderZPlanes over pairs of consecutive
                                   // z-planes, a work-group's two waves take the same 64 (y, x) sites of each;
                                   // optionally walked along T in (y, x) blocks of xyb tiles
-constexpr int kOrderSplit = 8;  // not a tile order: the small-lattice kernel (untuned launches only), T-slice tiles of 64
+constexpr int kOrderSplit = 8;  // not a tile order: the small-lattice kernel, T-slice tiles of 64 sites.  Not to be set; the
+                                // tuner reports it as kOrderTSweep, whose tiles and bits it has
 constexpr int kPatchX = 16, kPatchY = 4;  // patch extent in X and Y; Z extent = block / 64
 constexpr int kStationaryBlock = 128;     // work-group size of the link-stationary kernel (LDS budget)
 constexpr int kMaxStationaryRhs = 64;     // right-hand sides per link-stationary launch
@@ -70,6 +71,9 @@ struct LaunchCfg {
     int order, block, tchunk, nr;
     int persistent = 0;  // 1: a grid of the co-resident work-groups, each striding through the items
 };
+
+// The configuration of a launch that is neither tuned nor set (a rule on sizes, see dslash.hip)
+LaunchCfg untuned_cfg(const Geom &g, int prec, int n, int rows);
 
 // Autotuned configurations, keyed by lattice, precision, right-hand-side
 // bucket, link format and clover format (see tune.hip); returns false when

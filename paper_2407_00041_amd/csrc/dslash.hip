@@ -992,7 +992,7 @@ hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, b
 // us, one right-hand side: columns 349, site kernel in slabs 95); 512 x 8^3 has 64, one wave of a work-group whose LDS is
 // for four, which pairs, one wave per SIMD, do not make up for (eight: pairs 967, one per lane 449); 64 x 4 x 16^2 has two
 // z-pairs for eight XCDs (FP32 of eight: link-stationary 105, site kernel 52).
-static LaunchCfg default_cfg(const Geom &g, int prec, int n, int rows) {
+LaunchCfg untuned_cfg(const Geom &g, int prec, int n, int rows) {
     const int V = g.V;
     const long long w = (long long)V * n;
     if (w <= (prec == WDIRAC_F64 ? 1 << 14 : 1 << 15)) return {kOrderSplit, 256, 1, 1};
@@ -1022,7 +1022,7 @@ hipError_t dslash_launch_batches(const dirac_batch *batches, int nbatch, int pre
     const Tuning tu = tuning_snapshot();
     LaunchCfg cfg{tu.order, tu.block, tu.tchunk, (prec >= 0 && prec < 3) ? tu.nr[prec] : 1};
     if (!tu.explicit_launch && !tuned_cfg(g, prec, total, d.rows, d.clover_compact, cfg))
-        cfg = default_cfg(g, prec, total, d.rows);
+        cfg = untuned_cfg(g, prec, total, d.rows);
     return dslash_launch_cfg(batches, nbatch, prec, dagger, d, g, apbc, persistent, cfg, st);
 }
 

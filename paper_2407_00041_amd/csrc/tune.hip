@@ -4,7 +4,8 @@
 // a small set of candidate configurations (tile order including the lattice
 // order without XCD remapping, work-group size, T-chunk of the column sweep,
 // register block, persistent grid; for the link-stationary kernel the
-// right-hand sides per launch and the plane or z-pair tile shape) with HIP
+// right-hand sides per launch and the plane or z-pair tile shape; and what an
+// untuned launch would take, so that tuning does not make one slower) with HIP
 // events on temporary buffers and keeps the fastest.  Choices are stored per (lattice extents,
 // precision, right-hand-side bucket, link format, clover format) and used by
 // every later launch with that key; they can be appended to a JSON-lines cache file
@@ -12,6 +13,7 @@
 // time a key is looked up in a new process.
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <string>
@@ -56,8 +58,10 @@ void load_cache_locked() {
                    "\"persistent\": %d, \"us\": %lf",
                    key, &c.order, &c.block, &c.tchunk, &c.nr, &c.persistent, &us) == 7) {
             if (c.order >= 0 && c.order <= 6 && c.block >= 64 && c.block <= 256 && c.block % 64 == 0 &&
-                c.tchunk >= 1 && (c.nr == 1 || c.nr == 2 || c.nr == 4) && (c.persistent == 0 || c.persistent == 1))
+                c.tchunk >= 1 && (c.nr == 1 || c.nr == 2 || c.nr == 4) && (c.persistent == 0 || c.persistent == 1)) {
+                if (c.order == kOrderTSweep && strstr(line, "\"split\": 1")) c.order = kOrderSplit;
                 g_table[key] = c;
+            }
         }
     }
     fclose(f);
@@ -96,7 +100,7 @@ extern "C" int dirac_autotune(const dirac_op *op, int prec, int nrhs, int cfg_ou
         return fail(WDIRAC_ENOMEM, "autotune buffers");
     }
     int rc = WDIRAC_OK;
-    std::vector<LaunchCfg> cands;
+    std::vector<LaunchCfg> cands{untuned_cfg(op->g, prec, nrhs, op->link_rows)};
     const int nrs[3] = {1, 2, 4};
     if (prec != WDIRAC_F64 && op->link_rows == 2 && nrhs > 1)  // all right-hand sides per launch, or groups;
         for (int zw : {1, 2, 4})                 // plane tiles, z-pair tiles, z-pair tiles in (y, x) blocks
@@ -133,7 +137,8 @@ extern "C" int dirac_autotune(const dirac_op *op, int prec, int nrhs, int cfg_ou
             rc = fail(WDIRAC_EHIP, "autotune setup");
             break;
         }
-        const int reps = nrhs > 8 ? 2 : 3;
+        // launches of a few microseconds are told apart by several of them
+        const int reps = (long long)op->g.V * nrhs <= 1 << 17 ? 20 : nrhs > 8 ? 2 : 3;
         for (const LaunchCfg &c : cands) {
             hipError_t e = dslash_launch_cfg(&b, 1, prec, false, op->data(prec), op->g, apbc, false, c, st);
             if (e == hipSuccess) e = hipEventRecord(e0, st);
@@ -160,6 +165,8 @@ extern "C" int dirac_autotune(const dirac_op *op, int prec, int nrhs, int cfg_ou
     (void)hipFree(out);
     if (rc) return rc;
     const std::string key = key_of(op->g, prec, nrhs, op->link_rows, op->clover_compact ? 1 : 0);
+    const bool split = best.order == kOrderSplit;
+    const int order = split ? kOrderTSweep : best.order;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         load_cache_locked();
@@ -168,14 +175,15 @@ extern "C" int dirac_autotune(const dirac_op *op, int prec, int nrhs, int cfg_ou
             if (FILE *f = fopen(path, "a")) {
                 fprintf(f,
                         "{\"key\": \"%s\", \"order\": %d, \"block\": %d, \"tchunk\": %d, \"nr\": %d, "
-                        "\"persistent\": %d, \"us\": %.1f}\n",
-                        key.c_str(), best.order, best.block, best.tchunk, best.nr, best.persistent, best_ms * 1000.0);
+                        "\"persistent\": %d, \"us\": %.1f%s}\n",
+                        key.c_str(), order, best.block, best.tchunk, best.nr, best.persistent, best_ms * 1000.0,
+                        split ? ", \"split\": 1" : "");
                 fclose(f);
             }
         }
     }
     if (cfg_out) {
-        cfg_out[0] = best.order;
+        cfg_out[0] = order;
         cfg_out[1] = best.block;
         cfg_out[2] = best.tchunk;
         cfg_out[3] = best.nr;

@@ -3,6 +3,9 @@ still match the oracle, the cache file records them, and the full-size
 lattice in the benchmark's configuration (two-row links, autotuned launch)
 agrees with the oracle at sampled sites."""
 import json
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -103,3 +106,51 @@ def test_full_size_batched_launch(clean_table):
     tune_set("order", saved_order)
     del op, nat
     torch.cuda.empty_cache()
+
+
+def test_autotune_knows_the_small_lattice_kernel(clean_table, tmp_path, monkeypatch):
+    """8^4 in FP64: the four-wave kernel of untuned launches (6.3 us against the site kernel's 7.8) is a candidate, is
+    reported as tile order 2 and marked in the cache file; its results equal the site kernel's bit for bit."""
+    cache = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("WDIRAC_TUNE_CACHE", str(cache))
+    dims = (8, 8, 8, 8)
+    U, psi = fields(dims, 14, nrhs=1)
+    op = DiracOp(dims, U, -0.3, 1.0, antiperiodic_t=True)
+    cfg = op.autotune("f64", 1)
+    assert cfg["order"] == 2 and cfg["nr"] == 1 and cfg["persistent"] == 0
+    line = json.loads(cache.read_text().splitlines()[-1])
+    assert line["order"] == 2 and line["split"] == 1
+    x = op.pack(to_dev(psi), "f64")
+    tuned, site = (op.empty("f64", 1).zero_() for _ in range(2))
+    op.apply_native(tuned, x, 1, "f64")
+    order = tune_get("order")
+    tune_set("order", 2)
+    op.apply_native(site, x, 1, "f64")
+    tune_set("order", order)
+    tune_set("explicit", 0)
+    assert torch.equal(tuned, site)
+    want = oracle.dirac_apply(dims, U, psi, -0.3, 1.0, antiperiodic_t=True)
+    assert rel_l2(op.unpack(tuned, "f64", 1).cpu().numpy()[0], want[0]) < TOL["f64"]
+
+
+def test_cache_file_with_the_small_lattice_kernel_is_read(tmp_path):
+    """A new process reads the marked line, and a line of a file written before there was a mark."""
+    cache = tmp_path / "tune.jsonl"
+    line = {"key": "gfx950|4x4x4x4|p0|b0|r3|c0", "order": 2, "block": 256, "tchunk": 1, "nr": 1, "persistent": 0,
+            "us": 6.3}
+    old = dict(line, key="gfx950|4x4x4x4|p1|b0|r3|c0", order=3)
+    cache.write_text(json.dumps(dict(line, split=1)) + "\n" + json.dumps(old) + "\n")
+    code = """
+import numpy as np, torch, oracle
+from paper_2407_00041_amd import DiracOp
+from util import TOL, fields, rel_l2, to_dev
+U, psi = fields((4, 4, 4, 4), 15, nrhs=1)
+op = DiracOp((4, 4, 4, 4), U, -0.3, 1.0)
+want = oracle.dirac_apply((4, 4, 4, 4), U, psi, -0.3, 1.0)
+for p in ("f64", "f32"):
+    assert rel_l2(op.apply(to_dev(psi), p).cpu().numpy()[0], want[0]) < TOL[p]
+"""
+    need_gpu()
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    env = dict(os.environ, WDIRAC_TUNE_CACHE=str(cache), PYTHONPATH=os.pathsep.join([root, os.path.join(root, "tests")]))
+    subprocess.run([sys.executable, "-c", code], check=True, env=env, timeout=100)
