@@ -9,8 +9,8 @@
 //
 // Reductions are deterministic: a fixed grid of kRedBlocks work-groups, each
 // thread summing a fixed strided subset, group_sums per work-group, then one
-// work-group per output summing the per-group partials in order.  No
-// floating-point atomics.  (With an LDS tree over the work-group's 9 x 256
+// work-group per output summing the per-group partials the same way, in a fixed
+// order.  No floating-point atomics.  (With an LDS tree over the work-group's 9 x 256
 // values the inner products of one vector took 25 us at 16^4, mostly the tree;
 // now 8.)
 #include "blas.h"
@@ -27,14 +27,7 @@ __device__ __forceinline__ double2 cj_mul(double2 a, double2 b) {  // conj(a) b
     return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
 
-// Inner products of w with up to kGS basis vectors in ONE launch.  The grid
-// is (vector group of kMdot, element chunk) work-groups, dealt so that the
-// groups of one chunk are consecutive work-groups of the same XCD (the
-// hardware hands work-groups to the 8 XCDs round-robin): after the first
-// group, a chunk of w comes from that XCD's L2, so w crosses HBM about once
-// whatever the number of vectors.  partial[(chunk * ngroups + group) *
-// (kMdot + 1) + i] = sum conj(v_{kMdot group + i}) w over the chunk; column
-// kMdot of group 0 holds sum |w|^2.
+// a work-group's share of NV inner products and of |w|^2
 template <typename S, int NV>
 __device__ __forceinline__ void mdot_chunk(const VecList &vl, int i0, const S *__restrict__ w, long long e0,
                                            long long stride, long long N, double2 (&acc)[kMdot + 1]) {
@@ -89,7 +82,8 @@ __global__ __launch_bounds__(kRedThreads) void k_mdot_all(VecList vl, const S *_
         reinterpret_cast<double *>(partial + ((size_t)chunk * ngroups + group) * (kMdot + 1))[threadIdx.x] = t;
 }
 
-// Per work-group sum of entry `at` of n rows of `stride` entries, rows in order; thread 0 gets it
+// Work-group's sum of the first entries of n rows of `stride` entries each (a fixed order: strided over the threads,
+// then group_sums); thread 0 gets it
 __device__ __forceinline__ double2 sum_rows(const double2 *__restrict__ partial, int n, size_t stride, double *lds) {
     double v[2] = {0.0, 0.0};
     for (int c = threadIdx.x; c < n; c += blockDim.x) {
@@ -102,7 +96,7 @@ __device__ __forceinline__ double2 sum_rows(const double2 *__restrict__ partial,
 }
 
 // out[i] (i < nv) = sum over chunks of the inner-product partials of vector i, out[nv].x = |w|^2; one work-group
-// per output, chunks summed in order; scaled and host as in mdot_all
+// per output (sum_rows); scaled and host as in mdot_all
 __global__ __launch_bounds__(kRedThreads) void k_colsum_groups(const double2 *__restrict__ partial, int nchunks,
                                                                 int ngroups, int nv, double2 *__restrict__ out,
                                                                 ScaleList sl, double2 *__restrict__ scaled,

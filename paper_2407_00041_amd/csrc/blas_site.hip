@@ -15,7 +15,7 @@
 // Reductions are deterministic: a fixed grid of at most kRedBlocks work-groups
 // per right-hand side, each thread summing a fixed strided subset of sites,
 // group_sums per work-group; the inner cycle's state kernels add the per-group
-// partials in order.
+// partials in a fixed order.
 #include "blas.h"
 #include "spinor_io.h"
 

@@ -975,7 +975,7 @@ hipError_t dslash_launch_cfg(const dirac_batch *batches, int nbatch, int prec, b
 //   FP16S 4 RHS  site 18 / 62 / 149 / 232 / 460    column 21 / 62 / 154 / 245 / 477
 // The column sweep adds the hops in another order, so its last bits differ from the site kernel's; the choice between
 // the two goes by the lattice alone, so that a result does not depend on how many right-hand sides are applied
-// together: FP64 walks columns from 2^17 sites on (the lanes fill the chip), FP32 from 2^18, FP16S never.  Pairs per
+// together: FP64 walks columns past 2^17 sites (the lanes fill the chip), FP32 from 2^18, FP16S never.  Pairs per
 // lane halve the waves: site kernel from 2^17 site-right-hand-sides (FP32 16^4, two: one per lane 12.9, four: pairs
 // 22.8; 8^4: pairs 11.9 against 8), FP64 columns from 2^21 (48 x 24^3, two: one per lane 307, pairs 316; 32^4, two:
 // pairs 445; three 64 x 32^3 1349 against 1360).  T-chunks of 8 for one or two FP32 right-hand sides from 2^21 on (32^4

@@ -65,8 +65,6 @@ namespace {
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
-static_assert(kGSSite <= kMdot, "partial sums of a pass are laid out kMdot + 1 wide");
-
 // Device-side state of one right-hand side's inner GMRES cycle (carved from
 // its scalar block).
 struct InnerDev {

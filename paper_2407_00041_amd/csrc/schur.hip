@@ -55,7 +55,7 @@ __device__ __forceinline__ int parity_site(const Geom &g, int i, int p, int c[4]
 //    748 -> 619, FP16S pair 335 -> 308, FP16S single 213 -> 200; FP64 pair (column walk) 1403 -> 1380.  A fence
 //    every 8 hops spills in pairs and is slower.
 //  - right-hand sides of one tile run one after the other on the same XCD, so links and A come from its L2: four
-//    right-hand sides, pairs, FP64 2840 -> 2301, FP32 1495 -> 1150, FP16S 655 -> 578.
+//    right-hand sides, pairs, FP64 2840 -> 2301, FP32 1495 -> 1150.
 //  - right-hand sides per lane: a pair shares its links and A in registers, but halves the waves; below 2^18
 //    site-right-hand-sides (a few waves per SIMD) one per lane is faster: FP64 16^4, two: 47 -> 43; 8^4, two:
 //    25 -> 17; FP16S 16^4, two: 23 -> 17, four: 25 -> 23; above it pairs are: FP16S 32 x 16^2 x 32, two: 49 -> 43.
