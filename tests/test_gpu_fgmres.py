@@ -294,3 +294,22 @@ def test_create_rejects_nonfinite_links_and_clover():
     with pytest.raises(WdiracError) as e:
         DiracOp(dims, U, -0.3, 1.0, clover=C, precisions=("f64",))
     assert e.value.code == -1 and "NaN or Inf" in str(e.value)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_many_right_hand_sides_in_one_wave(graph):
+    """Nineteen right-hand sides in one wave: the inner cycle's kernels take sixteen per launch, its inner products two
+    passes of eight vectors; each solution and count equals that of a solve of its own."""
+    need_gpu()
+    dims, n = (2, 4, 2, 4), 19
+    U, b, op, bn = setup(dims, 15, -0.2, 1.0, nrhs=n)
+    kw = dict(restart=4, tol=1e-9, maxit=200, mode="mixed_f32", inner_restart=14, inner_tol=1e-3, inner_maxit=14,
+              graph=graph)
+    x, st, rc = op.solve(bn, nrhs=n, wave=n, **kw)
+    assert rc == 0 and all(s["wave"] == n for s in st)
+    rb = op.field_bytes("f64", 1)
+    for r in range(n):
+        xr, sr, _ = op.solve(bn[r * rb:(r + 1) * rb], nrhs=1, **kw)
+        assert torch.equal(x[r * rb:(r + 1) * rb], xr), r
+        assert (sr[0]["applies"], sr[0]["inner_applies"]) == (st[r]["applies"], st[r]["inner_applies"]), r
+    assert max(s["inner_applies"] for s in st) > 8 and all(s["converged"] for s in st)
