@@ -31,8 +31,9 @@ class DiracApply(torch.autograd.Function):
         nrhs = x.numel() // (12 * op.V)
         gn = op.pack(g.reshape(nrhs, op.V, 12), "f64")  # for both gradients
         if ctx.needs_input_grad[0]:
-            y = op.empty("f64", nrhs, g.device)
-            gx = op.unpack(op.apply_native(y, gn, nrhs, "f64", True), "f64", nrhs).reshape(g.shape)
+            # the native D^H g is not kept past its unpacking
+            gx = op.unpack(op.apply_native(op.empty("f64", nrhs, g.device), gn, nrhs, "f64", True), "f64",
+                           nrhs).reshape(g.shape)
         if ctx.needs_input_grad[1]:
             xn = op.pack(x.reshape(nrhs, op.V, 12), "f64")
             gU = op.force(gn, xn, nrhs, raw=True)

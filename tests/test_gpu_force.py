@@ -130,3 +130,22 @@ def test_force_workspace_size_and_rejection():
     assert rc == 0
     torch.cuda.synchronize()
     assert torch.equal(out, G0)
+
+
+def test_backward_holds_no_spent_field(monkeypatch):
+    """While dL/dU is formed, of the native fields only the packed cotangent and the packed x are alive beside dL/dx."""
+    need_gpu()
+    dims = (8, 8, 8, 16)
+    U = synth.smooth_links(dims, 21, device="cuda")
+    op = DiracOp(dims, U.cpu().numpy(), -0.3, 1.0, precisions=("f64",))
+    x = synth.gaussian_spinor(dims, 22, nrhs=1, device="cuda").requires_grad_()
+    Ug = U.clone().requires_grad_()
+    g = synth.gaussian_spinor(dims, 23, nrhs=1, device="cuda")
+    seen = []
+    force = op.force
+    monkeypatch.setattr(op, "force", lambda *a, **k: (seen.append(torch.cuda.memory_allocated()), force(*a, **k))[1])
+    y = dirac_apply(x, Ug, dims, op=op)
+    before = torch.cuda.memory_allocated()
+    torch.autograd.grad(y, (x, Ug), g)
+    field = op.field_bytes("f64", 1)
+    assert seen[0] - before < 3.5 * field, (seen[0] - before) / field
