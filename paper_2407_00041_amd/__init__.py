@@ -117,7 +117,7 @@ class DiracOp:
     def pack(self, canonical: torch.Tensor, prec="f64", out: torch.Tensor | None = None,
              stream=None) -> torch.Tensor:
         """canonical [nrhs, V, 12] (or [V, 12]) complex128 on the device -> native."""
-        c = canonical.contiguous()
+        c = canonical.resolve_conj().contiguous()  # a lazily conjugated view by its values
         assert c.dtype == torch.complex128 and c.is_cuda
         nrhs = c.numel() // (12 * self.V)
         assert nrhs * 12 * self.V == c.numel()
@@ -361,19 +361,19 @@ class TwoLevel:
 
     def prolong(self, coarse: torch.Tensor, nrhs: int = 1, stream=None) -> torch.Tensor:
         out = self.op.empty("f64", nrhs, coarse.device)
-        check(self.lib.dirac_amg_prolong(self.handle, _ptr(out), _ptr(coarse.contiguous()), int(nrhs),
+        check(self.lib.dirac_amg_prolong(self.handle, _ptr(out), _ptr(coarse.resolve_conj().contiguous()), int(nrhs),
                                          _stream(stream)), "dirac_amg_prolong")
         return out
 
     def coarse_apply(self, coarse: torch.Tensor, nrhs: int = 1, stream=None) -> torch.Tensor:
-        x = coarse.contiguous()
+        x = coarse.resolve_conj().contiguous()
         out = torch.empty_like(x)
         check(self.lib.dirac_amg_coarse_apply(self.handle, _ptr(out), _ptr(x), int(nrhs), _stream(stream)),
               "dirac_amg_coarse_apply")
         return out
 
     def coarse_solve(self, b: torch.Tensor, stream=None):
-        bb = b.contiguous()
+        bb = b.resolve_conj().contiguous()
         x = torch.empty_like(bb)
         it = ctypes.c_longlong()
         check(self.lib.dirac_amg_coarse_solve(self.handle, _ptr(x), _ptr(bb), ctypes.byref(it), _stream(stream)),
@@ -417,7 +417,7 @@ TUNE_KEYS = ("block", "order", "tchunk", "persistent_blocks", "nr_f64", "nr_f32"
 def clover_term(dims, links_dev: torch.Tensor, stream=None) -> torch.Tensor:
     """Unit-c_sw clover term [V, 42] c128 built on the device from device links."""
     lib = _lib.load()
-    L = links_dev.contiguous()
+    L = links_dev.resolve_conj().contiguous()
     assert L.dtype == torch.complex128 and L.is_cuda
     V = int(np.prod(dims))
     out = torch.empty((V, 42), dtype=torch.complex128, device=L.device)

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from paper_2407_00041_amd import DiracOp, synth
+from paper_2407_00041_amd import DiracOp, clover_term, synth
 from paper_2407_00041_amd.autograd import dirac_apply
 from util import need_gpu, rel_l2, to_dev
 
@@ -149,3 +149,24 @@ def test_backward_holds_no_spent_field(monkeypatch):
     torch.autograd.grad(y, (x, Ug), g)
     field = op.field_bytes("f64", 1)
     assert seen[0] - before < 3.5 * field, (seen[0] - before) / field
+
+
+def test_conjugate_views_are_taken_by_value():
+    """A lazily conjugated tensor (torch's conj(), which also hands such cotangents to backward) is packed conjugated."""
+    need_gpu()
+    dims = (4, 4, 2, 6)
+    U = synth.smooth_links(dims, 31).numpy()
+    op = DiracOp(dims, U, -0.3, 1.0, precisions=("f64",))
+    x = synth.gaussian_spinor(dims, 32, nrhs=1, device="cuda")
+    v = x.conj()
+    assert v.is_conj() and torch.equal(op.pack(v), op.pack(x.conj_physical()))
+    Ud = to_dev(U)
+    assert torch.equal(clover_term(dims, Ud.conj()), clover_term(dims, Ud.conj_physical()))
+    w = synth.gaussian_spinor(dims, 33, nrhs=1, device="cuda")
+    grads = []
+    for conj in (torch.conj, torch.conj_physical):
+        xi = x.clone().requires_grad_()
+        (conj(dirac_apply(xi, to_dev(U), dims, op=op)) * w).sum().real.backward()
+        grads.append(xi.grad)
+    assert torch.equal(*grads)
+    assert rel_l2(grads[0].cpu().numpy(), op.apply(w, "f64", dagger=True).cpu().numpy()) < 1e-13
