@@ -335,8 +335,8 @@ template <int N, int NR> __device__ __forceinline__ Chunk<N> sub_chunk(const Chu
 }
 
 // dslash_kernel with a last register block of `rest` < NR right-hand sides, tab.c[tab.nchunks].  As launches of their own
-// the last few left most of the chip idle (us, three right-hand sides, 16^4 FP32 25.4 -> 18.5, 24 x 16^2 x 24 FP32 59.9
-// -> 51.4; seven at 12^4 FP64 43 -> 31).  FP64 and FP32 take it in its tile's turn (after all whole blocks: 51.4 -> 61.1),
+// the last few left most of the chip idle (us, three right-hand sides, 16^4 FP32 25.6 -> 18.1, 24 x 16^2 x 24 FP32 59.5
+// -> 51.3; seven at 12^4 FP64 43 -> 31).  FP64 and FP32 take it in its tile's turn (after all whole blocks: 51.4 -> 61.1),
 // FP16S after all whole blocks (32^4, three: 183, in turn 200).  A kernel of its own, since the second path would change
 // the whole blocks' registers.
 template <int P, bool DAG, int ROWS, int NR>
@@ -998,12 +998,14 @@ LaunchCfg untuned_cfg(const Geom &g, int prec, int n, int rows) {
     if (w <= (prec == WDIRAC_F64 ? 1 << 14 : 1 << 15)) return {kOrderSplit, 256, 1, 1};
     // whether work-groups of `lanes` lanes keep three quarters of them busy
     const auto full = [&](const TileMap &m, int lanes) { return 4LL * V >= 3LL * m.ntiles * lanes; };
-    const int waves = make_tilemap(g, kOrderColumn, 64, 4).ntiles;  // of columns, per right-hand side
-    const bool columns = full(make_tilemap(g, kOrderColumn, 64, 1), 64) && (waves <= 1024 || waves >= 1400);
-    if (prec == WDIRAC_F64 && V > 1 << 17 && columns)
+    const auto columns = [&] {
+        const int waves = make_tilemap(g, kOrderColumn, 64, 4).ntiles;  // per right-hand side
+        return full(make_tilemap(g, kOrderColumn, 64, 1), 64) && (waves <= 1024 || waves >= 1400);
+    };
+    if (prec == WDIRAC_F64 && V > 1 << 17 && columns())
         return {kOrderColumn, 256, 4,
                 w >= (n == 3 ? 1 << 24 : 1 << 21) && full(make_tilemap(g, kOrderColumn, 256, 1), 256) ? 2 : 1};
-    if (prec == WDIRAC_F32 && V >= 1 << 18 && columns)
+    if (prec == WDIRAC_F32 && V >= 1 << 18 && columns())
         return {kOrderColumn, 256, w >= 1 << 21 && n < 3 ? 8 : 4, n > 1 ? 2 : 1};
     if (prec == WDIRAC_F32 && rows == 2 && n >= 6 && V >= 1 << 16 &&
         full(make_tilemap(g, kOrderZGroups, kStationaryBlock, 0), kStationaryBlock))

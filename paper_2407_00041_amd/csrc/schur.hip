@@ -374,10 +374,11 @@ __device__ __forceinline__ void parity_column_apply(const ParityTable &tab, cons
     }
 }
 
-template <int P, bool DAG, int SELF, bool INV, int ROWS, int NR, bool LONE>
+template <int P, bool DAG, int SELF, bool HOP, bool INV, int ROWS, int NR, bool LONE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void parity_column_kernel(ParityTable tab, OpData d, const void *cinv, Geom g, int parity, int apbc,
                           typename Store<P>::T fh, int tpr) {
+    static_assert(HOP, "the column walk carries T hops");
     const int C = g.stride[0];
     int col, t0, r0;
     {
@@ -412,10 +413,10 @@ hipError_t launch_nr(const dirac_op *op, int parity, const ParityTable &tab, dou
             const int tpc = ((g.stride[0] + 7) / 8 + 255) / 256;
             const dim3 grid((g.n[0] + kParChunk - 1) / kParChunk * 8 * tpc * ((tab.n + NR - 1) / NR));
             if (rows2)
-                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, INV, 2, NR, LONE>), grid, dim3(256), 0, st, tab,
+                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 2, NR, LONE>), grid, dim3(256), 0, st, tab,
                                    op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
             else
-                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, INV, 3, NR, LONE>), grid, dim3(256), 0, st, tab,
+                hipLaunchKernelGGL((parity_column_kernel<P, DAG, SELF, HOP, INV, 3, NR, LONE>), grid, dim3(256), 0, st, tab,
                                    op->data(P), op->cinv(P), g, parity, apbc, (T)fh, tpc);
             return hipGetLastError();
         }
