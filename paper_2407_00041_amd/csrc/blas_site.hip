@@ -80,7 +80,8 @@ __global__ __launch_bounds__(kRedThreads) void k_site_mdot(SiteBatch b, int i0, 
                 acc[2 * i] += vv[k].x * wv[k].x + vv[k].y * wv[k].y;
                 acc[2 * i + 1] += vv[k].x * wv[k].y - vv[k].y * wv[k].x;
             }
-            // one vector's loads behind the last one's sums: 48^3 x 96 FP16S 706 -> 568 us per pass (every two: 634)
+            // one vector's loads behind the last one's sums: 48^3 x 96 FP16S 706 -> 568 us per pass (every two: 634);
+            // without it whole mixed solves from 8^4 to 48 x 24^3 are 1-8 % slower at FP16S, 0-4 % at FP32
             asm volatile("" : "+v"(acc[2 * i]), "+v"(acc[2 * i + 1]) : : "memory");
             __builtin_amdgcn_sched_barrier(0);
         }
